@@ -59,11 +59,15 @@ double region_size(const vlc_shape& s) {
 
 // Workspace layout: [partial row statistics][3 arrays of B L Hq tau floats: two hold the row max and row sum of a
 // standalone vlc_sparsity sweep]
-struct WsPlan { size_t part, stats, total; bool mfma; };
+enum class Sweeps { kSimple, kMfma, kWave };
+struct WsPlan { size_t part, stats, total; Sweeps route; };
 
 WsPlan ws_plan(const vlc_shape& s) {
     WsPlan w;
-    w.mfma = vlc::score_mfma_supported(s) && !(s.flags & VLC_SHAPE_SCORE_PLAIN_ALU);
+    w.route = (s.flags & VLC_SHAPE_SCORE_PLAIN_ALU) ? Sweeps::kSimple
+              : vlc::score_mfma_supported(s)        ? Sweeps::kMfma
+              : vlc::score_wave_supported(s)        ? Sweeps::kWave
+                                                    : Sweeps::kSimple;
     const size_t a = vlc::score_simple_workspace_bytes(s), b = vlc::score_mfma_workspace_bytes(s);
     w.part = align_up(a > b ? a : b, 256);
     w.stats = align_up((size_t)s.B * s.L * s.Hq * s.tau * sizeof(float), 256);
@@ -106,11 +110,13 @@ vlc_status static_scratch(void** out) {
     return VLC_OK;
 }
 
-hipError_t run_rowstats(const vlc::ScoreArgs& a, bool mfma) {
-    return mfma ? vlc::launch_rowstats_mfma(a) : vlc::launch_rowstats_simple(a);
+hipError_t run_rowstats(const vlc::ScoreArgs& a, Sweeps route) {
+    return route == Sweeps::kMfma ? vlc::launch_rowstats_mfma(a) : route == Sweeps::kWave ? vlc::launch_rowstats_wave(a) : vlc::launch_rowstats_simple(a);
 }
-hipError_t run_colsweep(const vlc::ScoreArgs& a, bool mfma, bool after_rowstats) {
-    return mfma ? vlc::launch_colsweep_mfma(a, after_rowstats) : vlc::launch_colsweep_simple(a);
+hipError_t run_colsweep(const vlc::ScoreArgs& a, Sweeps route, bool after_rowstats) {
+    return route == Sweeps::kMfma   ? vlc::launch_colsweep_mfma(a, after_rowstats)
+           : route == Sweeps::kWave ? vlc::launch_colsweep_wave(a, after_rowstats)
+                                    : vlc::launch_colsweep_simple(a);
 }
 
 }  // namespace
@@ -135,10 +141,10 @@ vlc_status vlc_score(const vlc_shape* shape, const void* q_win, const void* k, c
     if (workspace_bytes < vlc_workspace_bytes(shape))
         return fail(VLC_ERR_CAPACITY, "vlc_score: workspace of %zu bytes, %zu needed", workspace_bytes, vlc_workspace_bytes(shape));
     vlc::ScoreArgs a = score_args(shape, q_win, k, sm_scale, p, scores, row_max, row_sum, nnz, workspace, stream);
-    const bool mfma = ws_plan(*shape).mfma;
-    hipError_t e = run_rowstats(a, mfma);
+    const Sweeps route = ws_plan(*shape).route;
+    hipError_t e = run_rowstats(a, route);
     if (e != hipSuccess) return hip_fail(e, "vlc_score row statistics");
-    e = run_colsweep(a, mfma, true);              // the counters were zeroed by the row-statistics sweep
+    e = run_colsweep(a, route, true);              // the counters were zeroed by the row-statistics sweep
     if (e != hipSuccess) return hip_fail(e, "vlc_score column sweep");
     return VLC_OK;
 }
@@ -160,9 +166,9 @@ vlc_status vlc_score_static(const vlc_shape* shape, const void* q_win, const voi
     // Every partial the column sweep reads is written by the row-statistics sweep of the same call, so
     // what an earlier call left in the array is never seen and nothing has to be cleared.
     vlc::ScoreArgs a = score_args(shape, q_win, k, sm_scale, p, scores, row_max, row_sum, nnz, ws, stream);
-    hipError_t e = run_rowstats(a, wp.mfma);
+    hipError_t e = run_rowstats(a, wp.route);
     if (e != hipSuccess) return hip_fail(e, "vlc_score_static row statistics");
-    e = run_colsweep(a, wp.mfma, true);
+    e = run_colsweep(a, wp.route, true);
     if (e != hipSuccess) return hip_fail(e, "vlc_score_static column sweep");
     return VLC_OK;
 }
@@ -187,7 +193,7 @@ vlc_status vlc_sparsity(const vlc_shape* shape, const void* q_win, const void* k
             char* tail = (char*)workspace + wp.part + wp.stats;
             a.row_max = (float*)tail;
             a.row_sum = (float*)(tail + wp.stats);
-            hipError_t e = run_rowstats(a, wp.mfma);
+            hipError_t e = run_rowstats(a, wp.route);
             if (e != hipSuccess) return hip_fail(e, "vlc_sparsity row statistics");
             a.row_sum = nullptr;
             have_t = true;                          // that pass also zeroed the counters
@@ -195,7 +201,7 @@ vlc_status vlc_sparsity(const vlc_shape* shape, const void* q_win, const void* k
         hipError_t e = hipSuccess;
         if (!have_t) e = vlc::launch_fill_u64(nnz, (size_t)shape->B * shape->L * shape->Hq, 0, hs);
         if (e != hipSuccess) return hip_fail(e, "vlc_sparsity clear counts");
-        e = run_colsweep(a, wp.mfma, have_t);
+        e = run_colsweep(a, wp.route, have_t);
         if (e != hipSuccess) return hip_fail(e, "vlc_sparsity count sweep");
     }
     if (gamma) {
@@ -252,7 +258,7 @@ vlc_status vlc_score_from_stats(const vlc_shape* shape, const void* q_win, const
     hipError_t e = hipSuccess;
     if (nnz) e = vlc::launch_fill_u64(nnz, (size_t)shape->B * shape->L * shape->Hq, 0, a.stream);
     if (e != hipSuccess) return hip_fail(e, "vlc_score_from_stats clear counts");
-    e = run_colsweep(a, ws_plan(*shape).mfma, false);
+    e = run_colsweep(a, ws_plan(*shape).route, false);
     if (e != hipSuccess) return hip_fail(e, "vlc_score_from_stats column sweep");
     return VLC_OK;
 }

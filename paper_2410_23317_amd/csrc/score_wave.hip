@@ -1,0 +1,452 @@
+// Scoring sweeps on the matrix cores for bf16 storage with d = 64 and for fp32 storage (gfx950;
+// v_mfma_f32_32x32x16_bf16, v_mfma_f32_32x32x2_f32).  bf16 with d = 128 has kernels of its own (score_mfma.hip).
+//
+// The same two sweeps (App. A.3) with another division of the work: the block's Q' rows are put into LDS once (they
+// are few and serve the whole sweep), and every wave walks 32-key tiles of its own, K fragments straight from memory
+// into registers, each tile multiplied with all 32-row blocks of the window.  The loop over the keys holds no barrier,
+// so the waves of a SIMD drift apart and one's products run under another's exponentials; the next tile's K is
+// requested into the same registers as soon as the last row block's products are issued.
+// In both sweeps a tile is S^T = K Q'^T: the 16 values a lane holds belong to ONE query row, whose constants are then
+// one value per lane.  Sweep 1 keeps each row block's running max and sum in registers, with one rescale per tile.
+// Sweep 2 adds into one accumulator per key slot over all row blocks and sums across lanes once per key tile.
+// Each head's window rows are padded to a multiple of 32 so that every 32-row block belongs to one query head; the
+// blocks of a request are those of its own window length, so a short window in a ragged batch costs what it holds.
+//
+// What bounds them: at d = 64 in bf16 the vector unit (about 330 issue cycles per tile beside 128 of matrix work), in
+// fp32 the matrix cores (64 cycles per instruction and 2 contraction indexes), and for the smallest problems the
+// chain of launch, first loads and merge.  Measured against one thread per key on the
+// plain ALU: bf16, 2 x 24 layers of 16 (4 KV) heads of 64 over 4096 keys with 50 window rows, 717 + 9 + 417 us -> 56 + 61 us;
+// fp32, 2 layers of 4 (2 KV) heads of 64 over 512 keys with 32 rows, 30 + 4 + 31 us -> 11.5 + 9.4 us.  Errors against
+// 64-bit arithmetic are those of the plain-ALU sweeps or smaller (scores 0.5-3e-7 relative, row sums 1-4e-7).
+#include "common.h"
+#include "internal.h"
+#include "score_tiles.h"     // acc_row, as_frag
+
+namespace vlc {
+namespace {
+
+using tiles::acc_row;
+
+struct SweepArgs {
+    const char* q_win;
+    const char* k;
+    const float* sm_scale;
+    float2* part;            // [group][split][g * tau] partial (max, sum), exponent domain (log2)
+    const float* row_max;    // natural-log domain, [B,L,Hq,tau]
+    const float* row_sum;    // null: count only
+    const float2* part_in;   // sweep 2: partials of sweep 1 to merge in the prologue, or null (statistics given)
+    float* row_max_out;      // sweep 2 with part_in: where the merged statistics go ([B,L,Hq,tau]; either may be null)
+    float* row_sum_out;
+    float* scores;           // may be null
+    unsigned long long* nnz; // may be null
+    const int32_t* lens;     // per-request (m_b, tau_b), or null
+    float log2p, default_scale;
+    int L, Hq, Hkv, g, m, tau, keys_per_split, nsplit;
+    int rb0;                 // first 32-row block of this launch
+    int accumulate;          // sweep 2: add to scores instead of overwriting (row groups after the first)
+};
+
+// RBYTES: bytes of a Q' or K row.  NRB: most 32-row blocks of a launch.  W: waves per block.  Registers for four waves
+// per SIMD: two 8-wave blocks per CU, or one of 16 waves where the Q' rows fill the LDS.  A K tile of 512-byte rows
+// takes 64 registers (spills at four waves per SIMD): one 8-wave block per CU, whose matrix instructions (4096
+// cycles per tile) need no other wave's help to keep the matrix cores busy.
+template <bool F32_, int RBYTES_, int NRB_, int W_>
+struct Form {
+    static constexpr bool F32 = F32_;
+    static constexpr int RBYTES = RBYTES_, NRB = NRB_, W = W_;
+    static constexpr int THREADS = W * 64;
+    static constexpr int WAVES_PER_SIMD = RBYTES == 512 ? 2 : 4;
+    static constexpr int KS = RBYTES / 32;              // 16-byte fragments per lane and row
+    static constexpr int PITCH = RBYTES + 16;           // LDS row of Q': 16-byte fragment reads free of bank conflicts
+    static constexpr int ROWS = NRB * 32;
+    static constexpr int CPR = RBYTES / 16;             // 16-byte pieces of a row
+    static constexpr int NQ = ROWS * CPR / THREADS;     // pieces of Q' per thread
+    static_assert(ROWS * CPR % THREADS == 0 && ROWS <= THREADS, "staging and statistics in whole passes");
+};
+
+// What the blocks of one (request, layer, KV head) share.
+struct Where {
+    int hkv, bl, l, mb, tb, nb, nrb;        // nb: 32-row blocks per head, nrb: row blocks of this launch
+    int k_begin, k_end, nt;                 // key range of the split, its 32-key tiles
+    float c;                                // logit scale in the exponent domain
+};
+__device__ __forceinline__ Where locate(const SweepArgs& a, int group, int split, int max_rb) {
+    Where w;
+    w.hkv = group % a.Hkv; w.bl = group / a.Hkv; w.l = w.bl % a.L;
+    const ReqLen rl = request_len(a.lens, w.bl / a.L, a.m, a.tau);
+    w.mb = rl.m; w.tb = rl.tau;                             // this request's prompt and window length
+    w.nb = (w.tb + 31) >> 5;
+    w.nrb = min(a.g * w.nb - a.rb0, max_rb);
+    w.k_begin = split * a.keys_per_split;
+    w.k_end = min(w.mb, w.k_begin + a.keys_per_split);
+    w.nt = w.k_end > w.k_begin ? (w.k_end - w.k_begin + 31) >> 5 : 0;
+    w.c = (a.sm_scale ? a.sm_scale[w.l] : a.default_scale) * kLog2e;
+    return w;
+}
+// Row r of the launch's row blocks: its head, its window row, and whether it exists.
+struct Row { int hl, iw; bool real; };
+__device__ __forceinline__ Row window_row(const SweepArgs& a, const Where& w, int r) {
+    const int rb = a.rb0 + (r >> 5);
+    Row o;
+    o.hl = rb / w.nb;
+    o.iw = (rb - o.hl * w.nb) * 32 + (r & 31);
+    o.real = (r >> 5) < w.nrb && o.iw < w.tb;
+    return o;
+}
+
+// K fragments of the 32-key tile that starts at key0: lane l % 32 owns a key, lane half l / 32 the 16-byte pieces
+// 2 s + half.  Keys beyond the prompt read its last row (the causal mask drops them), so nothing past it is touched.
+template <int KS, int RBYTES>
+__device__ __forceinline__ void load_keys(const char* kg, int key0, int mb, int lane, uint4 (&kf)[KS]) {
+    const char* base = kg + (size_t)key0 * RBYTES;          // wave-uniform
+    const uint32_t off = (uint32_t)min(lane & 31, mb - 1 - key0) * RBYTES + (lane >> 5) * 16;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) kf[s] = *reinterpret_cast<const uint4*>(base + off + s * 32);
+}
+
+// The block's Q' rows into LDS; rows that do not exist are zero.  All requests of a thread are in flight together.
+template <typename F>
+__device__ __forceinline__ void stage_q(const SweepArgs& a, const Where& w, char* sQ) {
+    uint4 q[F::NQ];
+#pragma unroll
+    for (int u = 0; u < F::NQ; ++u) {
+        const int x = threadIdx.x + F::THREADS * u, r = x / F::CPR;
+        const Row o = window_row(a, w, r);
+        const char* src = a.q_win + (((size_t)w.bl * a.Hq + (size_t)w.hkv * a.g + (o.real ? o.hl : 0)) * a.tau + (o.real ? o.iw : 0)) * F::RBYTES;
+        q[u] = *reinterpret_cast<const uint4*>(src + (x % F::CPR) * 16);
+        if (!o.real) q[u] = make_uint4(0, 0, 0, 0);
+    }
+#pragma unroll
+    for (int u = 0; u < F::NQ; ++u) {
+        const int x = threadIdx.x + F::THREADS * u;
+        *reinterpret_cast<uint4*>(sQ + (x / F::CPR) * F::PITCH + (x % F::CPR) * 16) = q[u];
+    }
+}
+
+// acc[i] = <key, row>: key acc_row(i, lane) of the tile, window row lane % 32 of row block rb.
+template <typename F>
+__device__ __forceinline__ f32x16_t tile_product(const char* sQ, int rb, int lane, const uint4 (&kf)[F::KS]) {
+    const char* row = sQ + (rb * 32 + (lane & 31)) * F::PITCH + (lane >> 5) * 16;
+    f32x16_t acc = {0};
+#pragma unroll
+    for (int s = 0; s < F::KS; ++s) {
+        const uint4 q = *reinterpret_cast<const uint4*>(row + s * 32);
+        if constexpr (F::F32) {
+            // a lane half supplies one of the two contraction indexes of an instruction: element e of its 16-byte piece
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(kf[s].x), __uint_as_float(q.x), acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(kf[s].y), __uint_as_float(q.y), acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(kf[s].z), __uint_as_float(q.z), acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(kf[s].w), __uint_as_float(q.w), acc, 0, 0, 0);
+        } else {
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(tiles::as_frag(kf[s]), tiles::as_frag(q), acc, 0, 0, 0);
+        }
+    }
+    return acc;
+}
+
+// ------------------------------------------------------------------------------------------------
+// Sweep 1: partial row statistics of one key range of one KV group.
+template <typename F>
+__global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void rowstats_wave_kernel(SweepArgs a) {
+    constexpr int RBYTES = F::RBYTES, NRB = F::NRB, W = F::W, KS = F::KS;
+    constexpr int QBYTES = F::ROWS * F::PITCH, MBYTES = W * F::ROWS * (int)sizeof(float2);
+    __shared__ __align__(16) char smem[QBYTES > MBYTES ? QBYTES : MBYTES];      // Q' rows; after the sweep the waves' statistics
+    const int group = blockIdx.x, split = blockIdx.y;       // group-major: see the launch
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;     // wave index in a scalar register
+    const Where w = locate(a, group, split, NRB);
+    if (a.nnz && split == 0 && a.rb0 == 0 && (int)threadIdx.x < a.g)
+        a.nnz[(size_t)w.bl * a.Hq + (size_t)w.hkv * a.g + threadIdx.x] = 0;      // sweep 2 adds into these
+    if (w.nrb <= 0) return;                                 // a shorter window than the longest of the batch
+    const char* kg = a.k + (size_t)group * a.m * RBYTES;
+    uint4 kf[KS];
+    if (wave < w.nt) load_keys<KS, RBYTES>(kg, w.k_begin + wave * 32, w.mb, lane, kf);
+    stage_q<F>(a, w, smem);
+    __syncthreads();
+    float m_run[NRB], z_run[NRB];                           // this lane's row of each row block, over the keys its half holds
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb) { m_run[rb] = -INFINITY; z_run[rb] = 0.f; }
+#pragma unroll 1
+    for (int t = wave; t < w.nt; t += W) {
+        const int key0 = w.k_begin + t * 32;
+        const bool masked = key0 + 32 > w.mb - w.tb + 1;    // the tile reaches past the first window key
+#pragma unroll
+        for (int rb = 0; rb < NRB; ++rb) {
+            if (rb < w.nrb) {                               // wave-uniform
+                const f32x16_t acc = tile_product<F>(smem, rb, lane, kf);
+                if (rb == w.nrb - 1 && t + W < w.nt) load_keys<KS, RBYTES>(kg, key0 + W * 32, w.mb, lane, kf);
+                float v[16];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) v[i] = acc[i];
+                if (masked) {                               // last key this lane's row may see (causal mask of Alg. 1)
+                    int rbg = a.rb0 + rb;
+                    asm volatile("" : "+s"(rbg));           // computed here: hoisted, the limits of all row blocks would take registers
+                    const int jlim = min(w.mb - w.tb + (rbg % w.nb) * 32 + (lane & 31), w.mb - 1) - key0;
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) v[i] = acc_row(i, lane) <= jlim ? v[i] : -INFINITY;
+                }
+                float tmax = v[0];
+#pragma unroll
+                for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, v[i]);
+                const float m_new = fmaxf(m_run[rb], tmax * w.c);
+                const float m_use = m_new > -INFINITY ? m_new : 0.f;      // a row that has seen no key yet: every term is 0
+                float zs = 0.f;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) zs += exp2_fast(fmaf(v[i], w.c, -m_use));
+                z_run[rb] = z_run[rb] * exp2_fast(m_run[rb] - m_use) + zs;
+                m_run[rb] = m_new;
+            }
+        }
+    }
+    // the two lane halves hold disjoint keys of the same rows, the waves disjoint tiles
+    __syncthreads();                                        // Q' is no longer read
+    float2* sStat = reinterpret_cast<float2*>(smem);        // [W][ROWS]
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb) {
+        const float mo = __shfl_xor(m_run[rb], 32, 64), zo = __shfl_xor(z_run[rb], 32, 64);
+        const float mm = fmaxf(m_run[rb], mo);
+        float z = 0.f;
+        if (m_run[rb] > -INFINITY) z += z_run[rb] * exp2_fast(m_run[rb] - mm);
+        if (mo > -INFINITY) z += zo * exp2_fast(mo - mm);
+        if (lane < 32) sStat[wave * F::ROWS + rb * 32 + lane] = make_float2(mm, z);
+    }
+    __syncthreads();
+    const int r = threadIdx.x;
+    const Row o = window_row(a, w, r);
+    if (r < F::ROWS && o.real) {
+        float M = -INFINITY, Z = 0.f;
+#pragma unroll
+        for (int v = 0; v < W; ++v) M = fmaxf(M, sStat[v * F::ROWS + r].x);
+#pragma unroll
+        for (int v = 0; v < W; ++v) {
+            const float2 s = sStat[v * F::ROWS + r];
+            if (s.x > -INFINITY) Z += s.y * exp2_fast(s.x - M);
+        }
+        a.part[((size_t)group * a.nsplit + split) * a.g * a.tau + o.hl * a.tau + o.iw] = make_float2(M, Z);
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+// Sweep 2: column sums of the softmax over all window rows of the KV group, and per-head counts.
+template <typename F>
+__global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void colsweep_wave_kernel(SweepArgs a) {
+    constexpr int RBYTES = F::RBYTES, W = F::W, KS = F::KS;
+    __shared__ __align__(16) char sQ[F::ROWS * F::PITCH];
+    __shared__ float2 sConst[F::ROWS];                      // per row: exponent offset (+inf for rows that do not exist), 1 / row sum
+    __shared__ uint32_t sCnt[8];                            // Eq. 1 entries per query head of the group
+    const int group = blockIdx.x, split = blockIdx.y;       // group-major: see the launch
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;     // wave index in a scalar register
+    const Where w = locate(a, group, split, F::NRB);
+    if (w.nrb <= 0) return;
+    const char* kg = a.k + (size_t)group * a.m * RBYTES;
+    // Order of the first requests: the few bytes of the statistics go out first (every block of the launch starts at
+    // once, and behind the K bursts they would wait), then the first K tile, then Q'.
+    const Row o = window_row(a, w, (int)threadIdx.x);
+    const bool mine = (int)threadIdx.x < F::ROWS && o.real;
+    constexpr int kSplitRegs = 4;                           // splits whose partials a thread holds at once (more are merged in rounds)
+    float2 pin[kSplitRegs];
+    const float2* pp = a.part_in + (size_t)group * a.nsplit * a.g * a.tau + o.hl * a.tau + o.iw;
+    const size_t split_stride = (size_t)a.g * a.tau;
+    if (mine && a.part_in) {
+#pragma unroll
+        for (int sp = 0; sp < kSplitRegs; ++sp) pin[sp] = sp < a.nsplit ? pp[sp * split_stride] : make_float2(-INFINITY, 0.f);
+    }
+    uint4 kf[KS];
+    if (wave < w.nt) load_keys<KS, RBYTES>(kg, w.k_begin + wave * 32, w.mb, lane, kf);
+    stage_q<F>(a, w, sQ);
+    if (threadIdx.x < 8) sCnt[threadIdx.x] = 0;
+    if ((int)threadIdx.x < F::ROWS) {
+        float2 st = make_float2(INFINITY, 0.f);
+        const size_t x = ((size_t)w.bl * a.Hq + (size_t)w.hkv * a.g + o.hl) * a.tau + o.iw;
+        if (mine && a.part_in) {
+            // merge of the key splits of sweep 1; the block of the first split also writes the row maximum and sum
+            // the caller asked for (either may be absent: a count-only sweep keeps no row sums)
+            float M = -INFINITY, Z = 0.f;
+            for (int sp0 = 0; sp0 < a.nsplit; sp0 += kSplitRegs) {
+                if (sp0 > 0) {
+#pragma unroll
+                    for (int sp = 0; sp < kSplitRegs; ++sp) pin[sp] = sp0 + sp < a.nsplit ? pp[(sp0 + sp) * split_stride] : make_float2(-INFINITY, 0.f);
+                }
+                float Mn = M;
+#pragma unroll
+                for (int sp = 0; sp < kSplitRegs; ++sp) Mn = fmaxf(Mn, pin[sp].x);
+                if (Mn > -INFINITY) {
+                    Z *= exp2_fast(M - Mn);                 // 0 on the first round (M = -inf)
+#pragma unroll
+                    for (int sp = 0; sp < kSplitRegs; ++sp)
+                        if (pin[sp].x > -INFINITY) Z += pin[sp].y * exp2_fast(pin[sp].x - Mn);
+                    M = Mn;
+                }
+            }
+            st = make_float2(M, 1.f / Z);
+            if (split == 0) {
+                if (a.row_max_out) a.row_max_out[x] = M * kLn2;
+                if (a.row_sum_out) a.row_sum_out[x] = Z;
+            }
+        } else if (mine) {
+            st = make_float2(a.row_max[x] * kLog2e, a.row_sum ? 1.f / a.row_sum[x] : 0.f);
+        }
+        sConst[threadIdx.x] = st;
+    }
+    __syncthreads();
+    const int j_first = a.rb0 % w.nb, h_first = a.rb0 / w.nb;
+#pragma unroll 1
+    for (int t = wave; t < w.nt; t += W) {
+        const int key0 = w.k_begin + t * 32;
+        const bool masked = key0 + 32 > w.mb - w.tb + 1;    // the tile reaches past the first window key
+        float col[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) col[i] = 0.f;
+        uint32_t cnt = 0;                                   // wave-wide, on the scalar unit
+        int j = j_first, hl = h_first;                      // block within its head, head
+#pragma unroll 1
+        for (int rb = 0; rb < w.nrb; ++rb) {
+            const float2 rc = sConst[rb * 32 + (lane & 31)];
+            const f32x16_t acc = tile_product<F>(sQ, rb, lane, kf);
+            if (rb == w.nrb - 1 && t + W < w.nt) load_keys<KS, RBYTES>(kg, key0 + W * 32, w.mb, lane, kf);
+            float ea[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) ea[i] = fmaf(acc[i], w.c, -rc.x);
+            if (masked) {
+                const int jlim = min(w.mb - w.tb + j * 32 + (lane & 31), w.mb - 1) - key0;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) ea[i] = acc_row(i, lane) <= jlim ? ea[i] : -INFINITY;
+            }
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                col[i] = fmaf(exp2_fast(ea[i]), rc.y, col[i]);
+                cnt += (uint32_t)__popcll(__ballot(ea[i] >= a.log2p));
+            }
+            if (++j == w.nb || rb == w.nrb - 1) {           // last block of its head here
+                if (a.nnz && lane == 0 && cnt) atomicAdd(&sCnt[hl], cnt);
+                cnt = 0; j = 0; ++hl;
+            }
+        }
+        if (!a.scores) continue;
+        // Sum over the 32 rows each lane half holds: v_permlane16_swap halves 16 slots to 8 (lane row 0 of a half keeps
+        // slots 0..7, row 1 slots 8..15), the row reduce-scatter leaves one slot per lane pair.
+        float h8[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const auto s2 = __builtin_amdgcn_permlane16_swap(__float_as_uint(col[i]), __float_as_uint(col[i + 8]), false, false);
+            h8[i] = __uint_as_float(s2[0]) + __uint_as_float(s2[1]);
+        }
+        const float tot = row16_reduce_scatter8<8>(h8, lane & 15);
+        const int slot = ((lane >> 1) & 1) + ((lane >> 2) & 1) * 2 + ((lane >> 3) & 1) * 4 + ((lane >> 4) & 1) * 8;
+        const int key = key0 + acc_row(slot, lane);
+        if ((lane & 1) == 0 && key < w.k_end) {
+            float* dst = a.scores + (size_t)group * a.m + key;
+            *dst = a.accumulate ? *dst + tot : tot;
+        }
+    }
+    // keys of the padded prompt beyond this request's own length score zero
+    if (a.scores && a.lens && !a.accumulate) {
+        const int z_end = min(a.m, w.k_begin + a.keys_per_split);
+        for (int x = max(w.k_begin, w.mb) + (int)threadIdx.x; x < z_end; x += F::THREADS) a.scores[(size_t)group * a.m + x] = 0.f;
+    }
+    if (a.nnz) {
+        __syncthreads();
+        if ((int)threadIdx.x < a.g && sCnt[threadIdx.x])
+            atomicAdd(a.nnz + (size_t)w.bl * a.Hq + (size_t)w.hkv * a.g + threadIdx.x, (unsigned long long)sCnt[threadIdx.x]);
+    }
+}
+
+int row_bytes(const vlc_shape& s) { return s.d * (s.dtype == VLC_F32 ? 4 : 2); }
+int max_row_blocks(const vlc_shape& s) { return row_bytes(s) == 512 ? 8 : 16; }       // per launch: what fits the LDS
+
+struct Plan { int nrb, nsplit, keys_per_split; };
+
+Plan make_plan(const vlc_shape& s) {
+    Plan p;
+    const int g = s.Hq / s.Hkv;
+    p.nrb = g * ((s.tau + 31) / 32);
+    const int64_t groups = (int64_t)s.B * s.L * s.Hkv;
+    const int tiles = s.m / 32 + (s.m % 32 != 0);
+    const int nrb = p.nrb < max_row_blocks(s) ? p.nrb : max_row_blocks(s);
+    const bool wide = row_bytes(s) == 256 && nrb > 8;                      // see launch_sweep
+    const int W = wide ? 16 : 8, resident = wide || row_bytes(s) == 512 ? 256 : 512;      // blocks that 256 CUs hold at once
+    // Splits of the key range per KV group: the number with the least modelled time, in units of one key tile per
+    // wave -- rounds of resident blocks, each as long as its fullest wave plus a prologue (Q' into LDS, statistics:
+    // about 3 us, where a tile costs a wave about 1 us per row block).  At most one split per 256 keys and 32 in all:
+    // the partial statistics then never need more than those of the plain-ALU sweep of the same shape (one per 256 keys).
+    const double prologue = 3.0 / nrb;
+    double best = 0.0;
+    int ns = 1;
+    const int top = s.m / 256 + (s.m % 256 != 0) < 32 ? s.m / 256 + (s.m % 256 != 0) : 32;
+    for (int n = 1; n <= top; ++n) {
+        const int tps = (tiles + n - 1) / n;
+        const double cost = (double)((groups * n + resident - 1) / resident) * ((tps + W - 1) / W + prologue);
+        if (n == 1 || cost < best * 0.999) { best = cost; ns = n; }
+    }
+    const int tps = (tiles + ns - 1) / ns;
+    p.keys_per_split = tps * 32;
+    p.nsplit = (tiles + tps - 1) / tps;
+    return p;
+}
+
+SweepArgs make_args(const ScoreArgs& a, const Plan& p) {
+    SweepArgs m;
+    const vlc_shape& s = a.s;
+    m.q_win = (const char*)a.q_win; m.k = (const char*)a.k; m.sm_scale = a.sm_scale;
+    m.part = (float2*)a.workspace;
+    m.row_max = a.row_max; m.row_sum = a.row_sum;
+    m.part_in = nullptr; m.row_max_out = a.row_max; m.row_sum_out = a.row_sum;
+    m.scores = a.scores; m.nnz = (unsigned long long*)a.nnz;
+    m.log2p = log2f(a.p); m.default_scale = 1.0f / sqrtf((float)s.d);
+    m.lens = s.lens;
+    m.L = s.L; m.Hq = s.Hq; m.Hkv = s.Hkv; m.g = s.Hq / s.Hkv; m.m = s.m; m.tau = s.tau;
+    m.keys_per_split = p.keys_per_split; m.nsplit = p.nsplit;
+    m.rb0 = 0; m.accumulate = 0;
+    return m;
+}
+
+template <bool SWEEP1, bool F32, int RBYTES, int NRB, int W>
+void launch_form(const SweepArgs& m, dim3 grid, hipStream_t st) {
+    using F = Form<F32, RBYTES, NRB, W>;
+    if (SWEEP1) rowstats_wave_kernel<F><<<grid, F::THREADS, 0, st>>>(m);
+    else colsweep_wave_kernel<F><<<grid, F::THREADS, 0, st>>>(m);
+}
+
+// Windows of more row blocks than a launch holds take several launches over consecutive row-block ranges.  Group-major
+// grid: blocks go to the 8 XCDs round-robin by linear index, so with a multiple of 8 KV groups the key splits of a
+// group run on one XCD and share its Q' rows in that XCD's L2.
+template <bool SWEEP1>
+hipError_t launch_sweep(SweepArgs m, const Plan& p, const vlc_shape& s, hipStream_t st) {
+    const dim3 grid(s.B * s.L * s.Hkv, p.nsplit);
+    const int step = max_row_blocks(s);
+    for (int rb0 = 0; rb0 < p.nrb; rb0 += step) {
+        const int nrb = p.nrb - rb0 < step ? p.nrb - rb0 : step;
+        m.rb0 = rb0;
+        m.accumulate = rb0 > 0;                 // launches of one stream run in order: the column sums add up deterministically
+        if (s.dtype == VLC_F32 && s.d == 128) {
+            if (nrb <= 4) launch_form<SWEEP1, true, 512, 4, 8>(m, grid, st);
+            else launch_form<SWEEP1, true, 512, 8, 8>(m, grid, st);
+        } else if (s.dtype == VLC_F32) {
+            if (nrb <= 4) launch_form<SWEEP1, true, 256, 4, 8>(m, grid, st);
+            else if (nrb <= 8) launch_form<SWEEP1, true, 256, 8, 8>(m, grid, st);
+            else launch_form<SWEEP1, true, 256, 16, 16>(m, grid, st);
+        } else {
+            if (nrb <= 4) launch_form<SWEEP1, false, 128, 4, 8>(m, grid, st);
+            else if (nrb <= 8) launch_form<SWEEP1, false, 128, 8, 8>(m, grid, st);
+            else launch_form<SWEEP1, false, 128, 16, 8>(m, grid, st);
+        }
+    }
+    return hipGetLastError();
+}
+
+}  // namespace
+
+bool score_wave_supported(const vlc_shape& s) { return s.dtype == VLC_F32 || s.d == 64; }
+
+hipError_t launch_rowstats_wave(const ScoreArgs& a) {
+    const Plan p = make_plan(a.s);
+    return launch_sweep<true>(make_args(a, p), p, a.s, a.stream);
+}
+
+hipError_t launch_colsweep_wave(const ScoreArgs& a, bool merge_partials) {
+    const Plan p = make_plan(a.s);
+    SweepArgs m = make_args(a, p);
+    if (merge_partials) m.part_in = m.part;          // sweep 1 ran just before on the same workspace
+    return launch_sweep<false>(m, p, a.s, a.stream);
+}
+
+}  // namespace vlc

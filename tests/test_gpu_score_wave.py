@@ -1,0 +1,64 @@
+"""The scoring sweeps for bf16 storage with d = 64 and for fp32 storage (score_wave.hip) at the sizes where their
+division of the work can go wrong: one key, one window row, remainders of the 32-key tiles and 32-row blocks, each
+block form (up to 4, 8, 16 row blocks), windows that take several launches, more tiles than a round of waves, ragged
+batches with NaN in all padding.  Against the oracle, to the tolerances of the scoring path (fp32 accumulation of
+products that are exact in fp32, respectively rounded once; a 1-ulp exponential)."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from gpu_util import SCORE_TOL, assert_close, check_nnz, torch_dtype
+from oracle import vlcache_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype,d,Hq,Hkv,lens", [
+    ("bf16", 64, 2, 2, [(1, 1)]),                                # one key
+    ("bf16", 64, 4, 1, [(31, 1), (33, 33)]),                     # shorter than a tile; the window is the whole prompt
+    ("bf16", 64, 8, 2, [(2049, 32)]),                            # 4 row blocks, several rounds of tiles, a tile of one key
+    ("bf16", 64, 5, 1, [(300, 32), (257, 7)]),                   # 5 row blocks
+    ("bf16", 64, 8, 1, [(515, 33), (515, 5)]),                   # 16 row blocks; 8 for the shorter window
+    ("bf16", 64, 8, 1, [(700, 65), (64, 64), (40, 3)]),          # 24 row blocks: two launches, the second empty for the others
+    ("f32", 64, 4, 2, [(544, 32), (512, 31)]),
+    ("f32", 64, 7, 1, [(385, 40)]),                              # 14 row blocks: the 16-wave form
+    ("f32", 64, 3, 1, [(1000, 200), (95, 95)]),                  # 21 row blocks: two launches
+    ("f32", 128, 4, 2, [(1, 1), (290, 29)]),
+    ("f32", 128, 6, 2, [(333, 64), (65, 1)]),                    # 6 row blocks of 512-byte rows
+    ("f32", 128, 6, 1, [(2200, 50)]),                            # 12: two launches
+])
+def test_wave_sweeps_match_the_oracle(dtype, d, Hq, Hkv, lens):
+    import paper_2410_23317_amd as V
+    B, L = len(lens), 2
+    m, tau = max(x[0] for x in lens), max(x[1] for x in lens)
+    cfgs = [W.custom_config(cid=800 + b, name=f"wave-{b}", dtype=dtype, d=d, Hq=Hq, Hkv=Hkv, m=mb, tau=tb, lead_text=0,
+                            n_visual=mb, L=L, B=1, sinks=min(4, mb), alphas=((1, 5),)) for b, (mb, tb) in enumerate(lens)]
+    dt = torch_dtype(cfgs[0])
+    q_win = torch.full((B, L, Hq, tau, d), float("nan"), dtype=dt, device="cuda")
+    k = torch.full((B, L, Hkv, m, d), float("nan"), dtype=dt, device="cuda")
+    host = {}
+    for b, cfg in enumerate(cfgs):
+        for l in range(L):
+            t = host[b, l] = W.layer_inputs(cfg, 0, l)
+            q_win[b, l, :, : cfg.tau].copy_(torch.from_numpy(t["q_win"]).to(dt))
+            k[b, l, :, : cfg.m].copy_(torch.from_numpy(t["k"]).to(dt))
+    lens_t = torch.tensor(lens, dtype=torch.int32, device="cuda") if B > 1 else None
+    scales = W.sm_scale(cfgs[0])
+    shape = V.make_shape(B, L, Hq, Hkv, d, m, tau, dtype, lens=lens_t)
+    ws = torch.full((V.vlc_workspace_bytes(shape),), 255, dtype=torch.uint8, device="cuda")
+    new = lambda *s: torch.full(s, float("nan"), dtype=torch.float32, device="cuda")
+    scores, row_max, row_sum = new(B, L, Hkv, m), new(B, L, Hq, tau), new(B, L, Hq, tau)
+    nnz = torch.full((B, L, Hq), 77, dtype=torch.int64, device="cuda")
+    V.vlc_score(shape, q_win, k, torch.from_numpy(scales).cuda(), 0.01, scores, row_max, row_sum, nnz, ws)
+    torch.cuda.synchronize()
+    for b, cfg in enumerate(cfgs):
+        assert torch.all(scores[b, :, :, cfg.m:] == 0), "keys beyond the request's prompt score zero"
+        assert torch.all(torch.isnan(row_max[b, :, :, cfg.tau:])), "window rows beyond the request's are left untouched"
+        for l in range(L):
+            t, what = host[b, l], f"b={b} l={l}"
+            psi, _, M, Z = O.score(t["q_win"], t["k"], scales[l])
+            assert_close(scores[b, l, :, : cfg.m].cpu().numpy(), psi, what=what + " scores", **SCORE_TOL)
+            assert_close(row_max[b, l, :, : cfg.tau].cpu().numpy(), M, atol=2e-5, rtol=2e-6, what=what + " row_max")
+            assert_close(row_sum[b, l, :, : cfg.tau].cpu().numpy(), Z, atol=0, rtol=5e-5, what=what + " row_sum")
+            check_nnz(nnz[b, l].cpu().numpy(), t["q_win"], t["k"], scales[l], 0.01, what + " nnz")
