@@ -14,6 +14,9 @@
 // chunks of 128 keys (global -> registers -> LDS, the next chunk in flight while the current one is
 // multiplied).  Each head's tau window rows are padded to a multiple of 32 so that every 32-row
 // block belongs to one query head; padded rows carry a +inf offset and vanish from every sum.
+// In a ragged batch the blocks are those of the request's own window length, dealt to the waves from the first on (and
+// round-robin where a wave takes two), so a shorter window costs the blocks it holds: the waves beyond it only
+// help to stage K; where the longest window takes the 16-block forms, requests of up to 8 blocks get a launch of their own.
 #include "common.h"
 #include "internal.h"
 #include "score_tiles.h"
@@ -37,10 +40,17 @@ struct MfmaArgs {
     unsigned long long* nnz; // may be null
     const int32_t* lens;     // per-request (m_b, tau_b), or null
     float log2p;
-    int L, Hq, Hkv, g, m, tau, tauP, RP, keys_per_split, nsplit;
+    int L, Hq, Hkv, g, m, tau, RP, keys_per_split, nsplit;     // RP: padded window rows of a KV group, for the longest window
     int rb0;                 // first 32-row block of this launch (a launch covers at most 16 of them)
+    int rb_above, rb_upto;   // requests of this launch: those with more than rb_above row blocks from rb0 on, and at most rb_upto
     int accumulate;          // sweep 2: add to scores instead of overwriting (row groups after the first)
 };
+
+// Whether a launch takes the requests with RP padded window rows per KV group (block-uniform).
+__device__ __forceinline__ bool in_class(const MfmaArgs& a, int RP) {
+    const int nrb = RP / 32 - a.rb0;
+    return nrb > a.rb_above && nrb <= a.rb_upto;
+}
 
 // ------------------------------------------------------------------------------------------------
 // Sweep 1: partial row statistics of one key range of one KV group.
@@ -55,20 +65,22 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 0) void rowstats_mfma_
     const bf16_t* kg = a.k + (size_t)group * a.m * kD;
     const ReqLen rl = request_len(a.lens, bl / a.L, a.m, a.tau);
     const int mb = rl.m, tb = rl.tau;                       // this request's prompt and window length
+    const int tauP = padded_rows(tb), RP = a.g * tauP;      // and its padded rows, the launch's (a.RP) or fewer
     const int k_begin = split * a.keys_per_split;
     const int k_end = min(mb, k_begin + a.keys_per_split);
 
     if (a.nnz && split == 0 && a.rb0 == 0 && (int)threadIdx.x < a.g)
         a.nnz[(size_t)bl * a.Hq + (size_t)hkv * a.g + threadIdx.x] = 0;      // sweep 2 adds into these
+    if (!in_class(a, RP)) return;                           // this request's window is another launch's work
     uint4 qf[RB][kKSteps];
-    load_q_frags<WAVES, RB>(a, bl, hkv, wave, lane, tb, qf);
+    load_q_frags<RB, WAVES>(a, bl, hkv, a.rb0 + wave, lane, tb, tauP, qf);      // row blocks rb0 + wave + WAVES * rb
     // this lane's query row per row block, and the last key it may see (causal mask of Alg. 1)
     int jlim[RB];
     float m_run[RB], z_run[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-        const int r = (a.rb0 + wave * RB + rb) * 32 + (lane & 31);
-        jlim[rb] = mb - tb + (r % a.tauP);
+        const int r = (a.rb0 + wave + WAVES * rb) * 32 + (lane & 31);
+        jlim[rb] = mb - tb + (r % tauP);
         m_run[rb] = -INFINITY;
         z_run[rb] = 0.f;
     }
@@ -88,7 +100,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 0) void rowstats_mfma_
             load_k_frags(sK, t, lane, kf);
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {
-                if ((a.rb0 + wave * RB + rb) * 32 >= a.RP) continue;       // wave-uniform: no rows here
+                if ((a.rb0 + wave + WAVES * rb) * 32 >= RP) continue;       // wave-uniform: no rows here
                 f32x16_t acc = {0};
 #pragma unroll
                 for (int ks = 0; ks < kKSteps; ++ks)
@@ -124,8 +136,8 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 0) void rowstats_mfma_
         float z = 0.f;
         if (m_run[rb] > -INFINITY) z += z_run[rb] * exp2_fast(m_run[rb] - mm);
         if (mo > -INFINITY) z += zo * exp2_fast(mo - mm);
-        const int r = (a.rb0 + wave * RB + rb) * 32 + (lane & 31);
-        if (lane < 32 && r < a.RP) a.part[((size_t)group * a.nsplit + split) * a.RP + r] = make_float2(mm, z);
+        const int r = (a.rb0 + wave + WAVES * rb) * 32 + (lane & 31);
+        if (lane < 32 && r < RP) a.part[((size_t)group * a.nsplit + split) * a.RP + r] = make_float2(mm, z);
     }
 }
 
@@ -143,6 +155,8 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 4) void colsweep_mfma_
     const bf16_t* kg = a.k + (size_t)group * a.m * kD;
     const ReqLen rl = request_len(a.lens, bl / a.L, a.m, a.tau);
     const int mb = rl.m, tb = rl.tau;                       // this request's prompt and window length
+    const int tauP = padded_rows(tb), RP = a.g * tauP;      // and its padded rows, the launch's (a.RP) or fewer
+    if (!in_class(a, RP)) return;                           // this request's window is another launch's work
     const int k_begin = split * a.keys_per_split;
     const int k_end = min(mb, k_begin + a.keys_per_split);
 
@@ -152,7 +166,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 4) void colsweep_mfma_
     constexpr int kSplitRegs = 4;               // splits whose partials a thread holds at once (more are merged in rounds)
     float2 pin[kSplitRegs];
     const int r_mine = a.rb0 * 32 + (int)threadIdx.x;       // the row whose statistics this thread merges (first round)
-    const bool mine = a.part_in && (int)threadIdx.x < WAVES * RB * 32 && r_mine < a.RP;
+    const bool mine = a.part_in && (int)threadIdx.x < WAVES * RB * 32 && r_mine < RP;
     if (mine) {
 #pragma unroll
         for (int sp = 0; sp < kSplitRegs; ++sp)
@@ -161,7 +175,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 4) void colsweep_mfma_
     KStage<THREADS> st;
     if (k_begin < k_end) st.load(kg, k_begin, mb);
     uint4 qf[RB][kKSteps];
-    load_q_frags<WAVES, RB>(a, bl, hkv, wave, lane, tb, qf);
+    load_q_frags<RB, WAVES>(a, bl, hkv, a.rb0 + wave, lane, tb, tauP, qf);      // row blocks rb0 + wave + WAVES * rb
     // per accumulator slot: exponent offset (+inf for padded rows) and 1 / row sum
     float mc[RB][16], iz[RB][16];
     uint32_t cnt[RB];
@@ -172,8 +186,8 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 4) void colsweep_mfma_
         for (int t = threadIdx.x; t < WAVES * RB * 32; t += THREADS) {
             const int r = a.rb0 * 32 + t;
             float2 st = make_float2(INFINITY, 0.f);
-            const int hl = r / a.tauP, iw = r % a.tauP;
-            if (r < a.RP && hl < a.g && iw < tb) {
+            const int hl = r / tauP, iw = r % tauP;
+            if (r < RP && hl < a.g && iw < tb) {
                 float M = -INFINITY, Z = 0.f;
                 for (int sp0 = 0; sp0 < a.nsplit; sp0 += kSplitRegs) {
                     if (sp0 > 0 || t != (int)threadIdx.x) {          // beyond what was requested at the start
@@ -207,7 +221,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 4) void colsweep_mfma_
     for (int rb = 0; rb < RB; ++rb) {
         cnt[rb] = 0;
         if (a.part_in) {
-            const float2* sp = sStat + (wave * RB + rb) * 32 + 4 * (lane >> 5);
+            const float2* sp = sStat + (wave + WAVES * rb) * 32 + 4 * (lane >> 5);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const float4 lo = *reinterpret_cast<const float4*>(sp + 8 * q);
@@ -219,8 +233,8 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 4) void colsweep_mfma_
         }
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            const int r = (a.rb0 + wave * RB + rb) * 32 + acc_row(i, lane);
-            const int hl = r / a.tauP, iw = r % a.tauP;
+            const int r = (a.rb0 + wave + WAVES * rb) * 32 + acc_row(i, lane);
+            const int hl = r / tauP, iw = r % tauP;
             const bool ok = hl < a.g && iw < tb;
             const size_t o = ((size_t)bl * a.Hq + (size_t)hkv * a.g + (ok ? hl : 0)) * a.tau + (ok ? iw : 0);
             mc[rb][i] = ok ? a.row_max[o] * kLog2e : INFINITY;
@@ -244,14 +258,14 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 4) void colsweep_mfma_
             float col = 0.f;
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {
-                if ((a.rb0 + wave * RB + rb) * 32 >= a.RP) continue;
+                if ((a.rb0 + wave + WAVES * rb) * 32 >= RP) continue;
                 f32x16_t acc = {0};
 #pragma unroll
                 for (int ks = 0; ks < kKSteps; ++ks)
                     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(qf[rb][ks]), as_frag(kf[ks]), acc, 0, 0, 0);
                 // acc[i] = <q_row, k_key>, row = row block base + acc_row(i), key = this lane's
                 if (masked) {
-                    const int base = mb - tb + ((a.rb0 + wave * RB + rb) * 32) % a.tauP;
+                    const int base = mb - tb + ((a.rb0 + wave + WAVES * rb) * 32) % tauP;
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
                         const bool valid = key <= base + acc_row(i, lane);
@@ -293,25 +307,24 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 4) void colsweep_mfma_
     if (a.nnz) {
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb) {
-            const int rbase = (a.rb0 + wave * RB + rb) * 32;
-            if (rbase >= a.RP) continue;
+            const int rbase = (a.rb0 + wave + WAVES * rb) * 32;
+            if (rbase >= RP) continue;
             const uint32_t tot = cnt[rb];                        // already a wave-wide count
-            const int hl = rbase / a.tauP;
+            const int hl = rbase / tauP;
             if (lane == 0 && tot && hl < a.g)
                 atomicAdd(a.nnz + (size_t)bl * a.Hq + (size_t)hkv * a.g + hl, (unsigned long long)tot);
         }
     }
 }
 
-struct Plan { int tauP, RP, nsplit, keys_per_split; };
+struct Plan { int RP, nsplit, keys_per_split; };
 
 constexpr int kMaxRowBlocksPerLaunch = 16;      // 512 padded window rows per KV head and launch
 
 Plan make_plan(const vlc_shape& s) {
     Plan p;
     const int g = s.Hq / s.Hkv;
-    p.tauP = (s.tau + 31) / 32 * 32;
-    p.RP = g * p.tauP;
+    p.RP = g * ((s.tau + 31) / 32 * 32);
     const int groups = s.B * s.L * s.Hkv;
     const int chunks = (s.m + kChunk - 1) / kChunk;
     // Splits of the key range per KV group.  Measured on the 7B and 34B shapes: about one resident
@@ -339,8 +352,8 @@ MfmaArgs make_args(const ScoreArgs& a, const Plan& p) {
     m.log2p = log2f(a.p);
     m.lens = s.lens;
     m.L = s.L; m.Hq = s.Hq; m.Hkv = s.Hkv; m.g = s.Hq / s.Hkv; m.m = s.m; m.tau = s.tau;
-    m.tauP = p.tauP; m.RP = p.RP; m.keys_per_split = p.keys_per_split; m.nsplit = p.nsplit;
-    m.rb0 = 0; m.accumulate = 0;
+    m.RP = p.RP; m.keys_per_split = p.keys_per_split; m.nsplit = p.nsplit;
+    m.rb0 = 0; m.accumulate = 0; m.rb_above = 0; m.rb_upto = INT32_MAX;
     return m;
 }
 
@@ -362,6 +375,10 @@ size_t score_mfma_workspace_bytes(const vlc_shape& s) {
 // A launch covers up to 16 row blocks (32 padded window rows each) of every KV group; longer windows
 // take several launches over consecutive row-block ranges.  Block shape by row blocks in the launch:
 // up to 4 -> 4 waves, up to 8 -> 8 waves, else 8 waves x 2 row blocks (sweep 1) or 16 waves (sweep 2).
+// A ragged batch whose longest window takes the last forms runs its requests of up to 8 row blocks in the 8-wave form, in
+// a launch of their own (blocks of the other class leave at once): in 16-wave blocks half of the waves would idle.
+// 7B shape, 8 requests of up to 4099 tokens and 100 window rows (mean 62): every request padded to the longest window
+// 1042 + 1197 us, each request's own row blocks 0.79 of that, with the launch per class 731 + 846 us, all with the same sums.
 hipError_t launch_rowstats_mfma(const ScoreArgs& a) {
     const vlc_shape& s = a.s;
     const Plan p = make_plan(s);
@@ -374,10 +391,17 @@ hipError_t launch_rowstats_mfma(const ScoreArgs& a) {
     const int total_rb = p.RP / 32;
     for (int rb0 = 0; rb0 < total_rb; rb0 += kMaxRowBlocksPerLaunch) {
         const int nrb = total_rb - rb0 < kMaxRowBlocksPerLaunch ? total_rb - rb0 : kMaxRowBlocksPerLaunch;
-        m.rb0 = rb0;
+        m.rb0 = rb0; m.rb_above = 0;
         if (nrb <= 4) rowstats_mfma_kernel<4, 1><<<grid, 256, 0, a.stream>>>(m);
         else if (nrb <= 8) rowstats_mfma_kernel<8, 1><<<grid, 512, 0, a.stream>>>(m);
-        else rowstats_mfma_kernel<8, 2><<<grid, 512, 0, a.stream>>>(m);        // measured faster than 16 x 1 for this sweep
+        else {
+            if (a.s.lens) {                     // the requests with short windows in the form for them
+                m.rb_upto = 8;
+                rowstats_mfma_kernel<8, 1><<<grid, 512, 0, a.stream>>>(m);
+                m.rb_above = 8; m.rb_upto = INT32_MAX;
+            }
+            rowstats_mfma_kernel<8, 2><<<grid, 512, 0, a.stream>>>(m);        // measured faster than 16 x 1 for this sweep
+        }
     }
     return hipGetLastError();
 }
@@ -391,11 +415,18 @@ hipError_t launch_colsweep_mfma(const ScoreArgs& a, bool merge_partials) {
     const int total_rb = p.RP / 32;
     for (int rb0 = 0; rb0 < total_rb; rb0 += kMaxRowBlocksPerLaunch) {
         const int nrb = total_rb - rb0 < kMaxRowBlocksPerLaunch ? total_rb - rb0 : kMaxRowBlocksPerLaunch;
-        m.rb0 = rb0;
+        m.rb0 = rb0; m.rb_above = 0;
         m.accumulate = rb0 > 0;                 // launches of one stream run in order: the column sums add up deterministically
         if (nrb <= 4) colsweep_mfma_kernel<4, 1><<<grid, 256, 0, a.stream>>>(m);
         else if (nrb <= 8) colsweep_mfma_kernel<8, 1><<<grid, 512, 0, a.stream>>>(m);
-        else colsweep_mfma_kernel<16, 1><<<grid, 1024, 0, a.stream>>>(m);
+        else {
+            if (a.s.lens) {
+                m.rb_upto = 8;
+                colsweep_mfma_kernel<8, 1><<<grid, 512, 0, a.stream>>>(m);
+                m.rb_above = 8; m.rb_upto = INT32_MAX;
+            }
+            colsweep_mfma_kernel<16, 1><<<grid, 1024, 0, a.stream>>>(m);
+        }
     }
     return hipGetLastError();
 }

@@ -17,13 +17,14 @@ constexpr int kKSteps = kD / 16;        // MFMA k-steps per tile
 // 8 consecutive k-values [16 ks + 8 half, +8).
 __device__ __forceinline__ bf16x8_t as_frag(const uint4& v) { return __builtin_bit_cast(bf16x8_t, v); }
 
-template <int WAVES, int RB, typename Args>
-__device__ __forceinline__ void load_q_frags(const Args& a, int bl, int hkv, int wave, int lane, int tb, uint4 (&qf)[RB][kKSteps]) {
+// The 32-row blocks rb0 + STRIDE * rb (rb < RB) of this wave: rows of the KV group's window, each head padded to tauP.
+template <int RB, int STRIDE, typename Args>
+__device__ __forceinline__ void load_q_frags(const Args& a, int bl, int hkv, int rb0, int lane, int tb, int tauP, uint4 (&qf)[RB][kKSteps]) {
     const int half = lane >> 5;
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
-        const int r = (a.rb0 + wave * RB + rb) * 32 + (lane & 31);
-        const int hl = r / a.tauP, iw = r % a.tauP;
+        const int r = (rb0 + STRIDE * rb) * 32 + (lane & 31);
+        const int hl = r / tauP, iw = r % tauP;
         const bool ok = hl < a.g && iw < tb;
         const bf16_t* row = a.q_win + (((size_t)bl * a.Hq + (size_t)hkv * a.g + (ok ? hl : 0)) * a.tau + (ok ? iw : 0)) * kD;
 #pragma unroll
@@ -31,6 +32,9 @@ __device__ __forceinline__ void load_q_frags(const Args& a, int bl, int hkv, int
             qf[rb][ks] = ok ? *reinterpret_cast<const uint4*>(row + ks * 16 + half * 8) : make_uint4(0, 0, 0, 0);
     }
 }
+
+// Window rows of one head padded to whole 32-row blocks.
+__device__ __forceinline__ int padded_rows(int tb) { return (tb + 31) & ~31; }
 
 // K chunk staging: global -> registers -> LDS.  Keys at or beyond m are zero-filled.
 template <int THREADS>

@@ -44,7 +44,7 @@ struct WinArgs {
     float* part_o;           // [group][split][RP][kD] unnormalised partial outputs
     float2* part_ms;         // [group][split][RP] (max in the exponent domain, sum)
     const int32_t* lens;
-    int L, Hq, Hkv, g, m, tau, tauP, RP, keys_per_split, nsplit;
+    int L, Hq, Hkv, g, m, tau, RP, keys_per_split, nsplit;     // RP: padded window rows of a KV group, for the longest window
     int rb0;                 // first 32-row block of this launch
 };
 
@@ -149,12 +149,14 @@ __global__ __launch_bounds__(WAVES * 64, 2) void window_attn_kernel(WinArgs a) {
     const int mb = rl.m, tb = rl.tau;
     const int k_begin = split * a.keys_per_split;
     const int k_end = min(mb, k_begin + a.keys_per_split);
-    const bool has_rows = (a.rb0 + wave) * 32 < a.RP;          // wave-uniform
+    const int tauP = padded_rows(tb), RP = a.g * tauP;         // this request's padded window rows, the launch's (a.RP) or fewer
+    if (a.rb0 * 32 >= RP) return;                              // a later launch of a longer window than this request's
+    const bool has_rows = (a.rb0 + wave) * 32 < RP;            // wave-uniform
 
     uint4 qf[1][kKSteps];
-    load_q_frags<WAVES, 1>(a, bl, hkv, wave, lane, tb, qf);
+    load_q_frags<1, WAVES>(a, bl, hkv, a.rb0 + wave, lane, tb, tauP, qf);
     const int r = (a.rb0 + wave) * 32 + (lane & 31);           // this lane's padded window row
-    const int jlim = mb - tb + (r % a.tauP);                   // last key it may see
+    const int jlim = mb - tb + (r % tauP);                     // last key it may see
     float m_run = -INFINITY, z_run = 0.f;
     f32x16_t o[kD / 32];
 #pragma unroll
@@ -242,8 +244,8 @@ __global__ __launch_bounds__(WAVES * 64, 2) void window_attn_kernel(WinArgs a) {
     if (!has_rows) return;
     // the two lane halves hold disjoint keys of the same query row under the same max
     const float z = z_run + __shfl_xor(z_run, 32, 64);
-    const int hl = r / a.tauP, iw = r % a.tauP;
-    const bool real = hl < a.g && iw < tb && r < a.RP;
+    const int hl = r / tauP, iw = r % tauP;
+    const bool real = hl < a.g && iw < tb && r < RP;
     if (a.nsplit == 1) {
         if (!real) return;
         const size_t orow = ((size_t)bl * a.Hq + (size_t)hkv * a.g + hl) * a.tau + iw;
@@ -261,7 +263,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void window_attn_kernel(WinArgs a) {
         if (lane < 32) { a.row_max[orow] = m_run * kLn2; a.row_sum[orow] = z; }
         return;
     }
-    if (r >= a.RP) return;
+    if (r >= RP) return;
     const size_t prow = ((size_t)group * a.nsplit + split) * a.RP + r;
     float* dst = a.part_o + prow * kD;
 #pragma unroll
@@ -280,9 +282,10 @@ __global__ __launch_bounds__(256) void window_attn_merge_kernel(WinArgs a, int g
         const size_t x = ((size_t)blockIdx.x * 4 + it) * 8 + sub;      // (group, padded row)
         if (x >= (size_t)groups * a.RP) return;
         const int r = (int)(x % a.RP), group = (int)(x / a.RP);
-        const int hl = r / a.tauP, iw = r % a.tauP;
         const int hkv = group % a.Hkv, bl = group / a.Hkv;
-        if (hl >= a.g || iw >= request_len(a.lens, bl / a.L, a.m, a.tau).tau) continue;
+        const int tb = request_len(a.lens, bl / a.L, a.m, a.tau).tau, tauP = padded_rows(tb);
+        const int hl = r / tauP, iw = r % tauP;
+        if (hl >= a.g || iw >= tb) continue;
         float M = -INFINITY;
         for (int s = 0; s < a.nsplit; ++s) M = fmaxf(M, a.part_ms[((size_t)group * a.nsplit + s) * a.RP + r].x);
         float Z = 0.f;
@@ -305,13 +308,12 @@ __global__ __launch_bounds__(256) void window_attn_merge_kernel(WinArgs a, int g
     }
 }
 
-struct WinPlan { int tauP, RP, nsplit, keys_per_split; };
+struct WinPlan { int RP, nsplit, keys_per_split; };
 
 WinPlan make_plan(const vlc_shape& s) {
     WinPlan p;
     const int g = s.Hq / s.Hkv;
-    p.tauP = (s.tau + 31) / 32 * 32;
-    p.RP = g * p.tauP;
+    p.RP = g * ((s.tau + 31) / 32 * 32);
     const int groups = s.B * s.L * s.Hkv;
     const int chunks = (s.m + kChunk - 1) / kChunk;
     // Two staged chunks (66 KB of LDS) allow two blocks per compute unit: about one resident round
@@ -351,7 +353,7 @@ hipError_t launch_window_attn(const WindowAttnArgs& w) {
     a.part_ms = (float2*)((char*)w.workspace + (rows * kD * sizeof(float) + 255) / 256 * 256);
     a.lens = s.lens;
     a.L = s.L; a.Hq = s.Hq; a.Hkv = s.Hkv; a.g = s.Hq / s.Hkv; a.m = s.m; a.tau = s.tau;
-    a.tauP = p.tauP; a.RP = p.RP; a.keys_per_split = p.keys_per_split; a.nsplit = p.nsplit;
+    a.RP = p.RP; a.keys_per_split = p.keys_per_split; a.nsplit = p.nsplit;
     dim3 grid(p.nsplit, groups);
     const int total_rb = p.RP / 32;
     // Windows beyond 8 row blocks (256 padded rows per KV head) take one launch per 8 row blocks;

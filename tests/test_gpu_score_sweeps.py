@@ -1,5 +1,5 @@
-"""The scoring sweeps for bf16 storage with d = 64 and for fp32 storage (score_wave.hip) at the sizes where their
-division of the work can go wrong: one key, one window row, remainders of the 32-key tiles and 32-row blocks, each
+"""The matrix-core scoring sweeps (bf16 with d = 64 and fp32 storage: score_wave.hip; ragged batches of bf16 with
+d = 128: score_mfma.hip) at the sizes where their division of the work can go wrong: one key, one window row, remainders of the 32-key tiles and 32-row blocks, each
 block form (up to 4, 8, 16 row blocks), windows that take several launches, more tiles than a round of waves, ragged
 batches with NaN in all padding.  Against the oracle, to the tolerances of the scoring path (fp32 accumulation of
 products that are exact in fp32, respectively rounded once; a 1-ulp exponential)."""
@@ -27,8 +27,10 @@ pytestmark = pytest.mark.gpu
     ("f32", 128, 4, 2, [(1, 1), (290, 29)]),
     ("f32", 128, 6, 2, [(333, 64), (65, 1)]),                    # 6 row blocks of 512-byte rows
     ("f32", 128, 6, 1, [(2200, 50)]),                            # 12: two launches
+    ("bf16", 128, 4, 1, [(600, 100), (500, 64), (257, 20)]),     # 16, 8 and 4 row blocks: a launch per class of windows
+    ("bf16", 128, 8, 1, [(700, 70), (300, 33), (65, 5)]),        # 24, 16 and 8: the first needs a second launch
 ])
-def test_wave_sweeps_match_the_oracle(dtype, d, Hq, Hkv, lens):
+def test_sweeps_match_the_oracle(dtype, d, Hq, Hkv, lens):
     import paper_2410_23317_amd as V
     B, L = len(lens), 2
     m, tau = max(x[0] for x in lens), max(x[1] for x in lens)
