@@ -270,7 +270,7 @@ constexpr int kSelWaves = kSelThreads / 64;
 
 // Visit the candidates of this wave's segment [j0, j1): f(position, key, inside).  Every lane calls f
 // the same number of times, so f may hold wave-wide ballots.  With NK > 0 the keys come from the
-// registers filled at the start of the kernel, else they are streamed from memory four at a time.
+// registers filled at the start of the kernel, else they are streamed from memory sixteen at a time.
 template <int NK, typename F>
 __device__ __forceinline__ void for_keys(const uint32_t (&key)[NK > 0 ? NK : 1], const float* __restrict__ s,
                                          int j0, int j1, int lane, F f) {
@@ -281,12 +281,13 @@ __device__ __forceinline__ void for_keys(const uint32_t (&key)[NK > 0 ? NK : 1],
             f(j, key[i], j < j1);
         }
     } else {
-        for (int jb = j0; jb < j1; jb += 4 * 64) {
-            float v[4];
+        constexpr int N = 16;                   // loads in flight per lane
+        for (int jb = j0; jb < j1; jb += N * 64) {
+            float v[N];
 #pragma unroll
-            for (int x = 0; x < 4; ++x) v[x] = s[min(jb + x * 64 + lane, j1 - 1)];    // unconditional: no wait between loads
+            for (int x = 0; x < N; ++x) v[x] = s[min(jb + x * 64 + lane, j1 - 1)];    // unconditional: no wait between loads
 #pragma unroll
-            for (int x = 0; x < 4; ++x) {
+            for (int x = 0; x < N; ++x) {
                 const int j = jb + x * 64 + lane;
                 f(j, order_key(v[x]), j < j1);
             }
@@ -322,6 +323,13 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __rest
     constexpr int kSelSub = NK == 8 ? 4 : 8;
     __shared__ __align__(16) uint32_t hist[256 * kSelSub];
     __shared__ uint32_t sel_bin, sel_above;
+    // A row that does not fit the registers is read once per pass; once the digit found so far leaves few enough
+    // candidates, the next pass also collects their keys here and the passes after it read these.  With sixteen loads
+    // of a lane in flight instead of four: 256 rows of 131072 scores 318 -> 178 us.  (Keys in registers gain nothing by it:
+    // 1024 rows of 10368 43.9 -> 43.1 us, and 4 KB more of LDS leave one folded block per CU.)
+    constexpr int kCand = NK == 0 ? 8192 : 1;
+    __shared__ uint32_t cand[kCand];
+    __shared__ uint32_t sel_count, n_cand;
     __shared__ uint32_t cnt_gt[kSelWaves], cnt_eq[kSelWaves];
     if constexpr (FOLD) {
         if (blockIdx.x < 2) {                        // first, so that they start with the first rows
@@ -415,16 +423,33 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __rest
         int bits_left = diff ? 32 - __clz((int)diff) : 0;          // low bits still to be resolved
         mask = bits_left >= 32 ? 0u : ~((1u << bits_left) - 1u);
         prefix = all_or & mask;
+        bool few = false, collected = false;    // block-uniform
         while (bits_left > 0) {
             const int width = min(8, bits_left);
             const int shift = bits_left - width;
             const uint32_t dmask = (1u << width) - 1u;
             for (int x = tid; x < 256 * kSelSub / 4; x += kSelThreads)
                 reinterpret_cast<uint4*>(hist)[x] = make_uint4(0, 0, 0, 0);
+            if (NK == 0 && few && !collected && tid == 0) n_cand = 0;
             __syncthreads();
-            for_keys<NK>(key, s, j0, j1, lane, [&](int, uint32_t u, bool in) {
-                if (in && (u & mask) == prefix) atomicAdd(&hist[((u >> shift) & dmask) * kSelSub + (lane & (kSelSub - 1))], 1u);
-            });
+            auto count = [&](uint32_t u) { atomicAdd(&hist[((u >> shift) & dmask) * kSelSub + (lane & (kSelSub - 1))], 1u); };
+            if (NK == 0 && collected) {
+                const int n = (int)n_cand;
+                for (int x = tid; x < n; x += kSelThreads)
+                    if ((cand[x] & mask) == prefix) count(cand[x]);
+            } else if (NK == 0 && few) {
+                for_keys<NK>(key, s, j0, j1, lane, [&](int, uint32_t u, bool in) {
+                    if (in && (u & mask) == prefix) {
+                        count(u);
+                        cand[atomicAdd(&n_cand, 1u)] = u;          // as many as the last pass counted in the bin
+                    }
+                });
+                collected = true;
+            } else {
+                for_keys<NK>(key, s, j0, j1, lane, [&](int, uint32_t u, bool in) {
+                    if (in && (u & mask) == prefix) count(u);
+                });
+            }
             __syncthreads();
             if (wave == 0) {
                 // lane i owns bins 4i..4i+3; find the highest bin whose count, added to everything
@@ -447,7 +472,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __rest
                 if (above < remaining && remaining <= above + tot) {
 #pragma unroll
                     for (int x = 3; x >= 0; --x) {
-                        if (above + c[x] >= remaining) { sel_bin = lane * 4 + x; sel_above = above; break; }
+                        if (above + c[x] >= remaining) { sel_bin = lane * 4 + x; sel_above = above; sel_count = c[x]; break; }
                         above += c[x];
                     }
                 }
@@ -456,6 +481,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __rest
             prefix |= sel_bin << shift;
             mask |= dmask << shift;
             remaining -= sel_above;            // those above are all kept; keep looking inside the bin
+            few = sel_count <= (uint32_t)kCand;
             bits_left = shift;
             __syncthreads();
         }
@@ -619,7 +645,8 @@ hipError_t launch_topk_compact(const vlc_cache& c, const int32_t* lens, const fl
     const vlc_shape& s = c.shape;
     const int rows = s.B * s.L * s.Hkv;
     LayoutArgs la{k, lens, s.B, s.L, s.Hkv, s.m, s.tau, s.d, c.T_max, c.slots_per_request};
-    // values per lane of a wave's segment (an eighth of the row, rounded up to whole wave loads)
+    // values per lane of a wave's segment (an eighth of the row, rounded up to whole wave loads); a form for 12 because
+    // every pass visits all register slots (2048 rows of 4099 scores, 9 per lane: 62 us in the form for 24, 45 in this)
     const int per_lane = (((s.m + kSelWaves - 1) / kSelWaves + 63) / 64);
     // the layout as one more block of the selection (short rows only), or as a kernel of its own
     const bool fold = c.opt.select_fold == 2 && per_lane <= 8;
@@ -627,6 +654,7 @@ hipError_t launch_topk_compact(const vlc_cache& c, const int32_t* lens, const fl
 #define VLC_SELECT(NK) select_kernel<NK, false, false><<<rows, kSelThreads, 0, st>>>(scores, c.dev, s.L, s.Hkv, s.m, lens != nullptr, c.T_max, n_recent, recent_num, recent_den, idx_out, nullptr, nullptr, la)
     if (fold) select_kernel<8, false, true><<<rows + 2, kSelThreads, 0, st>>>(scores, c.dev, s.L, s.Hkv, s.m, lens != nullptr, c.T_max, n_recent, recent_num, recent_den, idx_out, nullptr, nullptr, la);
     else if (per_lane <= 8) VLC_SELECT(8);
+    else if (per_lane <= 12) VLC_SELECT(12);
     else if (per_lane <= 24) VLC_SELECT(24);
     else if (per_lane <= 64) VLC_SELECT(64);
     else VLC_SELECT(0);
@@ -658,6 +686,7 @@ hipError_t launch_cache_hit_count(const vlc_cache& c, const float* scores_star, 
     const int per_lane = (((s.m + kSelWaves - 1) / kSelWaves + 63) / 64);
 #define VLC_HITS(NK) select_kernel<NK, true, false><<<rows, kSelThreads, 0, st>>>(scores_star, c.dev, s.L, s.Hkv, s.m, c.ragged, c.T_max, 0, 0, 0, nullptr, hits_out, rate_out, LayoutArgs{})
     if (per_lane <= 8) VLC_HITS(8);
+    else if (per_lane <= 12) VLC_HITS(12);
     else if (per_lane <= 24) VLC_HITS(24);
     else if (per_lane <= 64) VLC_HITS(64);
     else VLC_HITS(0);

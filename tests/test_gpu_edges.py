@@ -175,6 +175,34 @@ def test_topk_row_lengths_around_the_register_resident_limits(m):
             assert torch.equal(kc[h], K[0, 0, h][torch.from_numpy(want).cuda()])
 
 
+@pytest.mark.parametrize("kind", ["few above", "one bin", "flat", "signs"])
+def test_topk_of_streamed_rows_collects_the_candidates(kind):
+    """Rows that do not fit the registers: the candidates of the cut's bin fit the collecting buffer (8192 keys) after
+    the first digit, after a later one, or never; and a work list of many units per row (positions of every unit)."""
+    V = _V()
+    m = 70003
+    r = np.random.default_rng(5)
+    s = r.random((1, 1, 2, m)).astype(np.float32)
+    if kind == "few above":
+        s = np.exp(4 * s).astype(np.float32)
+    elif kind == "one bin":                            # all but one key share the first digits, 20000 of them all but the last bits
+        s = (1.0 + s * 2.0 ** -12).astype(np.float32)
+        s[..., :20000] = 1.0 + 2.0 ** -22
+        s[..., 17] = 1000.0
+    elif kind == "flat":                               # more equal keys than the buffer holds, the cut among them
+        s = np.where(s < 0.9, np.float32(0.25), s).astype(np.float32)
+    else:
+        s = (s - 0.5).astype(np.float32)
+    for k, n_recent in [(m // 10, 0), (30011, 700), (1, 0)]:
+        cache, idx_out, K, Vv, view = _topk_case(V, s, np.array([[k]]), n_recent, m, d=64)
+        V.vlc_cache_status(cache)
+        kc, vc, idx = view(cache, 0, 0)
+        for h in range(2):
+            want = O.topk(s[0, 0, h].astype(np.float64), k, n_recent)
+            assert np.array_equal(idx[h].cpu().numpy(), want), (kind, k, n_recent, h)
+            assert torch.equal(vc[h], Vv[0, 0, h][torch.from_numpy(want).cuda()])
+
+
 def test_device_side_errors_are_sticky_and_harmless():
     V = _V()
     m = 300
