@@ -35,12 +35,13 @@ __device__ __forceinline__ RowUnits row_units(int kk, int T_max, int ub, int us)
     return RowUnits{big, (rem + us - 1) / us, big + (rem + T_max + us - 1) / us};
 }
 
-// Runs in TWO blocks of NT threads (every thread of a block must enter): the lists are independent of each other
-// once budgets and slab offsets are known, and those are cheap, so both blocks derive them and part 0 writes them
-// out, zeroes the counters and builds the layer-ordered list, while part 1 builds the list of the all-layer launches
-// (and the gather's, when that is a list of its own).  Errors are reported by part 0.
+// Runs in several blocks of NT threads (every thread of a block must enter): the lists are independent of each other
+// once budgets and slab offsets are known, and those are cheap, so every block derives them.  A block builds the lists
+// of the bit mask `lists`, and of those the records of every shares-th group of rows, from its own `share` on (the
+// prefix sums are repeated in each block, the records are what takes the time: 58,000 of 64 bytes for one prompt
+// of 131,072 tokens, 44 us with one block per list, 12 with sixteen; four prompts of 10,368, 22 -> 15).  The first block of list 0 also writes out budgets and offsets, zeroes the counters and reports errors.
 template <int NT>
-__device__ void layout_body(const LayoutArgs& a, CacheDev dev, int part) {
+__device__ void layout_body(const LayoutArgs& a, CacheDev dev, int lists, int share, int shares) {
     const int32_t* __restrict__ k = a.k;
     const int32_t* __restrict__ lens = a.lens;
     const int B = a.B, L = a.L, Hkv = a.Hkv, m = a.m, tau = a.tau, d = a.d, T_max = a.T_max;
@@ -55,7 +56,7 @@ __device__ void layout_body(const LayoutArgs& a, CacheDev dev, int part) {
     __shared__ uint32_t sSort[kLayoutMaxBL];        // (request, layer) entries in the order of the size-class walk's second class
     const int tid = threadIdx.x;
     const int BL = B * L;
-    const bool first = part == 0;               // the part that owns everything but the lists of part 1
+    const bool first = (lists & 1) && share == 0;           // the block that owns everything but the lists
     if (first && tid < 4) dev.status[tid] = 0;
     __syncthreads();
     // per-request lengths: checked here (the only place with an error channel), kept in the cache
@@ -140,16 +141,17 @@ __device__ void layout_body(const LayoutArgs& a, CacheDev dev, int part) {
         if (tid == 0) { sTotals[0] = (int)(total2 >> 32); sTotals[1] = (int)(total2 & 0xffffffff); }
         if (total > wl.cap) {                   // cannot happen for budgets that passed the capacity check
             if (tid == 0) {
-                set_sticky(dev.status, VLC_ERR_CAPACITY, -1, -1, -1);
+                if (share == 0) set_sticky(dev.status, VLC_ERR_CAPACITY, -1, -1, -1);
                 sBad = 1;
             }
-            for (int l = tid; l <= L + 1; l += NT) wl.layer_start[l] = 0;
+            if (share == 0)
+                for (int l = tid; l <= L + 1; l += NT) wl.layer_start[l] = 0;
         } else {
             int64_t acc = inc - run, acc2 = inc2 - run2;
             for (int y = y0; y < y1; ++y) {
                 const int l = y / B, b = y % B;
                 const RowUnits ru = row_units(sKept[b * L + l], T_max, ub, us);
-                if (b == 0) wl.layer_start[l] = (int)acc;
+                if (b == 0 && share == 0) wl.layer_start[l] = (int)acc;
                 sFirst[b * L + l] = (int)acc;
                 sBigFirst[b * L + l] = (int)(acc2 >> 32);
                 sLiveFirst[b * L + l] = (int)(acc2 & 0xffffffff);
@@ -157,7 +159,7 @@ __device__ void layout_body(const LayoutArgs& a, CacheDev dev, int part) {
                 acc += (int64_t)ru.total * Hkv;
                 acc2 += ((int64_t)ru.big * Hkv << 32) | (int64_t)(ru.live * Hkv);
             }
-            if (tid == 0) wl.layer_start[L] = (int)total;
+            if (tid == 0 && share == 0) wl.layer_start[L] = (int)total;
         }
         __syncthreads();
         if (sBad) return;
@@ -216,8 +218,11 @@ __device__ void layout_body(const LayoutArgs& a, CacheDev dev, int part) {
             __syncthreads();
         }
         const int n_big = sTotals[0], n_live = sTotals[1];
-        if (tid == 0) wl.layer_start[L + 1] = n_big;               // decode reverses the walk over the u_big units on odd steps
-        for (int x = tid; x < BL * Hkv; x += NT) {
+        if (tid == 0 && share == 0) wl.layer_start[L + 1] = n_big;               // decode reverses the walk over the u_big units on odd steps
+        // rows of many units: sixteen lanes per row, a record each; else a lane per row (where the lanes are few, the
+        // sixteen would walk the rows too many times: folded, 256 rows of 3 units, 10.5 -> 12.9 us)
+        const int lg = total > (shares > 1 ? 4 : 16) * BL * Hkv ? 4 : 0, ul = tid & ((1 << lg) - 1);
+        for (int x = share * (NT >> lg) + (tid >> lg); x < BL * Hkv; x += shares * (NT >> lg)) {
             const int h = x % Hkv, bl = x / Hkv, b = bl / L, l = bl % L;
             const int kk = sKept[bl];
             const RowUnits ru = row_units(kk, T_max, ub, us);
@@ -232,8 +237,8 @@ __device__ void layout_body(const LayoutArgs& a, CacheDev dev, int part) {
             const int w0 = sFirst[bl] + h * ru.total;
             // units of the third class that precede this row's in the list (all units before it minus big and live)
             const int res0 = n_big + n_live + sResFirst[bl] + h * nres;
-            wl.row_first[x] = w0;
-            for (int u = 0; u < ru.total; ++u) {
+            if (ul == 0) wl.row_first[x] = w0;
+            for (int u = ul; u < ru.total; u += 1 << lg) {
                 it.unit = u;
                 it.key0 = u < ru.big ? u * ub : ru.big * ub + (u - ru.big) * us;
                 it.ucap = u < ru.big ? ub : us;
@@ -248,16 +253,21 @@ __device__ void layout_body(const LayoutArgs& a, CacheDev dev, int part) {
             }
         }
     };
-    if (first) {
-        build_list(dev.list[0]);
-    } else {
-        build_list(dev.list[1]);
-        if (dev.list[2].items != dev.list[0].items && dev.list[2].items != dev.list[1].items) build_list(dev.list[2]);   // else the gather shares a decode list
-    }
+    if (lists & 1) build_list(dev.list[0]);
+    if (lists & 2) build_list(dev.list[1]);
+    if (lists & 4) build_list(dev.list[2]);
     static_assert(kNumLists == 3, "one call per list");
 }
 
-__global__ __launch_bounds__(256) void layout_kernel(LayoutArgs a, CacheDev dev) { layout_body<256>(a, dev, (int)blockIdx.x); }   // two blocks
+// The gather's list may be one of the decode lists.
+__host__ __device__ __forceinline__ bool own_gather_list(const CacheDev& dev) {
+    return dev.list[2].items != dev.list[0].items && dev.list[2].items != dev.list[1].items;
+}
+
+constexpr int kLayoutShares = 16;       // blocks per list
+__global__ __launch_bounds__(256) void layout_kernel(LayoutArgs a, CacheDev dev) {
+    layout_body<256>(a, dev, 1 << (blockIdx.x / kLayoutShares), blockIdx.x % kLayoutShares, kLayoutShares);
+}
 
 // Order-preserving map float -> uint32 (larger float, larger key).
 __device__ __forceinline__ uint32_t order_key(float f) {
@@ -333,7 +343,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __rest
     __shared__ uint32_t cnt_gt[kSelWaves], cnt_eq[kSelWaves];
     if constexpr (FOLD) {
         if (blockIdx.x < 2) {                        // first, so that they start with the first rows
-            layout_body<kSelThreads>(la, dev, (int)blockIdx.x);
+            layout_body<kSelThreads>(la, dev, blockIdx.x == 0 ? 1 : own_gather_list(dev) ? 6 : 2, 0, 1);
             return;
         }
     }
@@ -650,7 +660,7 @@ hipError_t launch_topk_compact(const vlc_cache& c, const int32_t* lens, const fl
     const int per_lane = (((s.m + kSelWaves - 1) / kSelWaves + 63) / 64);
     // the layout as one more block of the selection (short rows only), or as a kernel of its own
     const bool fold = c.opt.select_fold == 2 && per_lane <= 8;
-    if (!fold) layout_kernel<<<2, 256, 0, st>>>(la, c.dev);
+    if (!fold) layout_kernel<<<kLayoutShares * (own_gather_list(c.dev) ? 3 : 2), 256, 0, st>>>(la, c.dev);
 #define VLC_SELECT(NK) select_kernel<NK, false, false><<<rows, kSelThreads, 0, st>>>(scores, c.dev, s.L, s.Hkv, s.m, lens != nullptr, c.T_max, n_recent, recent_num, recent_den, idx_out, nullptr, nullptr, la)
     if (fold) select_kernel<8, false, true><<<rows + 2, kSelThreads, 0, st>>>(scores, c.dev, s.L, s.Hkv, s.m, lens != nullptr, c.T_max, n_recent, recent_num, recent_den, idx_out, nullptr, nullptr, la);
     else if (per_lane <= 8) VLC_SELECT(8);
