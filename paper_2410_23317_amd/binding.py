@@ -126,7 +126,8 @@ def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # the handle itself: torch.cuda.current_stream() builds a Stream object around it on every call
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 VLC_SHAPE_SCORE_PLAIN_ALU = 1
