@@ -48,9 +48,9 @@ def assert_close(got, want, atol, rtol, what):
     want = np.asarray(want, dtype=np.float64)
     err = np.abs(got - want)
     lim = atol + rtol * np.abs(want)
-    bad = err > lim
+    bad = ~((err <= lim) | (got == want))           # a NaN is never within a tolerance
     if bad.any():
-        i = np.unravel_index(np.argmax(err - lim), err.shape)
+        i = np.unravel_index(np.argmax(np.where(bad, np.nan_to_num(err - lim, nan=np.inf), -np.inf)), err.shape)
         raise AssertionError(f"{what}: {int(bad.sum())} of {bad.size} outside atol={atol} rtol={rtol}; "
                              f"worst at {i}: got {got[i]!r} want {want[i]!r}")
 
