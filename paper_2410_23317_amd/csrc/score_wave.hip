@@ -68,7 +68,8 @@ struct Form {
 struct Where {
     int hkv, bl, l, mb, tb, nb, nrb;        // nb: 32-row blocks per head, nrb: row blocks of this launch
     int k_begin, k_end, nt;                 // key range of the split, its 32-key tiles
-    float c;                                // logit scale in the exponent domain
+    float c;                                // magnitude of the logit scale in the exponent domain
+    float scale;                            // the layer's logit scale
 };
 __device__ __forceinline__ Where locate(const SweepArgs& a, int group, int split, int max_rb) {
     Where w;
@@ -80,8 +81,18 @@ __device__ __forceinline__ Where locate(const SweepArgs& a, int group, int split
     w.k_begin = split * a.keys_per_split;
     w.k_end = min(w.mb, w.k_begin + a.keys_per_split);
     w.nt = w.k_end > w.k_begin ? (w.k_end - w.k_begin + 31) >> 5 : 0;
-    w.c = (a.sm_scale ? a.sm_scale[w.l] : a.default_scale) * kLog2e;
+    w.scale = a.sm_scale ? a.sm_scale[w.l] : a.default_scale;
+    w.c = (w.scale == 0.f ? 1.f : fabsf(w.scale)) * kLog2e;
     return w;
+}
+
+// A logit is the product times the layer's scale.  The sweeps mask (-inf) and take maxima of the products, which
+// stands for the logits only where the scale is positive: so the scale's sign is moved to Q' (exact), and for a
+// scale of zero, where every logit is 0, Q' is.
+template <bool F32>
+__device__ __forceinline__ uint4 apply_sign(uint4 q, float scale) {
+    const uint32_t flip = scale < 0.f ? (F32 ? 0x80000000u : 0x80008000u) : 0u, keep = scale == 0.f ? 0u : 0xffffffffu;
+    return make_uint4((q.x ^ flip) & keep, (q.y ^ flip) & keep, (q.z ^ flip) & keep, (q.w ^ flip) & keep);
 }
 // Row r of the launch's row blocks: its head, its window row, and whether it exists.
 struct Row { int hl, iw; bool real; };
@@ -113,7 +124,7 @@ __device__ __forceinline__ void stage_q(const SweepArgs& a, const Where& w, char
         const int x = threadIdx.x + F::THREADS * u, r = x / F::CPR;
         const Row o = window_row(a, w, r);
         const char* src = a.q_win + (((size_t)w.bl * a.Hq + (size_t)w.hkv * a.g + (o.real ? o.hl : 0)) * a.tau + (o.real ? o.iw : 0)) * F::RBYTES;
-        q[u] = *reinterpret_cast<const uint4*>(src + (x % F::CPR) * 16);
+        q[u] = apply_sign<F::F32>(*reinterpret_cast<const uint4*>(src + (x % F::CPR) * 16), w.scale);
         if (!o.real) q[u] = make_uint4(0, 0, 0, 0);
     }
 #pragma unroll

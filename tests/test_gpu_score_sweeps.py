@@ -64,3 +64,47 @@ def test_sweeps_match_the_oracle(dtype, d, Hq, Hkv, lens):
             assert_close(row_max[b, l, :, : cfg.tau].cpu().numpy(), M, atol=2e-5, rtol=2e-6, what=what + " row_max")
             assert_close(row_sum[b, l, :, : cfg.tau].cpu().numpy(), Z, atol=0, rtol=5e-5, what=what + " row_sum")
             check_nnz(nnz[b, l].cpu().numpy(), t["q_win"], t["k"], scales[l], 0.01, what + " nnz")
+
+
+def _upload(dtype, d, L, Hq, Hkv, m, tau, cid):
+    """One request on the GPU (q_win [1,L,Hq,tau,d], k, v [1,L,Hkv,m,d]) and the host arrays of its layers."""
+    cfg = W.custom_config(cid=cid, name=f"wave-{cid}", dtype=dtype, d=d, Hq=Hq, Hkv=Hkv, m=m, tau=tau, lead_text=0, n_visual=m,
+                          L=L, B=1, sinks=4, alphas=((1, 5),))
+    dt = torch_dtype(cfg)
+    host = [W.layer_inputs(cfg, 0, l) for l in range(L)]
+    dev = [torch.from_numpy(np.stack([t[n] for t in host])[None]).to(dt).cuda() for n in ("q_win", "k", "v")]
+    return host, dev, W.sm_scale(cfg)
+
+
+def _score(V, q_win, k, sm, dtype, flags=0, stats=None):
+    """vlc_score (or, with stats = (row_max, row_sum), vlc_score_from_stats): scores, row_max, row_sum, counts."""
+    (B, L, Hq, tau, d), (Hkv, m) = q_win.shape, k.shape[2:4]
+    shape = V.make_shape(B, L, Hq, Hkv, d, m, tau, dtype, flags=flags)
+    new = lambda *s: torch.full(s, float("nan"), dtype=torch.float32, device="cuda")
+    scores, nnz = new(B, L, Hkv, m), torch.full((B, L, Hq), 77, dtype=torch.int64, device="cuda")
+    row_max, row_sum = stats or (new(B, L, Hq, tau), new(B, L, Hq, tau))
+    if stats:
+        V.vlc_score_from_stats(shape, q_win, k, sm, 0.01, row_max, row_sum, scores, nnz)
+    else:
+        ws = torch.full((V.vlc_workspace_bytes(shape),), 255, dtype=torch.uint8, device="cuda")
+        V.vlc_score(shape, q_win, k, sm, 0.01, scores, row_max, row_sum, nnz, ws)
+    torch.cuda.synchronize()
+    return scores, row_max, row_sum, nnz
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 64), ("f32", 128)])
+@pytest.mark.parametrize("plain", [False, True])
+def test_a_layers_logit_scale_may_be_zero_or_negative(dtype, d, plain):
+    """The scale is any finite number: zero makes every softmax uniform over the keys a row may see, a negative one
+    turns the order of the logits around.  The causal mask holds either way."""
+    import paper_2410_23317_amd as V
+    host, (q, k, _), _ = _upload(dtype, d, 4, 4, 2, 300, 21, 820)
+    scales = np.array([0.0, -0.09, 0.09, -0.0], dtype=np.float32)
+    scores, row_max, row_sum, nnz = _score(V, q, k, torch.from_numpy(scales).cuda(), dtype, int(plain) * V.VLC_SHAPE_SCORE_PLAIN_ALU)
+    for l, t in enumerate(host):
+        what = f"scale {scales[l]}"
+        psi, _, M, Z = O.score(t["q_win"], t["k"], scales[l])
+        assert_close(scores[0, l].cpu().numpy(), psi, what=what + " scores", **SCORE_TOL)
+        assert_close(row_max[0, l].cpu().numpy(), M, atol=2e-5, rtol=2e-6, what=what + " row_max")
+        assert_close(row_sum[0, l].cpu().numpy(), Z, atol=0, rtol=5e-5, what=what + " row_sum")
+        check_nnz(nnz[0, l].cpu().numpy(), t["q_win"], t["k"], scales[l], 0.01, what + " nnz")
