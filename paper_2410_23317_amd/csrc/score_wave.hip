@@ -86,14 +86,6 @@ __device__ __forceinline__ Where locate(const SweepArgs& a, int group, int split
     return w;
 }
 
-// A logit is the product times the layer's scale.  The sweeps mask (-inf) and take maxima of the products, which
-// stands for the logits only where the scale is positive: so the scale's sign is moved to Q' (exact), and for a
-// scale of zero, where every logit is 0, Q' is.
-template <bool F32>
-__device__ __forceinline__ uint4 apply_sign(uint4 q, float scale) {
-    const uint32_t flip = scale < 0.f ? (F32 ? 0x80000000u : 0x80008000u) : 0u, keep = scale == 0.f ? 0u : 0xffffffffu;
-    return make_uint4((q.x ^ flip) & keep, (q.y ^ flip) & keep, (q.z ^ flip) & keep, (q.w ^ flip) & keep);
-}
 // Row r of the launch's row blocks: its head, its window row, and whether it exists.
 struct Row { int hl, iw; bool real; };
 __device__ __forceinline__ Row window_row(const SweepArgs& a, const Where& w, int r) {
@@ -124,13 +116,21 @@ __device__ __forceinline__ void stage_q(const SweepArgs& a, const Where& w, char
         const int x = threadIdx.x + F::THREADS * u, r = x / F::CPR;
         const Row o = window_row(a, w, r);
         const char* src = a.q_win + (((size_t)w.bl * a.Hq + (size_t)w.hkv * a.g + (o.real ? o.hl : 0)) * a.tau + (o.real ? o.iw : 0)) * F::RBYTES;
-        q[u] = apply_sign<F::F32>(*reinterpret_cast<const uint4*>(src + (x % F::CPR) * 16), w.scale);
+        q[u] = *reinterpret_cast<const uint4*>(src + (x % F::CPR) * 16);
         if (!o.real) q[u] = make_uint4(0, 0, 0, 0);
     }
+    // A logit is the product times the layer's scale.  The sweeps mask (-inf) and take maxima of the products, which
+    // stand for the logits only where the scale is positive: so Q' takes the scale's sign (exact), and is zero for a
+    // scale of zero, where every logit is 0.  (The scale is first looked at here: a wait for it in front of the
+    // requests above costs a small sweep 0.4 us of 9.)
+    uint32_t scale = __float_as_uint(w.scale);
+    asm volatile("" : "+s"(scale) : : "memory");
+    const uint32_t flip = (scale >> 31) * (F::F32 ? 0x80000000u : 0x80008000u), keep = scale << 1 ? 0xffffffffu : 0u;
 #pragma unroll
     for (int u = 0; u < F::NQ; ++u) {
         const int x = threadIdx.x + F::THREADS * u;
-        *reinterpret_cast<uint4*>(sQ + (x / F::CPR) * F::PITCH + (x % F::CPR) * 16) = q[u];
+        *reinterpret_cast<uint4*>(sQ + (x / F::CPR) * F::PITCH + (x % F::CPR) * 16) =
+            make_uint4((q[u].x ^ flip) & keep, (q[u].y ^ flip) & keep, (q[u].z ^ flip) & keep, (q[u].w ^ flip) & keep);
     }
 }
 
