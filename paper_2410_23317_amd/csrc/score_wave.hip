@@ -107,7 +107,9 @@ __device__ __forceinline__ void load_keys(const char* kg, int key0, int mb, int 
     for (int s = 0; s < KS; ++s) kf[s] = *reinterpret_cast<const uint4*>(base + off + s * 32);
 }
 
-// The block's Q' rows into LDS; rows that do not exist are zero.  All requests of a thread are in flight together.
+// The block's Q' rows into LDS.  A row that does not exist takes the values of its head's last row, which sees every key:
+// its products are then the numbers of a row that exists, and drop out by an exponent of -inf (zeros would not: times a
+// key's infinite entry they are NaN).  All requests of a thread are in flight together.
 template <typename F>
 __device__ __forceinline__ void stage_q(const SweepArgs& a, const Where& w, char* sQ) {
     uint4 q[F::NQ];
@@ -115,9 +117,8 @@ __device__ __forceinline__ void stage_q(const SweepArgs& a, const Where& w, char
     for (int u = 0; u < F::NQ; ++u) {
         const int x = threadIdx.x + F::THREADS * u, r = x / F::CPR;
         const Row o = window_row(a, w, r);
-        const char* src = a.q_win + (((size_t)w.bl * a.Hq + (size_t)w.hkv * a.g + (o.real ? o.hl : 0)) * a.tau + (o.real ? o.iw : 0)) * F::RBYTES;
+        const char* src = a.q_win + (((size_t)w.bl * a.Hq + (size_t)w.hkv * a.g + min(o.hl, a.g - 1)) * a.tau + min(o.iw, w.tb - 1)) * F::RBYTES;
         q[u] = *reinterpret_cast<const uint4*>(src + (x % F::CPR) * 16);
-        if (!o.real) q[u] = make_uint4(0, 0, 0, 0);
     }
     // A logit is the product times the layer's scale.  The sweeps mask (-inf) and take maxima of the products, which
     // stand for the logits only where the scale is positive: so Q' takes the scale's sign (exact), and is zero for a

@@ -108,3 +108,26 @@ def test_a_layers_logit_scale_may_be_zero_or_negative(dtype, d, plain):
         assert_close(row_max[0, l].cpu().numpy(), M, atol=2e-5, rtol=2e-6, what=what + " row_max")
         assert_close(row_sum[0, l].cpu().numpy(), Z, atol=0, rtol=5e-5, what=what + " row_sum")
         check_nnz(nnz[0, l].cpu().numpy(), t["q_win"], t["k"], scales[l], 0.01, what + " nnz")
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 64), ("f32", 128)])
+@pytest.mark.parametrize("plain", [False, True])
+def test_keys_with_infinite_entries_score_zero(dtype, d, plain):
+    """Keys that every window row gives a logit of -inf (a caller's way to mask them) have weight 0 and disturb no other
+    key, also where window rows are padded to whole row blocks."""
+    import paper_2410_23317_amd as V
+    host, (q, k, _), scales = _upload(dtype, d, 2, 4, 2, 300, 21, 821)
+    gone = [0, 5, 31, 32, 190, 277]                     # the last key that every row sees is 279
+    q[..., 0] = 1.0
+    k[:, :, :, gone, 0] = float("-inf")
+    scores, row_max, row_sum, nnz = _score(V, q, k, torch.from_numpy(scales).cuda(), dtype, int(plain) * V.VLC_SHAPE_SCORE_PLAIN_ALU)
+    for l in range(2):
+        what = f"l={l}"
+        qh, kh = q[0, l].float().cpu().numpy(), k[0, l].float().cpu().numpy()
+        psi, _, M, Z = O.score(qh, kh, scales[l])
+        assert np.all(psi[:, gone] == 0)
+        assert_close(scores[0, l].cpu().numpy(), psi, what=what + " scores", **SCORE_TOL)
+        assert_close(row_max[0, l].cpu().numpy(), M, atol=2e-5, rtol=2e-6, what=what + " row_max")
+        assert_close(row_sum[0, l].cpu().numpy(), Z, atol=0, rtol=5e-5, what=what + " row_sum")
+        nnz_o, *_ = O.sparsity(qh, kh, scales[l], 0.01)
+        assert np.abs(nnz[0, l].cpu().numpy() - nnz_o).sum() <= 2       # a threshold decision within rounding
