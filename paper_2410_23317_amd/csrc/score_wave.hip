@@ -31,7 +31,7 @@ struct SweepArgs {
     const char* q_win;
     const char* k;
     const float* sm_scale;
-    float2* part;            // [group][split][g * tau] partial (max, sum), exponent domain (log2)
+    float2* part;            // [group][split][g * tau] partial (maximum M of the products, sum relative to 2^offset(M))
     const float* row_max;    // natural-log domain, [B,L,Hq,tau]
     const float* row_sum;    // null: count only
     const float2* part_in;   // sweep 2: partials of sweep 1 to merge in the prologue, or null (statistics given)
@@ -68,8 +68,8 @@ struct Form {
 struct Where {
     int hkv, bl, l, mb, tb, nb, nrb;        // nb: 32-row blocks per head, nrb: row blocks of this launch
     int k_begin, k_end, nt;                 // key range of the split, its 32-key tiles
-    float c;                                // magnitude of the logit scale in the exponent domain
-    float scale;                            // the layer's logit scale
+    float scale, c;                         // magnitude of the layer's logit scale (1 if it is zero), the same in the exponent domain
+    float signed_scale;
 };
 __device__ __forceinline__ Where locate(const SweepArgs& a, int group, int split, int max_rb) {
     Where w;
@@ -81,10 +81,27 @@ __device__ __forceinline__ Where locate(const SweepArgs& a, int group, int split
     w.k_begin = split * a.keys_per_split;
     w.k_end = min(w.mb, w.k_begin + a.keys_per_split);
     w.nt = w.k_end > w.k_begin ? (w.k_end - w.k_begin + 31) >> 5 : 0;
-    w.scale = a.sm_scale ? a.sm_scale[w.l] : a.default_scale;
-    w.c = (w.scale == 0.f ? 1.f : fabsf(w.scale)) * kLog2e;
+    w.signed_scale = a.sm_scale ? a.sm_scale[w.l] : a.default_scale;
+    w.scale = w.signed_scale == 0.f ? 1.f : fabsf(w.signed_scale);
+    w.c = w.scale * kLog2e;
     return w;
 }
+
+// Exponent offset of a row whose largest product is m: rounded by itself, so that the same maximum gives the same number
+// everywhere (fused into a subtraction it would be another).
+__device__ __forceinline__ float exp_offset(float m, float c) {
+    float o = m * c;
+    asm("" : "+v"(o));
+    return o;
+}
+// Row statistics as the caller sees them.  A row's maximum is a rounded number, and exponents are measured from another
+// rounded number, its offset; at logits of a few hundred the two differ by 1e-5.  So the row sum that is handed out belongs to the
+// maximum that is handed out, and what rounding the offset of a given maximum leaves over goes into its row's factor: fp32, d = 128,
+// logits up to 123, scores from vlc_score's own statistics 8.1e-7 off -> 3.3e-7, as its scores are.
+__device__ __forceinline__ double exponent_per_logit(const Where& w) {      // c as rounded over the scale's magnitude
+    return (double)kLog2e + (double)(fmaf(-w.scale, kLog2e, w.c) / w.scale);
+}
+__device__ __forceinline__ float exp2_rest(float a, double b) { return fabsf(a) < INFINITY ? exp2_fast((float)((double)a - b)) : 1.f; }
 
 // Row r of the launch's row blocks: its head, its window row, and whether it exists.
 struct Row { int hl, iw; bool real; };
@@ -124,7 +141,7 @@ __device__ __forceinline__ void stage_q(const SweepArgs& a, const Where& w, char
     // stand for the logits only where the scale is positive: so Q' takes the scale's sign (exact), and is zero for a
     // scale of zero, where every logit is 0.  (The scale is first looked at here: a wait for it in front of the
     // requests above costs a small sweep 0.4 us of 9.)
-    uint32_t scale = __float_as_uint(w.scale);
+    uint32_t scale = __float_as_uint(w.signed_scale);
     asm volatile("" : "+s"(scale) : : "memory");
     const uint32_t flip = (scale >> 31) * (F::F32 ? 0x80000000u : 0x80008000u), keep = scale << 1 ? 0xffffffffu : 0u;
 #pragma unroll
@@ -199,12 +216,12 @@ __global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void rowstats_wave_k
                 float tmax = v[0];
 #pragma unroll
                 for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, v[i]);
-                const float m_new = fmaxf(m_run[rb], tmax * w.c);
-                const float m_use = m_new > -INFINITY ? m_new : 0.f;      // a row that has seen no key yet: every term is 0
+                const float m_new = fmaxf(m_run[rb], tmax);
+                const float m_use = m_new > -INFINITY ? exp_offset(m_new, w.c) : 0.f;     // a row that has seen no key yet: every term is 0
                 float zs = 0.f;
 #pragma unroll
                 for (int i = 0; i < 16; ++i) zs += exp2_fast(fmaf(v[i], w.c, -m_use));
-                z_run[rb] = z_run[rb] * exp2_fast(m_run[rb] - m_use) + zs;
+                z_run[rb] = z_run[rb] * exp2_fast(exp_offset(m_run[rb], w.c) - m_use) + zs;
                 m_run[rb] = m_new;
             }
         }
@@ -215,10 +232,10 @@ __global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void rowstats_wave_k
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) {
         const float mo = __shfl_xor(m_run[rb], 32, 64), zo = __shfl_xor(z_run[rb], 32, 64);
-        const float mm = fmaxf(m_run[rb], mo);
+        const float mm = fmaxf(m_run[rb], mo), om = exp_offset(mm, w.c);
         float z = 0.f;
-        if (m_run[rb] > -INFINITY) z += z_run[rb] * exp2_fast(m_run[rb] - mm);
-        if (mo > -INFINITY) z += zo * exp2_fast(mo - mm);
+        if (m_run[rb] > -INFINITY) z += z_run[rb] * exp2_fast(exp_offset(m_run[rb], w.c) - om);
+        if (mo > -INFINITY) z += zo * exp2_fast(exp_offset(mo, w.c) - om);
         if (lane < 32) sStat[wave * F::ROWS + rb * 32 + lane] = make_float2(mm, z);
     }
     __syncthreads();
@@ -231,7 +248,7 @@ __global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void rowstats_wave_k
 #pragma unroll
         for (int v = 0; v < W; ++v) {
             const float2 s = sStat[v * F::ROWS + r];
-            if (s.x > -INFINITY) Z += s.y * exp2_fast(s.x - M);
+            if (s.x > -INFINITY) Z += s.y * exp2_fast(exp_offset(s.x, w.c) - exp_offset(M, w.c));
         }
         a.part[((size_t)group * a.nsplit + split) * a.g * a.tau + o.hl * a.tau + o.iw] = make_float2(M, Z);
     }
@@ -282,20 +299,24 @@ __global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void colsweep_wave_k
 #pragma unroll
                 for (int sp = 0; sp < kSplitRegs; ++sp) Mn = fmaxf(Mn, pin[sp].x);
                 if (Mn > -INFINITY) {
-                    Z *= exp2_fast(M - Mn);                 // 0 on the first round (M = -inf)
+                    const float on = exp_offset(Mn, w.c);
+                    Z *= exp2_fast(exp_offset(M, w.c) - on);            // 0 on the first round (M = -inf)
 #pragma unroll
                     for (int sp = 0; sp < kSplitRegs; ++sp)
-                        if (pin[sp].x > -INFINITY) Z += pin[sp].y * exp2_fast(pin[sp].x - Mn);
+                        if (pin[sp].x > -INFINITY) Z += pin[sp].y * exp2_fast(exp_offset(pin[sp].x, w.c) - on);
                     M = Mn;
                 }
             }
-            st = make_float2(M, 1.f / Z);
+            const float off = exp_offset(M, w.c);
+            st = make_float2(off, 1.f / Z);
             if (split == 0) {
-                if (a.row_max_out) a.row_max_out[x] = M * kLn2;
-                if (a.row_sum_out) a.row_sum_out[x] = Z;
+                const float row_max = M * w.scale;
+                if (a.row_max_out) a.row_max_out[x] = row_max;
+                if (a.row_sum_out) a.row_sum_out[x] = Z * exp2_rest(off, (double)row_max * exponent_per_logit(w));
             }
         } else if (mine) {
-            st = make_float2(a.row_max[x] * kLog2e, a.row_sum ? 1.f / a.row_sum[x] : 0.f);
+            const double offset = (double)a.row_max[x] * exponent_per_logit(w);
+            st = make_float2((float)offset, a.row_sum ? exp2_rest((float)offset, offset) / a.row_sum[x] : 0.f);
         }
         sConst[threadIdx.x] = st;
     }

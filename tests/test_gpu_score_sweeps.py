@@ -131,3 +131,17 @@ def test_keys_with_infinite_entries_score_zero(dtype, d, plain):
         assert_close(row_sum[0, l].cpu().numpy(), Z, atol=0, rtol=5e-5, what=what + " row_sum")
         nnz_o, *_ = O.sparsity(qh, kh, scales[l], 0.01)
         assert np.abs(nnz[0, l].cpu().numpy() - nnz_o).sum() <= 2       # a threshold decision within rounding
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 64), ("f32", 128)])
+def test_scores_from_the_calls_own_statistics_are_as_accurate_as_its_scores(dtype, d):
+    """vlc_score_from_stats on the row maxima and sums that vlc_score wrote.  A row's maximum is rounded to fp32, which at
+    logits of a few hundred shifts every exponent by 1e-5; the row sum belongs to the rounded value, so the shift
+    cancels and the two calls agree to the rounding of an exponential and a sum (a few times 2^-24 per term, 6e-8)."""
+    import paper_2410_23317_amd as V
+    _, (q, k, _), _ = _upload(dtype, d, 2, 4, 2, 1500, 33, 822)
+    sm = torch.tensor([3.1, 0.7], device="cuda")        # logits of up to about 500
+    scores, row_max, row_sum, _ = _score(V, q, k, sm, dtype)
+    again = _score(V, q, k, sm, dtype, stats=(row_max, row_sum))[0]
+    want = scores.double()
+    assert ((again.double() - want).norm() / want.norm()).item() < 3e-7
