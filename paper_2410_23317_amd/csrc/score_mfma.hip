@@ -61,7 +61,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 0) void rowstats_mfma_
     const int group = blockIdx.x, split = blockIdx.y;       // group-major: see the launch
     const int hkv = group % a.Hkv, bl = group / a.Hkv, l = bl % a.L;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;     // wave index in a scalar register
-    const float c = (a.sm_scale ? a.sm_scale[l] : rsqrtf((float)kD)) * kLog2e;
+    const float scale = a.sm_scale ? a.sm_scale[l] : rsqrtf((float)kD), c = exp_scale(scale);
     const bf16_t* kg = a.k + (size_t)group * a.m * kD;
     const ReqLen rl = request_len(a.lens, bl / a.L, a.m, a.tau);
     const int mb = rl.m, tb = rl.tau;                       // this request's prompt and window length
@@ -87,6 +87,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 0) void rowstats_mfma_
 
     KStage<THREADS> st;
     if (k_begin < k_end) st.load(kg, k_begin, mb);
+    sign_q_frags(qf, scale);
     for (int kc = k_begin; kc < k_end; kc += kChunk) {
         __syncthreads();                                   // previous chunk fully consumed
         st.store(sK);
@@ -151,7 +152,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 4) void colsweep_mfma_
     const int group = blockIdx.x, split = blockIdx.y;       // group-major: see the launch
     const int hkv = group % a.Hkv, bl = group / a.Hkv, l = bl % a.L;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;     // wave index in a scalar register
-    const float c = (a.sm_scale ? a.sm_scale[l] : rsqrtf((float)kD)) * kLog2e;
+    const float scale = a.sm_scale ? a.sm_scale[l] : rsqrtf((float)kD), c = exp_scale(scale);
     const bf16_t* kg = a.k + (size_t)group * a.m * kD;
     const ReqLen rl = request_len(a.lens, bl / a.L, a.m, a.tau);
     const int mb = rl.m, tb = rl.tau;                       // this request's prompt and window length
@@ -176,6 +177,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 4) void colsweep_mfma_
     if (k_begin < k_end) st.load(kg, k_begin, mb);
     uint4 qf[RB][kKSteps];
     load_q_frags<RB, WAVES>(a, bl, hkv, a.rb0 + wave, lane, tb, tauP, qf);      // row blocks rb0 + wave + WAVES * rb
+    sign_q_frags(qf, scale);
     // per accumulator slot: exponent offset (+inf for padded rows) and 1 / row sum
     float mc[RB][16], iz[RB][16];
     uint32_t cnt[RB];

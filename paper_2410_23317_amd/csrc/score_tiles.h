@@ -33,6 +33,27 @@ __device__ __forceinline__ void load_q_frags(const Args& a, int bl, int hkv, int
     }
 }
 
+// A logit is the product times the layer's scale.  The kernels mask (-inf) and take maxima of the products, which stand for
+// the logits only where the scale is positive: so Q' takes the scale's sign (exact), and is zero for a scale of zero, where
+// every logit is 0.  To be called after a block's first requests are out: the scale is looked at here.
+template <int RB>
+__device__ __forceinline__ void sign_q_frags(uint4 (&qf)[RB][kKSteps], float scale) {
+    uint32_t bits = __float_as_uint(scale);
+    asm volatile("" : "+v"(bits) : : "memory");
+    bits = __builtin_amdgcn_readfirstlane(bits);
+    if ((int)bits > 0) return;                              // block-uniform
+    const uint32_t flip = (bits >> 31) * 0x80008000u, keep = bits << 1 ? 0xffffffffu : 0u;
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int ks = 0; ks < kKSteps; ++ks) {
+            uint4& q = qf[rb][ks];
+            q = make_uint4((q.x ^ flip) & keep, (q.y ^ flip) & keep, (q.z ^ flip) & keep, (q.w ^ flip) & keep);
+        }
+}
+// Scale of the products in the exponent domain, with Q' signed as above.
+__device__ __forceinline__ float exp_scale(float scale) { return (scale == 0.f ? 1.f : fabsf(scale)) * kLog2e; }
+
 // Window rows of one head padded to whole 32-row blocks.
 __device__ __forceinline__ int padded_rows(int tb) { return (tb + 31) & ~31; }
 

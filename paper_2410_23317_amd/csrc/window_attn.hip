@@ -142,7 +142,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void window_attn_kernel(WinArgs a) {
     const int group = blockIdx.y, split = blockIdx.x;
     const int hkv = group % a.Hkv, bl = group / a.Hkv, l = bl % a.L;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const float c = (a.sm_scale ? a.sm_scale[l] : rsqrtf((float)kD)) * kLog2e;
+    const float scale = a.sm_scale ? a.sm_scale[l] : rsqrtf((float)kD), c = exp_scale(scale);
     const bf16_t* kg = a.k + (size_t)group * a.m * kD;
     const bf16_t* vg = a.v + (size_t)group * a.m * kD;
     const ReqLen rl = request_len(a.lens, bl / a.L, a.m, a.tau);
@@ -165,6 +165,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void window_attn_kernel(WinArgs a) {
     KStage<THREADS> ks_;
     VStage<THREADS> vs_;
     if (k_begin < k_end) { ks_.load(kg, k_begin, mb); vs_.load(vg, k_begin, mb); }
+    sign_q_frags(qf, scale);
     for (int kc = k_begin; kc < k_end; kc += kChunk) {
         __syncthreads();                                       // previous chunk fully consumed
         ks_.store(sK);

@@ -92,7 +92,7 @@ def _score(V, q_win, k, sm, dtype, flags=0, stats=None):
     return scores, row_max, row_sum, nnz
 
 
-@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 64), ("f32", 128)])
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("f32", 64), ("f32", 128), ("bf16", 128)])
 @pytest.mark.parametrize("plain", [False, True])
 def test_a_layers_logit_scale_may_be_zero_or_negative(dtype, d, plain):
     """The scale is any finite number: zero makes every softmax uniform over the keys a row may see, a negative one

@@ -130,6 +130,30 @@ def test_window_attn_ragged_batch_reads_nothing_beyond_each_request():
             check_nnz(nnz[b, l].cpu().numpy(), t["q_win"], t["k"], scales[l], 0.01, what + " nnz")
 
 
+@pytest.mark.parametrize("plain", [False, True])
+def test_a_layers_logit_scale_may_be_zero_or_negative(plain):
+    """Any finite scale: zero makes every softmax uniform over the keys a row may see, a negative one turns the order
+    of the logits around; the causal mask holds either way (both attention kernels, several key splits)."""
+    import paper_2410_23317_amd as V
+    cfg = _cfg(431, 1, 4, 4, 2, 300, 21)
+    scales = np.array([0.0, -0.09, 0.09, -0.0], dtype=np.float32)
+    host = [W.layer_inputs(cfg, 0, l) for l in range(4)]
+    q_win, k, v = (torch.from_numpy(np.stack([t[n] for t in host])[None]).to(torch.bfloat16).cuda() for n in ("q_win", "k", "v"))
+    shape = V.make_shape(1, 4, 4, 2, 128, 300, 21, "bf16", flags=int(plain) * V.VLC_SHAPE_SCORE_PLAIN_ALU)
+    ws = torch.empty(V.vlc_window_attn_workspace_bytes(shape), dtype=torch.uint8, device="cuda")
+    out = torch.full((1, 4, 4, 21, 128), float("nan"), dtype=torch.bfloat16, device="cuda")
+    row_max = torch.full((1, 4, 4, 21), float("nan"), dtype=torch.float32, device="cuda")
+    row_sum = torch.full_like(row_max, float("nan"))
+    V.vlc_window_attn(shape, q_win, k, v, torch.from_numpy(scales).cuda(), out, row_max, row_sum, ws)
+    torch.cuda.synchronize()
+    for l, t in enumerate(host):
+        what = f"scale {scales[l]}"
+        o_ref, M, Z = O.window_attention(t["q_win"], t["k"], t["v"], scales[l])
+        assert_close(out[0, l].float().cpu().numpy(), o_ref, what=what + " out", **OUT_TOL)
+        assert_close(row_max[0, l].cpu().numpy(), M, atol=2e-5, rtol=2e-6, what=what + " row_max")
+        assert_close(row_sum[0, l].cpu().numpy(), Z, atol=0, rtol=5e-5, what=what + " row_sum")
+
+
 def test_score_from_stats_takes_the_statistics_as_given_fp32_storage():
     """Plain-ALU sweeps (fp32 storage, d = 64): statistics computed on the host by the oracle, handed in."""
     import paper_2410_23317_amd as V
