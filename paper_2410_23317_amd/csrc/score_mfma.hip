@@ -16,7 +16,8 @@
 // block belongs to one query head; padded rows carry a +inf offset and vanish from every sum.
 // In a ragged batch the blocks are those of the request's own window length, dealt to the waves from the first on (and
 // round-robin where a wave takes two), so a shorter window costs the blocks it holds: the waves beyond it only
-// help to stage K; where the longest window takes the 16-block forms, requests of up to 8 blocks get a launch of their own.
+// help to stage K; in large batches whose longest window takes the 16-block forms, requests of up to 8 blocks get a launch
+// of their own.
 #include "common.h"
 #include "internal.h"
 #include "score_tiles.h"
@@ -377,10 +378,17 @@ size_t score_mfma_workspace_bytes(const vlc_shape& s) {
 // A launch covers up to 16 row blocks (32 padded window rows each) of every KV group; longer windows
 // take several launches over consecutive row-block ranges.  Block shape by row blocks in the launch:
 // up to 4 -> 4 waves, up to 8 -> 8 waves, else 8 waves x 2 row blocks (sweep 1) or 16 waves (sweep 2).
-// A ragged batch whose longest window takes the last forms runs its requests of up to 8 row blocks in the 8-wave form, in
-// a launch of their own (blocks of the other class leave at once): in 16-wave blocks half of the waves would idle.
-// 7B shape, 8 requests of up to 4099 tokens and 100 window rows (mean 62): every request padded to the longest window
-// 1042 + 1197 us, each request's own row blocks 0.79 of that, with the launch per class 731 + 846 us, all with the same sums.
+// A request with a shorter window than the longest computes its own row blocks only.  Where the longest window of a ragged
+// batch takes the last forms, requests of up to 8 row blocks may also have a launch of the 8-wave form for themselves (the
+// blocks of the other class leave at once): in 16-wave blocks half of the waves would idle.  The windows lie on the
+// device, so a launch may turn out empty, and two launches one after the other need enough blocks each to fill the chip.
+// Both sweeps, 7B heads, 100 window rows, one launch -> two: 2048 KV groups of 4099 keys, all windows long 2650 -> 2662 us,
+// every other a third 2270 -> 2181, all but one 1738 -> 1524; 1024 groups of 2100 keys 761 -> 766, 684 -> 681, 537 -> 478;
+// 512 of 1000 204 -> 207, 197 -> 202, 157 -> 154; 256 of 4099 343 -> 357, 303 -> 337, 232 -> 281; 8 of 300 22 -> 27, 22 -> 27,
+// 22 -> 37.  And where prompts are short, blocks that leave at once cost as much as what they leave: 2048 groups of 300
+// keys 363 -> 375, 301 -> 304, 211 -> 184; of 1000 744 -> 743, 634 -> 627, 488 -> 424.  So from 1024 groups and 1000 keys on.
+bool launch_per_class(const vlc_shape& s) { return s.lens && s.B * s.L * s.Hkv >= 1024 && s.m >= 1000; }
+
 hipError_t launch_rowstats_mfma(const ScoreArgs& a) {
     const vlc_shape& s = a.s;
     const Plan p = make_plan(s);
@@ -397,7 +405,7 @@ hipError_t launch_rowstats_mfma(const ScoreArgs& a) {
         if (nrb <= 4) rowstats_mfma_kernel<4, 1><<<grid, 256, 0, a.stream>>>(m);
         else if (nrb <= 8) rowstats_mfma_kernel<8, 1><<<grid, 512, 0, a.stream>>>(m);
         else {
-            if (a.s.lens) {                     // the requests with short windows in the form for them
+            if (launch_per_class(s)) {          // the requests with short windows in the form for them
                 m.rb_upto = 8;
                 rowstats_mfma_kernel<8, 1><<<grid, 512, 0, a.stream>>>(m);
                 m.rb_above = 8; m.rb_upto = INT32_MAX;
@@ -422,7 +430,7 @@ hipError_t launch_colsweep_mfma(const ScoreArgs& a, bool merge_partials) {
         if (nrb <= 4) colsweep_mfma_kernel<4, 1><<<grid, 256, 0, a.stream>>>(m);
         else if (nrb <= 8) colsweep_mfma_kernel<8, 1><<<grid, 512, 0, a.stream>>>(m);
         else {
-            if (a.s.lens) {
+            if (launch_per_class(s)) {
                 m.rb_upto = 8;
                 colsweep_mfma_kernel<8, 1><<<grid, 512, 0, a.stream>>>(m);
                 m.rb_above = 8; m.rb_upto = INT32_MAX;

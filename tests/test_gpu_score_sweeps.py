@@ -27,7 +27,7 @@ pytestmark = pytest.mark.gpu
     ("f32", 128, 4, 2, [(1, 1), (290, 29)]),
     ("f32", 128, 6, 2, [(333, 64), (65, 1)]),                    # 6 row blocks of 512-byte rows
     ("f32", 128, 6, 1, [(2200, 50)]),                            # 12: two launches
-    ("bf16", 128, 4, 1, [(600, 100), (500, 64), (257, 20)]),     # 16, 8 and 4 row blocks: a launch per class of windows
+    ("bf16", 128, 4, 1, [(600, 100), (500, 64), (257, 20)]),     # 16, 8 and 4 row blocks in one launch
     ("bf16", 128, 8, 1, [(700, 70), (300, 33), (65, 5)]),        # 24, 16 and 8: the first needs a second launch
 ])
 def test_sweeps_match_the_oracle(dtype, d, Hq, Hkv, lens):
@@ -145,3 +145,42 @@ def test_scores_from_the_calls_own_statistics_are_as_accurate_as_its_scores(dtyp
     again = _score(V, q, k, sm, dtype, stats=(row_max, row_sum))[0]
     want = scores.double()
     assert ((again.double() - want).norm() / want.norm()).item() < 3e-7
+
+
+@pytest.mark.parametrize("L", [1, 32])
+def test_ragged_windows_on_both_sides_of_the_launch_per_class(L):
+    """bf16, d = 128, windows of 12, 8, 4 and 8 row blocks in one batch: with 32 KV groups (one launch for all) and with
+    1024 (requests of up to 8 row blocks in a launch of their own), by vlc_score and from its statistics.  NaN in the padding."""
+    import paper_2410_23317_amd as V
+    lens, Hq, Hkv, d, m, tau = [(1030, 70), (700, 33), (129, 20), (90, 64)], 32, 8, 128, 1030, 70
+    B = len(lens)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(7)
+    q = torch.randn((B, L, Hq, tau, d), generator=gen, device="cuda", dtype=torch.bfloat16)
+    k = torch.randn((B, L, Hkv, m, d), generator=gen, device="cuda", dtype=torch.bfloat16)
+    for b, (mb, tb) in enumerate(lens):
+        q[b, :, :, tb:] = float("nan")
+        k[b, :, :, mb:] = float("nan")
+    lens_t = torch.tensor(lens, dtype=torch.int32, device="cuda")
+    shape = V.make_shape(B, L, Hq, Hkv, d, m, tau, "bf16", lens=lens_t)
+    ws = torch.full((V.vlc_workspace_bytes(shape),), 255, dtype=torch.uint8, device="cuda")
+    new = lambda *s: torch.full(s, float("nan"), dtype=torch.float32, device="cuda")
+    scores, row_max, row_sum = new(B, L, Hkv, m), new(B, L, Hq, tau), new(B, L, Hq, tau)
+    nnz = torch.full((B, L, Hq), 77, dtype=torch.int64, device="cuda")
+    V.vlc_score(shape, q, k, None, 0.01, scores, row_max, row_sum, nnz, ws)
+    again, nnz2 = new(B, L, Hkv, m), torch.full_like(nnz, 77)
+    V.vlc_score_from_stats(shape, q, k, None, 0.01, row_max, row_sum, again, nnz2)
+    torch.cuda.synchronize()
+    for b, (mb, tb) in enumerate(lens):
+        for got in (scores, again):
+            assert torch.all(got[b, :, :, mb:] == 0), "keys beyond the request's prompt score zero"
+            np.testing.assert_allclose(got[b].sum(-1).cpu().numpy(), Hq // Hkv * tb, rtol=1e-4)
+        assert torch.all(torch.isnan(row_max[b, :, :, tb:])), "window rows beyond the request's are left untouched"
+        for l in (0, L - 1):
+            qh, kh = q[b, l, :, :tb].float().cpu().numpy(), k[b, l, :, :mb].float().cpu().numpy()
+            psi, _, M, Z = O.score(qh, kh, d ** -0.5)
+            for got, cnt, what in ((scores, nnz, f"b={b} l={l}"), (again, nnz2, f"b={b} l={l} from statistics")):
+                assert_close(got[b, l, :, :mb].cpu().numpy(), psi, what=what + " scores", **SCORE_TOL)
+                check_nnz(cnt[b, l].cpu().numpy(), qh, kh, d ** -0.5, 0.01, what + " nnz")
+            assert_close(row_max[b, l, :, :tb].cpu().numpy(), M, atol=2e-5, rtol=2e-6, what=f"b={b} l={l} row_max")
+            assert_close(row_sum[b, l, :, :tb].cpu().numpy(), Z, atol=0, rtol=5e-5, what=f"b={b} l={l} row_sum")
