@@ -11,6 +11,11 @@
 // Sweep 2 adds into one accumulator per key slot over all row blocks and sums across lanes once per key tile.
 // Each head's window rows are padded to a multiple of 32 so that every 32-row block belongs to one query head; the
 // blocks of a request are those of its own window length, so a short window in a ragged batch costs what it holds.
+// Windows of up to 16 rows (one row where the cache's hit rate is asked for) share a block between heads instead, each
+// head padded to a power of two; a row then counts its own entries of Eq. 1.  64 KV groups of 4 heads, 4096 keys, one row,
+// both sweeps and sweep 2 alone: the plain ALU 70.5
+// and 17.5 us, a block per head 85.5 and 42.0, shared 34.8 and 17.5 (fp32, d = 64); 121 and 32, 147 and 74.5, 55.1 and 27.1
+// (fp32, d = 128); 50.3 and 11.8, 25.2 and 12.4, 16.1 and 7.3 (bf16).
 //
 // What bounds them: at d = 64 in bf16 the vector unit (about 330 issue cycles per tile beside 128 of matrix work), in
 // fp32 the matrix cores (64 cycles per instruction and 2 contraction indexes), and for the smallest problems the
@@ -42,6 +47,7 @@ struct SweepArgs {
     const int32_t* lens;     // per-request (m_b, tau_b), or null
     float log2p, default_scale;
     int L, Hq, Hkv, g, m, tau, keys_per_split, nsplit;
+    int head_shift;          // shared blocks: log2 of the rows a head is padded to
     int rb0;                 // first 32-row block of this launch
     int accumulate;          // sweep 2: add to scores instead of overwriting (row groups after the first)
 };
@@ -50,9 +56,10 @@ struct SweepArgs {
 // per SIMD: two 8-wave blocks per CU, or one of 16 waves where the Q' rows fill the LDS.  A K tile of 512-byte rows
 // takes 64 registers (spills at four waves per SIMD): one 8-wave block per CU, whose matrix instructions (4096
 // cycles per tile) need no other wave's help to keep the matrix cores busy.
-template <bool F32_, int RBYTES_, int NRB_, int W_>
+// SHARED: heads share 32-row blocks (windows of up to 16 rows).
+template <bool F32_, int RBYTES_, int NRB_, int W_, bool SHARED_>
 struct Form {
-    static constexpr bool F32 = F32_;
+    static constexpr bool F32 = F32_, SHARED = SHARED_;
     static constexpr int RBYTES = RBYTES_, NRB = NRB_, W = W_;
     static constexpr int THREADS = W * 64;
     static constexpr int WAVES_PER_SIMD = RBYTES == 512 ? 2 : 4;
@@ -71,13 +78,14 @@ struct Where {
     float scale, c;                         // magnitude of the layer's logit scale (1 if it is zero), the same in the exponent domain
     float signed_scale;
 };
-__device__ __forceinline__ Where locate(const SweepArgs& a, int group, int split, int max_rb) {
+template <typename F>
+__device__ __forceinline__ Where locate(const SweepArgs& a, int group, int split) {
     Where w;
     w.hkv = group % a.Hkv; w.bl = group / a.Hkv; w.l = w.bl % a.L;
     const ReqLen rl = request_len(a.lens, w.bl / a.L, a.m, a.tau);
     w.mb = rl.m; w.tb = rl.tau;                             // this request's prompt and window length
     w.nb = (w.tb + 31) >> 5;
-    w.nrb = min(a.g * w.nb - a.rb0, max_rb);
+    w.nrb = F::SHARED ? ((a.g << a.head_shift) + 31) >> 5 : min(a.g * w.nb - a.rb0, F::NRB);
     w.k_begin = split * a.keys_per_split;
     w.k_end = min(w.mb, w.k_begin + a.keys_per_split);
     w.nt = w.k_end > w.k_begin ? (w.k_end - w.k_begin + 31) >> 5 : 0;
@@ -105,13 +113,25 @@ __device__ __forceinline__ float exp2_rest(float a, double b) { return fabsf(a) 
 
 // Row r of the launch's row blocks: its head, its window row, and whether it exists.
 struct Row { int hl, iw; bool real; };
+template <typename F>
 __device__ __forceinline__ Row window_row(const SweepArgs& a, const Where& w, int r) {
-    const int rb = a.rb0 + (r >> 5);
     Row o;
+    if (F::SHARED) {
+        o.hl = r >> a.head_shift;
+        o.iw = r - (o.hl << a.head_shift);
+        o.real = o.hl < a.g && o.iw < w.tb;
+        return o;
+    }
+    const int rb = a.rb0 + (r >> 5);
     o.hl = rb / w.nb;
     o.iw = (rb - o.hl * w.nb) * 32 + (r & 31);
     o.real = (r >> 5) < w.nrb && o.iw < w.tb;
     return o;
+}
+// Window row of this lane's row in block `rb` (counted from its head's first, where the head has blocks of its own).
+template <typename F>
+__device__ __forceinline__ int lane_row(const SweepArgs& a, int rb, int lane) {
+    return F::SHARED ? lane & ((1 << a.head_shift) - 1) : rb * 32 + (lane & 31);
 }
 
 // K fragments of the 32-key tile that starts at key0: lane l % 32 owns a key, lane half l / 32 the 16-byte pieces
@@ -133,7 +153,7 @@ __device__ __forceinline__ void stage_q(const SweepArgs& a, const Where& w, char
 #pragma unroll
     for (int u = 0; u < F::NQ; ++u) {
         const int x = threadIdx.x + F::THREADS * u, r = x / F::CPR;
-        const Row o = window_row(a, w, r);
+        const Row o = window_row<F>(a, w, r);
         const char* src = a.q_win + (((size_t)w.bl * a.Hq + (size_t)w.hkv * a.g + min(o.hl, a.g - 1)) * a.tau + min(o.iw, w.tb - 1)) * F::RBYTES;
         q[u] = *reinterpret_cast<const uint4*>(src + (x % F::CPR) * 16);
     }
@@ -182,7 +202,7 @@ __global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void rowstats_wave_k
     __shared__ __align__(16) char smem[QBYTES > MBYTES ? QBYTES : MBYTES];      // Q' rows; after the sweep the waves' statistics
     const int group = blockIdx.x, split = blockIdx.y;       // group-major: see the launch
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;     // wave index in a scalar register
-    const Where w = locate(a, group, split, NRB);
+    const Where w = locate<F>(a, group, split);
     if (a.nnz && split == 0 && a.rb0 == 0 && (int)threadIdx.x < a.g)
         a.nnz[(size_t)w.bl * a.Hq + (size_t)w.hkv * a.g + threadIdx.x] = 0;      // sweep 2 adds into these
     if (w.nrb <= 0) return;                                 // a shorter window than the longest of the batch
@@ -209,7 +229,7 @@ __global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void rowstats_wave_k
                 if (masked) {                               // last key this lane's row may see (causal mask of Alg. 1)
                     int rbg = a.rb0 + rb;
                     asm volatile("" : "+s"(rbg));           // computed here: hoisted, the limits of all row blocks would take registers
-                    const int jlim = min(w.mb - w.tb + (rbg % w.nb) * 32 + (lane & 31), w.mb - 1) - key0;
+                    const int jlim = min(w.mb - w.tb + lane_row<F>(a, rbg % w.nb, lane), w.mb - 1) - key0;
 #pragma unroll
                     for (int i = 0; i < 16; ++i) v[i] = acc_row(i, lane) <= jlim ? v[i] : -INFINITY;
                 }
@@ -240,7 +260,7 @@ __global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void rowstats_wave_k
     }
     __syncthreads();
     const int r = threadIdx.x;
-    const Row o = window_row(a, w, r);
+    const Row o = window_row<F>(a, w, r);
     if (r < F::ROWS && o.real) {
         float M = -INFINITY, Z = 0.f;
 #pragma unroll
@@ -262,14 +282,15 @@ __global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void colsweep_wave_k
     __shared__ __align__(16) char sQ[F::ROWS * F::PITCH];
     __shared__ float2 sConst[F::ROWS];                      // per row: exponent offset (+inf for rows that do not exist), 1 / row sum
     __shared__ uint32_t sCnt[8];                            // Eq. 1 entries per query head of the group
+    __shared__ uint32_t sRow[F::SHARED ? F::ROWS : 1];      // shared blocks: per row
     const int group = blockIdx.x, split = blockIdx.y;       // group-major: see the launch
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;     // wave index in a scalar register
-    const Where w = locate(a, group, split, F::NRB);
+    const Where w = locate<F>(a, group, split);
     if (w.nrb <= 0) return;
     const char* kg = a.k + (size_t)group * a.m * RBYTES;
     // Order of the first requests: the few bytes of the statistics go out first (every block of the launch starts at
     // once, and behind the K bursts they would wait), then the first K tile, then Q'.
-    const Row o = window_row(a, w, (int)threadIdx.x);
+    const Row o = window_row<F>(a, w, (int)threadIdx.x);
     const bool mine = (int)threadIdx.x < F::ROWS && o.real;
     constexpr int kSplitRegs = 4;                           // splits whose partials a thread holds at once (more are merged in rounds)
     float2 pin[kSplitRegs];
@@ -283,6 +304,7 @@ __global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void colsweep_wave_k
     if (wave < w.nt) load_keys<KS, RBYTES>(kg, w.k_begin + wave * 32, w.mb, lane, kf);
     stage_q<F>(a, w, sQ);
     if (threadIdx.x < 8) sCnt[threadIdx.x] = 0;
+    if (F::SHARED && (int)threadIdx.x < F::ROWS) sRow[threadIdx.x] = 0;
     if ((int)threadIdx.x < F::ROWS) {
         float2 st = make_float2(INFINITY, 0.f);
         const size_t x = ((size_t)w.bl * a.Hq + (size_t)w.hkv * a.g + o.hl) * a.tau + o.iw;
@@ -329,7 +351,7 @@ __global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void colsweep_wave_k
         float col[16];
 #pragma unroll
         for (int i = 0; i < 16; ++i) col[i] = 0.f;
-        uint32_t cnt = 0;                                   // wave-wide, on the scalar unit
+        uint32_t cnt = 0;                                   // wave-wide, on the scalar unit (shared blocks: per lane)
         int j = j_first, hl = h_first;                      // block within its head, head
 #pragma unroll 1
         for (int rb = 0; rb < w.nrb; ++rb) {
@@ -340,16 +362,20 @@ __global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void colsweep_wave_k
 #pragma unroll
             for (int i = 0; i < 16; ++i) ea[i] = fmaf(acc[i], w.c, -rc.x);
             if (masked) {
-                const int jlim = min(w.mb - w.tb + j * 32 + (lane & 31), w.mb - 1) - key0;
+                const int jlim = min(w.mb - w.tb + lane_row<F>(a, j, lane), w.mb - 1) - key0;
 #pragma unroll
                 for (int i = 0; i < 16; ++i) ea[i] = acc_row(i, lane) <= jlim ? ea[i] : -INFINITY;
             }
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 col[i] = fmaf(exp2_fast(ea[i]), rc.y, col[i]);
-                cnt += (uint32_t)__popcll(__ballot(ea[i] >= a.log2p));
+                if (F::SHARED) cnt += ea[i] >= a.log2p ? 1u : 0u;         // this lane's row
+                else cnt += (uint32_t)__popcll(__ballot(ea[i] >= a.log2p));
             }
-            if (++j == w.nb || rb == w.nrb - 1) {           // last block of its head here
+            if (F::SHARED) {
+                if (a.nnz && cnt) atomicAdd(&sRow[rb * 32 + (lane & 31)], cnt);
+                cnt = 0;
+            } else if (++j == w.nb || rb == w.nrb - 1) {           // last block of its head here
                 if (a.nnz && lane == 0 && cnt) atomicAdd(&sCnt[hl], cnt);
                 cnt = 0; j = 0; ++hl;
             }
@@ -378,6 +404,10 @@ __global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void colsweep_wave_k
     }
     if (a.nnz) {
         __syncthreads();
+        if (F::SHARED) {
+            if (mine && sRow[threadIdx.x]) atomicAdd(&sCnt[o.hl], sRow[threadIdx.x]);
+            __syncthreads();
+        }
         if ((int)threadIdx.x < a.g && sCnt[threadIdx.x])
             atomicAdd(a.nnz + (size_t)w.bl * a.Hq + (size_t)w.hkv * a.g + threadIdx.x, (unsigned long long)sCnt[threadIdx.x]);
     }
@@ -386,12 +416,18 @@ __global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void colsweep_wave_k
 int row_bytes(const vlc_shape& s) { return s.d * (s.dtype == VLC_F32 ? 4 : 2); }
 int max_row_blocks(const vlc_shape& s) { return row_bytes(s) == 512 ? 8 : 16; }       // per launch: what fits the LDS
 
-struct Plan { int nrb, nsplit, keys_per_split; };
+struct Plan { int nrb, nsplit, keys_per_split, head_shift; };      // head_shift < 0: every head has row blocks of its own
 
 Plan make_plan(const vlc_shape& s) {
     Plan p;
     const int g = s.Hq / s.Hkv;
-    p.nrb = g * ((s.tau + 31) / 32);
+    p.head_shift = s.tau <= 16 ? 0 : -1;
+    if (s.tau <= 16) {
+        while (1 << p.head_shift < s.tau) ++p.head_shift;
+        p.nrb = ((g << p.head_shift) + 31) / 32;
+    } else {
+        p.nrb = g * ((s.tau + 31) / 32);
+    }
     const int64_t groups = (int64_t)s.B * s.L * s.Hkv;
     const int tiles = s.m / 32 + (s.m % 32 != 0);
     const int nrb = p.nrb < max_row_blocks(s) ? p.nrb : max_row_blocks(s);
@@ -428,13 +464,14 @@ SweepArgs make_args(const ScoreArgs& a, const Plan& p) {
     m.lens = s.lens;
     m.L = s.L; m.Hq = s.Hq; m.Hkv = s.Hkv; m.g = s.Hq / s.Hkv; m.m = s.m; m.tau = s.tau;
     m.keys_per_split = p.keys_per_split; m.nsplit = p.nsplit;
+    m.head_shift = p.head_shift;
     m.rb0 = 0; m.accumulate = 0;
     return m;
 }
 
-template <bool SWEEP1, bool F32, int RBYTES, int NRB, int W>
+template <bool SWEEP1, bool F32, int RBYTES, int NRB, int W, bool SHARED = false>
 void launch_form(const SweepArgs& m, dim3 grid, hipStream_t st) {
-    using F = Form<F32, RBYTES, NRB, W>;
+    using F = Form<F32, RBYTES, NRB, W, SHARED>;
     if (SWEEP1) rowstats_wave_kernel<F><<<grid, F::THREADS, 0, st>>>(m);
     else colsweep_wave_kernel<F><<<grid, F::THREADS, 0, st>>>(m);
 }
@@ -450,7 +487,11 @@ hipError_t launch_sweep(SweepArgs m, const Plan& p, const vlc_shape& s, hipStrea
         const int nrb = p.nrb - rb0 < step ? p.nrb - rb0 : step;
         m.rb0 = rb0;
         m.accumulate = rb0 > 0;                 // launches of one stream run in order: the column sums add up deterministically
-        if (s.dtype == VLC_F32 && s.d == 128) {
+        if (p.head_shift >= 0) {                // at most 8 heads of 16 rows
+            if (s.dtype == VLC_F32 && s.d == 128) launch_form<SWEEP1, true, 512, 4, 8, true>(m, grid, st);
+            else if (s.dtype == VLC_F32) launch_form<SWEEP1, true, 256, 4, 8, true>(m, grid, st);
+            else launch_form<SWEEP1, false, 128, 4, 8, true>(m, grid, st);
+        } else if (s.dtype == VLC_F32 && s.d == 128) {
             if (nrb <= 4) launch_form<SWEEP1, true, 512, 4, 8>(m, grid, st);
             else launch_form<SWEEP1, true, 512, 8, 8>(m, grid, st);
         } else if (s.dtype == VLC_F32) {

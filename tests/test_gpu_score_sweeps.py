@@ -27,6 +27,13 @@ pytestmark = pytest.mark.gpu
     ("f32", 128, 4, 2, [(1, 1), (290, 29)]),
     ("f32", 128, 6, 2, [(333, 64), (65, 1)]),                    # 6 row blocks of 512-byte rows
     ("f32", 128, 6, 1, [(2200, 50)]),                            # 12: two launches
+    ("bf16", 64, 8, 1, [(300, 1)]),                              # windows of up to 16 rows: eight heads' rows in one block
+    ("bf16", 64, 7, 1, [(513, 3), (77, 2)]),                     # heads padded to four rows, the second request's too
+    ("bf16", 64, 5, 1, [(64, 16), (16, 16)]),                    # two heads per block, the third block half empty
+    ("f32", 64, 8, 1, [(290, 16), (65, 9)]),                     # four blocks
+    ("f32", 64, 6, 2, [(100, 5)]),                               # heads padded to eight rows, a block and a half
+    ("f32", 128, 8, 1, [(130, 9), (40, 1)]),
+    ("f32", 128, 3, 1, [(70, 17)]),                              # one row more: a block per head
     ("bf16", 128, 4, 1, [(600, 100), (500, 64), (257, 20)]),     # 16, 8 and 4 row blocks in one launch
     ("bf16", 128, 8, 1, [(700, 70), (300, 33), (65, 5)]),        # 24, 16 and 8: the first needs a second launch
 ])
