@@ -21,7 +21,7 @@
 // fp32 the matrix cores (64 cycles per instruction and 2 contraction indexes), and for the smallest problems the
 // chain of launch, first loads and merge.  Measured against one thread per key on the
 // plain ALU: bf16, 2 x 24 layers of 16 (4 KV) heads of 64 over 4096 keys with 50 window rows, 717 + 9 + 417 us -> 56 + 61 us;
-// fp32, 2 layers of 4 (2 KV) heads of 64 over 512 keys with 32 rows, 30 + 4 + 31 us -> 11.5 + 9.4 us.  Errors against
+// fp32, 2 layers of 4 (2 KV) heads of 64 over 512 keys with 32 rows, 30 + 4 + 31 us -> 11.5 + 9.4 us (6.5 with sweep 2's shorter splits).  Errors against
 // 64-bit arithmetic are those of the plain-ALU sweeps or smaller (scores 0.5-3e-7 relative, row sums 1-4e-7).
 #include "common.h"
 #include "internal.h"
@@ -71,12 +71,21 @@ struct Form {
     static_assert(ROWS * CPR % THREADS == 0 && ROWS <= THREADS, "staging and statistics in whole passes");
 };
 
+// A layer's logit scale, its magnitude (1 if it is zero), and that in the exponent domain.
+struct LogitScale { float given, mag, c; };
+__device__ __forceinline__ LogitScale logit_scale(const SweepArgs& a, int l) {
+    LogitScale s;
+    s.given = a.sm_scale ? a.sm_scale[l] : a.default_scale;
+    s.mag = s.given == 0.f ? 1.f : fabsf(s.given);
+    s.c = s.mag * kLog2e;
+    return s;
+}
+
 // What the blocks of one (request, layer, KV head) share.
 struct Where {
     int hkv, bl, l, mb, tb, nb, nrb;        // nb: 32-row blocks per head, nrb: row blocks of this launch
     int k_begin, k_end, nt;                 // key range of the split, its 32-key tiles
-    float scale, c;                         // magnitude of the layer's logit scale (1 if it is zero), the same in the exponent domain
-    float signed_scale;
+    LogitScale ls;
 };
 template <typename F>
 __device__ __forceinline__ Where locate(const SweepArgs& a, int group, int split) {
@@ -89,9 +98,7 @@ __device__ __forceinline__ Where locate(const SweepArgs& a, int group, int split
     w.k_begin = split * a.keys_per_split;
     w.k_end = min(w.mb, w.k_begin + a.keys_per_split);
     w.nt = w.k_end > w.k_begin ? (w.k_end - w.k_begin + 31) >> 5 : 0;
-    w.signed_scale = a.sm_scale ? a.sm_scale[w.l] : a.default_scale;
-    w.scale = w.signed_scale == 0.f ? 1.f : fabsf(w.signed_scale);
-    w.c = w.scale * kLog2e;
+    w.ls = logit_scale(a, w.l);
     return w;
 }
 
@@ -106,8 +113,8 @@ __device__ __forceinline__ float exp_offset(float m, float c) {
 // rounded number, its offset; at logits of a few hundred the two differ by 1e-5.  So the row sum that is handed out belongs to the
 // maximum that is handed out, and what rounding the offset of a given maximum leaves over goes into its row's factor: fp32, d = 128,
 // logits up to 123, scores from vlc_score's own statistics 8.1e-7 off -> 3.3e-7, as its scores are.
-__device__ __forceinline__ double exponent_per_logit(const Where& w) {      // c as rounded over the scale's magnitude
-    return (double)kLog2e + (double)(fmaf(-w.scale, kLog2e, w.c) / w.scale);
+__device__ __forceinline__ double exponent_per_logit(const LogitScale& s) {      // c as rounded over the scale's magnitude
+    return (double)kLog2e + (double)(fmaf(-s.mag, kLog2e, s.c) / s.mag);
 }
 __device__ __forceinline__ float exp2_rest(float a, double b) { return fabsf(a) < INFINITY ? exp2_fast((float)((double)a - b)) : 1.f; }
 
@@ -161,7 +168,7 @@ __device__ __forceinline__ void stage_q(const SweepArgs& a, const Where& w, char
     // stand for the logits only where the scale is positive: so Q' takes the scale's sign (exact), and is zero for a
     // scale of zero, where every logit is 0.  (The scale is first looked at here: a wait for it in front of the
     // requests above costs a small sweep 0.4 us of 9.)
-    uint32_t scale = __float_as_uint(w.signed_scale);
+    uint32_t scale = __float_as_uint(w.ls.given);
     asm volatile("" : "+s"(scale) : : "memory");
     const uint32_t flip = (scale >> 31) * (F::F32 ? 0x80000000u : 0x80008000u), keep = scale << 1 ? 0xffffffffu : 0u;
 #pragma unroll
@@ -237,11 +244,11 @@ __global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void rowstats_wave_k
 #pragma unroll
                 for (int i = 1; i < 16; ++i) tmax = fmaxf(tmax, v[i]);
                 const float m_new = fmaxf(m_run[rb], tmax);
-                const float m_use = m_new > -INFINITY ? exp_offset(m_new, w.c) : 0.f;     // a row that has seen no key yet: every term is 0
+                const float m_use = m_new > -INFINITY ? exp_offset(m_new, w.ls.c) : 0.f;     // a row that has seen no key yet: every term is 0
                 float zs = 0.f;
 #pragma unroll
-                for (int i = 0; i < 16; ++i) zs += exp2_fast(fmaf(v[i], w.c, -m_use));
-                z_run[rb] = z_run[rb] * exp2_fast(exp_offset(m_run[rb], w.c) - m_use) + zs;
+                for (int i = 0; i < 16; ++i) zs += exp2_fast(fmaf(v[i], w.ls.c, -m_use));
+                z_run[rb] = z_run[rb] * exp2_fast(exp_offset(m_run[rb], w.ls.c) - m_use) + zs;
                 m_run[rb] = m_new;
             }
         }
@@ -252,10 +259,10 @@ __global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void rowstats_wave_k
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb) {
         const float mo = __shfl_xor(m_run[rb], 32, 64), zo = __shfl_xor(z_run[rb], 32, 64);
-        const float mm = fmaxf(m_run[rb], mo), om = exp_offset(mm, w.c);
+        const float mm = fmaxf(m_run[rb], mo), om = exp_offset(mm, w.ls.c);
         float z = 0.f;
-        if (m_run[rb] > -INFINITY) z += z_run[rb] * exp2_fast(exp_offset(m_run[rb], w.c) - om);
-        if (mo > -INFINITY) z += zo * exp2_fast(exp_offset(mo, w.c) - om);
+        if (m_run[rb] > -INFINITY) z += z_run[rb] * exp2_fast(exp_offset(m_run[rb], w.ls.c) - om);
+        if (mo > -INFINITY) z += zo * exp2_fast(exp_offset(mo, w.ls.c) - om);
         if (lane < 32) sStat[wave * F::ROWS + rb * 32 + lane] = make_float2(mm, z);
     }
     __syncthreads();
@@ -268,9 +275,36 @@ __global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void rowstats_wave_k
 #pragma unroll
         for (int v = 0; v < W; ++v) {
             const float2 s = sStat[v * F::ROWS + r];
-            if (s.x > -INFINITY) Z += s.y * exp2_fast(exp_offset(s.x, w.c) - exp_offset(M, w.c));
+            if (s.x > -INFINITY) Z += s.y * exp2_fast(exp_offset(s.x, w.ls.c) - exp_offset(M, w.ls.c));
         }
         a.part[((size_t)group * a.nsplit + split) * a.g * a.tau + o.hl * a.tau + o.iw] = make_float2(M, Z);
+    }
+}
+
+// Merge of sweep 1's key splits where they are too many for sweep 2's prologue: a wave per window row, a split per lane.
+__global__ __launch_bounds__(256) void merge_splits_kernel(SweepArgs a, int rows) {
+    const int x = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (x >= rows) return;                                  // wave-uniform; no barrier below
+    const int per_group = a.g * a.tau, group = x / per_group, r = x % per_group;
+    const int hkv = group % a.Hkv, bl = group / a.Hkv, hl = r / a.tau, iw = r % a.tau;
+    if (iw >= request_len(a.lens, bl / a.L, a.m, a.tau).tau) return;
+    const LogitScale ls = logit_scale(a, bl % a.L);
+    const float2* p = a.part + (size_t)group * a.nsplit * per_group + r;
+    float M = -INFINITY;
+    for (int sp = lane; sp < a.nsplit; sp += 64) M = fmaxf(M, p[(size_t)sp * per_group].x);
+    M = wave_allreduce_max(M);
+    const float off = exp_offset(M, ls.c);
+    float Z = 0.f;
+    for (int sp = lane; sp < a.nsplit; sp += 64) {
+        const float2 s = p[(size_t)sp * per_group];
+        if (s.x > -INFINITY) Z += s.y * exp2_fast(exp_offset(s.x, ls.c) - off);
+    }
+    Z = wave_allreduce_sum(Z);
+    if (lane == 0) {
+        const size_t o = ((size_t)bl * a.Hq + (size_t)hkv * a.g + hl) * a.tau + iw;
+        const float row_max = M * ls.mag;
+        a.row_max_out[o] = row_max;
+        a.row_sum_out[o] = Z * exp2_rest(off, (double)row_max * exponent_per_logit(ls));
     }
 }
 
@@ -321,23 +355,23 @@ __global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void colsweep_wave_k
 #pragma unroll
                 for (int sp = 0; sp < kSplitRegs; ++sp) Mn = fmaxf(Mn, pin[sp].x);
                 if (Mn > -INFINITY) {
-                    const float on = exp_offset(Mn, w.c);
-                    Z *= exp2_fast(exp_offset(M, w.c) - on);            // 0 on the first round (M = -inf)
+                    const float on = exp_offset(Mn, w.ls.c);
+                    Z *= exp2_fast(exp_offset(M, w.ls.c) - on);            // 0 on the first round (M = -inf)
 #pragma unroll
                     for (int sp = 0; sp < kSplitRegs; ++sp)
-                        if (pin[sp].x > -INFINITY) Z += pin[sp].y * exp2_fast(exp_offset(pin[sp].x, w.c) - on);
+                        if (pin[sp].x > -INFINITY) Z += pin[sp].y * exp2_fast(exp_offset(pin[sp].x, w.ls.c) - on);
                     M = Mn;
                 }
             }
-            const float off = exp_offset(M, w.c);
+            const float off = exp_offset(M, w.ls.c);
             st = make_float2(off, 1.f / Z);
             if (split == 0) {
-                const float row_max = M * w.scale;
+                const float row_max = M * w.ls.mag;
                 if (a.row_max_out) a.row_max_out[x] = row_max;
-                if (a.row_sum_out) a.row_sum_out[x] = Z * exp2_rest(off, (double)row_max * exponent_per_logit(w));
+                if (a.row_sum_out) a.row_sum_out[x] = Z * exp2_rest(off, (double)row_max * exponent_per_logit(w.ls));
             }
         } else if (mine) {
-            const double offset = (double)a.row_max[x] * exponent_per_logit(w);
+            const double offset = (double)a.row_max[x] * exponent_per_logit(w.ls);
             st = make_float2((float)offset, a.row_sum ? exp2_rest((float)offset, offset) / a.row_sum[x] : 0.f);
         }
         sConst[threadIdx.x] = st;
@@ -360,7 +394,7 @@ __global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void colsweep_wave_k
             if (rb == w.nrb - 1 && t + W < w.nt) load_keys<KS, RBYTES>(kg, key0 + W * 32, w.mb, lane, kf);
             float ea[16];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) ea[i] = fmaf(acc[i], w.c, -rc.x);
+            for (int i = 0; i < 16; ++i) ea[i] = fmaf(acc[i], w.ls.c, -rc.x);
             if (masked) {
                 const int jlim = min(w.mb - w.tb + lane_row<F>(a, j, lane), w.mb - 1) - key0;
 #pragma unroll
@@ -416,7 +450,12 @@ __global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void colsweep_wave_k
 int row_bytes(const vlc_shape& s) { return s.d * (s.dtype == VLC_F32 ? 4 : 2); }
 int max_row_blocks(const vlc_shape& s) { return row_bytes(s) == 512 ? 8 : 16; }       // per launch: what fits the LDS
 
-struct Plan { int nrb, nsplit, keys_per_split, head_shift; };      // head_shift < 0: every head has row blocks of its own
+struct Plan {
+    int nrb, nsplit, keys_per_split;        // splits of sweep 1, whose partial statistics sweep 2 merges
+    int keys_per_split2;    // of sweep 2
+    int head_shift;         // < 0: every head has row blocks of its own
+    bool merge_apart;       // sweep 1's splits are merged by a kernel of their own, not in sweep 2's prologue
+};
 
 Plan make_plan(const vlc_shape& s) {
     Plan p;
@@ -440,15 +479,30 @@ Plan make_plan(const vlc_shape& s) {
     const double prologue = 3.0 / nrb;
     double best = 0.0;
     int ns = 1;
-    const int top = s.m / 256 + (s.m % 256 != 0) < 32 ? s.m / 256 + (s.m % 256 != 0) : 32;
+    const int top256 = s.m / 256 + (s.m % 256 != 0), top = top256 < 32 ? top256 : 32;
     for (int n = 1; n <= top; ++n) {
         const int tps = (tiles + n - 1) / n;
         const double cost = (double)((groups * n + resident - 1) / resident) * ((tps + W - 1) / W + prologue);
         if (n == 1 || cost < best * 0.999) { best = cost; ns = n; }
     }
+    // Fewer than 8 KV groups leave CUs idle at 32 splits: then as many as give every CU a block, and where that is more than
+    // a prologue should merge, a kernel merges them.  Plain-ALU sweeps, 32 splits, now, both sweeps and sweep 2 alone: one
+    // group of 8 heads, 65536 keys, 50 rows, fp32 d = 64 394 and 171 us, 547 and 274, 93 and 42; d = 128 685 and 317, 1033
+    // and 525, 167 and 78; bf16 383 and 161, 134 and 75, 37 and 15.  4 heads, 16384 keys, 32 rows, fp32 d = 64 106 and 54, 49 and
+    // 23, 28 and 9.  (7 groups of 20000 keys still take 32: 63 and 30.)
+    p.merge_apart = false;
+    if (groups < 8) {
+        const int n = top256 < 256 / (int)groups ? top256 : 256 / (int)groups;
+        if (n > 32) { ns = n; p.merge_apart = true; }
+    }
     const int tps = (tiles + ns - 1) / ns;
     p.keys_per_split = tps * 32;
     p.nsplit = (tiles + tps - 1) / tps;
+    // Sweep 2 leaves no partials: while CUs are idle its splits may be as short as 4 tiles, one per SIMD (fp32, 4 groups of
+    // 2 heads of 64 over 512 keys, 32 rows: 9.0 -> 6.3 us; 16 of 2 heads of 128 over 2048 keys, 33 rows: 22.5 -> 13.6).
+    p.keys_per_split2 = p.keys_per_split;
+    const int n2 = groups < 256 ? 256 / (int)groups : 1, tps2 = (tiles + n2 - 1) / n2 > 4 ? (tiles + n2 - 1) / n2 : 4;
+    if (tps2 < tps) p.keys_per_split2 = tps2 * 32;
     return p;
 }
 
@@ -481,7 +535,8 @@ void launch_form(const SweepArgs& m, dim3 grid, hipStream_t st) {
 // group run on one XCD and share its Q' rows in that XCD's L2.
 template <bool SWEEP1>
 hipError_t launch_sweep(SweepArgs m, const Plan& p, const vlc_shape& s, hipStream_t st) {
-    const dim3 grid(s.B * s.L * s.Hkv, p.nsplit);
+    m.keys_per_split = SWEEP1 ? p.keys_per_split : p.keys_per_split2;
+    const dim3 grid(s.B * s.L * s.Hkv, s.m / m.keys_per_split + (s.m % m.keys_per_split != 0));
     const int step = max_row_blocks(s);
     for (int rb0 = 0; rb0 < p.nrb; rb0 += step) {
         const int nrb = p.nrb - rb0 < step ? p.nrb - rb0 : step;
@@ -513,13 +568,18 @@ bool score_wave_supported(const vlc_shape& s) { return s.dtype == VLC_F32 || s.d
 
 hipError_t launch_rowstats_wave(const ScoreArgs& a) {
     const Plan p = make_plan(a.s);
-    return launch_sweep<true>(make_args(a, p), p, a.s, a.stream);
+    const SweepArgs m = make_args(a, p);
+    const hipError_t e = launch_sweep<true>(m, p, a.s, a.stream);
+    if (e != hipSuccess || !p.merge_apart) return e;
+    const int rows = a.s.B * a.s.L * a.s.Hq * a.s.tau;
+    merge_splits_kernel<<<(rows + 3) / 4, 256, 0, a.stream>>>(m, rows);
+    return hipGetLastError();
 }
 
 hipError_t launch_colsweep_wave(const ScoreArgs& a, bool merge_partials) {
     const Plan p = make_plan(a.s);
     SweepArgs m = make_args(a, p);
-    if (merge_partials) m.part_in = m.part;          // sweep 1 ran just before on the same workspace
+    if (merge_partials && !p.merge_apart) m.part_in = m.part;          // sweep 1 ran just before on the same workspace
     return launch_sweep<false>(m, p, a.s, a.stream);
 }
 

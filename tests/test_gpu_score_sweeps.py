@@ -191,3 +191,25 @@ def test_ragged_windows_on_both_sides_of_the_launch_per_class(L):
                 check_nnz(cnt[b, l].cpu().numpy(), qh, kh, d ** -0.5, 0.01, what + " nnz")
             assert_close(row_max[b, l, :, :tb].cpu().numpy(), M, atol=2e-5, rtol=2e-6, what=f"b={b} l={l} row_max")
             assert_close(row_sum[b, l, :, :tb].cpu().numpy(), Z, atol=0, rtol=5e-5, what=f"b={b} l={l} row_sum")
+
+
+@pytest.mark.parametrize("dtype,d,Hq,lens", [
+    ("bf16", 64, 4, [(8300, 7)]),                       # 33 splits of 8 tiles, shared row blocks
+    ("f32", 64, 1, [(16500, 33)]),                      # 65 splits: a second round of the merging wave's lanes
+    ("f32", 128, 2, [(9000, 20), (500, 3)]),            # the shorter request has no key in most splits
+])
+def test_few_groups_of_long_prompts_are_merged_by_a_kernel_of_their_own(dtype, d, Hq, lens):
+    """Fewer than 8 KV groups and more than 32 x 256 keys: more key splits than the column sweep merges itself.  Scores,
+    statistics and counts against the oracle, and the counts of the standalone sparsity sweep."""
+    import paper_2410_23317_amd as V
+    test_sweeps_match_the_oracle(dtype, d, Hq, 1, lens)
+    m, tau = lens[0]
+    _, (q, k, _), scales = _upload(dtype, d, 2, Hq, 1, m, tau, 823)
+    sm = torch.from_numpy(scales).cuda()
+    nnz = _score(V, q, k, sm, dtype)[3]
+    shape = V.make_shape(1, 2, Hq, 1, d, m, tau, dtype)
+    alone = torch.full_like(nnz, 77)
+    ws = torch.full((V.vlc_workspace_bytes(shape),), 255, dtype=torch.uint8, device="cuda")
+    V.vlc_sparsity(shape, q, k, sm, None, 0.01, alone, None, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(alone, nnz)
