@@ -62,12 +62,22 @@ double region_size(const vlc_shape& s) {
 enum class Sweeps { kSimple, kMfma, kWave };
 struct WsPlan { size_t part, stats, total; Sweeps route; };
 
+// One or two window rows per KV group (a one-row window is what the cache's hit rate takes) in fp32 storage: the matrix cores
+// multiply a block of 32 rows whatever it holds, 64 cycles per two contraction indexes.  For short prompts whose K comes
+// from the caches that is slower than the plain ALU, whose merge over blocks of 256 keys grows with the prompt.  One row,
+// both sweeps, matrix cores and plain ALU: 64 KV groups of 2048 keys of 64 23.2 and 17.6 us, of 128 35.4 and 33.5, 8 of 512
+// keys of 128 17.8 and 15.8; two rows 23.0 and 19.2, 35.5 and 35.3, 18.0 and 17.1.  Beyond: 64 groups of 4096 keys of 64 33.4
+// and 47.4, one of 16384 16.7 and 26.2, 256 of 2048 keys of 128 97 and 100; four rows 22.7 and 21.7, 35.5 and 39.9, 17.8 and 20.5.
+bool few_rows_of_fp32(const vlc_shape& s) {
+    return s.dtype == VLC_F32 && (int64_t)(s.Hq / s.Hkv) * s.tau <= 2 && s.m <= 2048 &&
+           (int64_t)s.B * s.L * s.Hkv * s.m * s.d <= 16 << 20;
+}
+
 WsPlan ws_plan(const vlc_shape& s) {
     WsPlan w;
-    w.route = (s.flags & VLC_SHAPE_SCORE_PLAIN_ALU) ? Sweeps::kSimple
-              : vlc::score_mfma_supported(s)        ? Sweeps::kMfma
-              : vlc::score_wave_supported(s)        ? Sweeps::kWave
-                                                    : Sweeps::kSimple;
+    w.route = (s.flags & VLC_SHAPE_SCORE_PLAIN_ALU) || few_rows_of_fp32(s) ? Sweeps::kSimple
+              : vlc::score_mfma_supported(s)                              ? Sweeps::kMfma
+                                                                          : Sweeps::kWave;
     const size_t a = vlc::score_simple_workspace_bytes(s), b = vlc::score_mfma_workspace_bytes(s);
     w.part = align_up(a > b ? a : b, 256);
     w.stats = align_up((size_t)s.B * s.L * s.Hq * s.tau * sizeof(float), 256);

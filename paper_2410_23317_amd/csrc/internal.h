@@ -90,7 +90,8 @@ struct vlc_cache {
 namespace vlc {
 
 // ---- scoring sweeps (score_mfma.hip: bf16, d = 128; score_wave.hip: bf16 with d = 64 and fp32 storage, both on the
-// matrix cores; score_simple.hip: any shape on the plain ALU, where VLC_SHAPE_SCORE_PLAIN_ALU asks for it) ----
+// matrix cores; score_simple.hip: any shape on the plain ALU, for one or two window rows of fp32 storage and where
+// VLC_SHAPE_SCORE_PLAIN_ALU asks for it) ----
 struct ScoreArgs {
     vlc_shape s;
     const void* q_win;
@@ -111,8 +112,8 @@ bool score_mfma_supported(const vlc_shape& s);            // bf16, d = 128
 size_t score_mfma_workspace_bytes(const vlc_shape& s);
 hipError_t launch_rowstats_mfma(const ScoreArgs& a);       // leaves per-split partial statistics in the workspace; zeroes nnz if given
 hipError_t launch_colsweep_mfma(const ScoreArgs& a, bool merge_partials);   // merge_partials: statistics come from the sweep just run (row_max, row_sum are then outputs)
-bool score_wave_supported(const vlc_shape& s);            // bf16 with d = 64, or fp32 storage; its partials fit the plain-ALU sweep's workspace
-hipError_t launch_rowstats_wave(const ScoreArgs& a);       // the same two sweeps with the same contracts as the mfma pair
+// bf16 with d = 64, or fp32 storage; the partials fit the plain-ALU sweep's workspace; the same contracts as the mfma pair
+hipError_t launch_rowstats_wave(const ScoreArgs& a);
 hipError_t launch_colsweep_wave(const ScoreArgs& a, bool merge_partials);
 hipError_t launch_fill_u64(uint64_t* p, size_t n, uint64_t v, hipStream_t st);
 hipError_t launch_gamma(const vlc_shape& s, const uint64_t* nnz, float* gamma, hipStream_t st);

@@ -5,8 +5,8 @@
 // Neither the logits nor the attention matrix ever reach HBM.
 //
 // One thread owns one key: its K row sits in registers, the query rows are broadcast from LDS.
-// This is the route VLC_SHAPE_SCORE_PLAIN_ALU asks for (the tests compare the matrix-core sweeps with it); it is
-// arithmetic-bound, not bandwidth-bound.
+// This is the route of fp32 storage with one or two window rows per KV group, and the one VLC_SHAPE_SCORE_PLAIN_ALU asks
+// for (the tests compare the matrix-core sweeps with it); it is arithmetic-bound, not bandwidth-bound.
 #include "common.h"
 #include "internal.h"
 

@@ -564,8 +564,6 @@ hipError_t launch_sweep(SweepArgs m, const Plan& p, const vlc_shape& s, hipStrea
 
 }  // namespace
 
-bool score_wave_supported(const vlc_shape& s) { return s.dtype == VLC_F32 || s.d == 64; }
-
 hipError_t launch_rowstats_wave(const ScoreArgs& a) {
     const Plan p = make_plan(a.s);
     const SweepArgs m = make_args(a, p);

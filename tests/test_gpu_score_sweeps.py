@@ -32,6 +32,9 @@ pytestmark = pytest.mark.gpu
     ("bf16", 64, 5, 1, [(64, 16), (16, 16)]),                    # two heads per block, the third block half empty
     ("f32", 64, 8, 1, [(290, 16), (65, 9)]),                     # four blocks
     ("f32", 64, 6, 2, [(100, 5)]),                               # heads padded to eight rows, a block and a half
+    ("f32", 64, 2, 1, [(300, 1), (77, 1)]),                      # two rows of fp32: the plain-ALU sweeps
+    ("f32", 128, 1, 1, [(257, 2)]),
+    ("f32", 64, 3, 1, [(300, 1)]),                               # three: the matrix cores
     ("f32", 128, 8, 1, [(130, 9), (40, 1)]),
     ("f32", 128, 3, 1, [(70, 17)]),                              # one row more: a block per head
     ("bf16", 128, 4, 1, [(600, 100), (500, 64), (257, 20)]),     # 16, 8 and 4 row blocks in one launch
@@ -213,3 +216,21 @@ def test_few_groups_of_long_prompts_are_merged_by_a_kernel_of_their_own(dtype, d
     V.vlc_sparsity(shape, q, k, sm, None, 0.01, alone, None, ws)
     torch.cuda.synchronize()
     assert torch.equal(alone, nnz)
+
+
+@pytest.mark.parametrize("L,d,Hq,m,tau,plain", [(2, 64, 2, 300, 1, True), (2, 128, 1, 257, 2, True), (2, 64, 3, 300, 1, False),
+                                                (2, 64, 1, 2048, 2, True), (2, 64, 1, 2049, 2, False),
+                                                (64, 128, 1, 2048, 1, True), (65, 128, 1, 2048, 1, False)])
+def test_one_or_two_rows_of_fp32_take_the_plain_alu_sweeps(L, d, Hq, m, tau, plain):
+    """Which kernels run, told by their rounding: the bits of the flagged call or not (up to two rows, 2048 keys, 64 MiB of K)."""
+    import paper_2410_23317_amd as V
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    q = torch.randn((1, L, Hq, tau, d), generator=gen, device="cuda")
+    k = torch.randn((1, L, 1, m, d), generator=gen, device="cuda")
+    got = _score(V, q, k, None, "f32")
+    flagged = _score(V, q, k, None, "f32", V.VLC_SHAPE_SCORE_PLAIN_ALU)
+    assert all(torch.equal(a, b) for a, b in zip(got, flagged)) == plain
+    stats = _score(V, q, k, None, "f32", stats=got[1:3])[0]
+    np.testing.assert_allclose(stats.cpu().numpy(), flagged[0].cpu().numpy(), rtol=5e-5, atol=1e-7)
+    np.testing.assert_allclose(got[0].cpu().numpy(), flagged[0].cpu().numpy(), rtol=5e-5, atol=1e-7)
