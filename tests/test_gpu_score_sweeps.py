@@ -1,8 +1,10 @@
-"""The matrix-core scoring sweeps (bf16 with d = 64 and fp32 storage: score_wave.hip; ragged batches of bf16 with
-d = 128: score_mfma.hip) at the sizes where their division of the work can go wrong: one key, one window row, remainders of the 32-key tiles and 32-row blocks, each
-block form (up to 4, 8, 16 row blocks), windows that take several launches, more tiles than a round of waves, ragged
-batches with NaN in all padding.  Against the oracle, to the tolerances of the scoring path (fp32 accumulation of
-products that are exact in fp32, respectively rounded once; a 1-ulp exponential)."""
+"""The scoring sweeps at the sizes where their division of the work can go wrong: bf16 with d = 64 and fp32 storage on the
+matrix cores (score_wave.hip), ragged batches of bf16 with d = 128 (score_mfma.hip), and the plain-ALU sweeps of every storage
+type and head dimension (score_simple.hip).  One key, one window row, remainders of the 32-key tiles and 32-row blocks, each
+block form (up to 4, 8, 16 row blocks, blocks shared between heads), windows that take several launches, waves that walk
+several tiles, ragged batches with NaN in all padding; each by vlc_score and from the statistics it wrote.  Against the
+oracle, to the tolerances of the scoring path (fp32 accumulation of products that are exact in fp32, respectively rounded
+once; a 1-ulp exponential)."""
 import numpy as np
 import pytest
 import torch
@@ -17,7 +19,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("dtype,d,Hq,Hkv,lens", [
     ("bf16", 64, 2, 2, [(1, 1)]),                                # one key
     ("bf16", 64, 4, 1, [(31, 1), (33, 33)]),                     # shorter than a tile; the window is the whole prompt
-    ("bf16", 64, 8, 2, [(2049, 32)]),                            # 4 row blocks, several rounds of tiles, a tile of one key
+    ("bf16", 64, 8, 2, [(2049, 32)]),                            # 4 row blocks, 9 splits, the last with a tile of one key
     ("bf16", 64, 5, 1, [(300, 32), (257, 7)]),                   # 5 row blocks
     ("bf16", 64, 8, 1, [(515, 33), (515, 5)]),                   # 16 row blocks; 8 for the shorter window
     ("bf16", 64, 8, 1, [(700, 65), (64, 64), (40, 3)]),          # 24 row blocks: two launches, the second empty for the others
@@ -37,10 +39,38 @@ pytestmark = pytest.mark.gpu
     ("f32", 64, 3, 1, [(300, 1)]),                               # three: the matrix cores
     ("f32", 128, 8, 1, [(130, 9), (40, 1)]),
     ("f32", 128, 3, 1, [(70, 17)]),                              # one row more: a block per head
+    # 8 KV groups of long prompts: splits of 24 tiles (of 32 for the 16-wave form), two or three tiles per wave, the last ones short
+    ("bf16", 64, 4, 4, [(20001, 20)]),
+    ("bf16", 64, 20, 4, [(20001, 64)]),                          # 10 row blocks
+    ("bf16", 64, 4, 2, [(20001, 20), (9000, 3)]),                # the second request ends in the middle of the splits
+    ("bf16", 64, 4, 4, [(20001, 5)]),                            # shared row blocks
+    ("f32", 64, 8, 4, [(20001, 33)]),
+    ("f32", 64, 12, 4, [(17000, 70)]),                           # the 16-wave form
+    ("f32", 128, 4, 4, [(17000, 40)]),
+    ("f32", 128, 4, 4, [(17000, 3)]),
     ("bf16", 128, 4, 1, [(600, 100), (500, 64), (257, 20)]),     # 16, 8 and 4 row blocks in one launch
     ("bf16", 128, 8, 1, [(700, 70), (300, 33), (65, 5)]),        # 24, 16 and 8: the first needs a second launch
 ])
 def test_sweeps_match_the_oracle(dtype, d, Hq, Hkv, lens):
+    _check_sweeps(dtype, d, Hq, Hkv, lens)
+
+
+@pytest.mark.parametrize("dtype,d,Hq,Hkv,lens", [
+    ("bf16", 64, 4, 1, [(31, 1), (33, 33)]),
+    ("bf16", 64, 14, 2, [(600, 50)]),
+    ("bf16", 128, 8, 2, [(700, 70), (300, 33), (65, 5)]),
+    ("f32", 64, 2, 1, [(800, 600)]),                             # 19 stages of 32 window rows
+    ("f32", 64, 4, 2, [(300, 20), (123, 9), (511, 31)]),
+    ("f32", 128, 6, 2, [(333, 64), (65, 1)]),
+    ("f32", 128, 3, 1, [(1, 1)]),
+])
+def test_plain_alu_sweeps_match_the_oracle(dtype, d, Hq, Hkv, lens):
+    """The sweeps that VLC_SHAPE_SCORE_PLAIN_ALU asks for, in each of their four instances."""
+    import paper_2410_23317_amd as V
+    _check_sweeps(dtype, d, Hq, Hkv, lens, V.VLC_SHAPE_SCORE_PLAIN_ALU)
+
+
+def _check_sweeps(dtype, d, Hq, Hkv, lens, flags=0):
     import paper_2410_23317_amd as V
     B, L = len(lens), 2
     m, tau = max(x[0] for x in lens), max(x[1] for x in lens)
@@ -57,23 +87,27 @@ def test_sweeps_match_the_oracle(dtype, d, Hq, Hkv, lens):
             k[b, l, :, : cfg.m].copy_(torch.from_numpy(t["k"]).to(dt))
     lens_t = torch.tensor(lens, dtype=torch.int32, device="cuda") if B > 1 else None
     scales = W.sm_scale(cfgs[0])
-    shape = V.make_shape(B, L, Hq, Hkv, d, m, tau, dtype, lens=lens_t)
+    shape = V.make_shape(B, L, Hq, Hkv, d, m, tau, dtype, lens=lens_t, flags=flags)
     ws = torch.full((V.vlc_workspace_bytes(shape),), 255, dtype=torch.uint8, device="cuda")
     new = lambda *s: torch.full(s, float("nan"), dtype=torch.float32, device="cuda")
     scores, row_max, row_sum = new(B, L, Hkv, m), new(B, L, Hq, tau), new(B, L, Hq, tau)
     nnz = torch.full((B, L, Hq), 77, dtype=torch.int64, device="cuda")
-    V.vlc_score(shape, q_win, k, torch.from_numpy(scales).cuda(), 0.01, scores, row_max, row_sum, nnz, ws)
+    sm = torch.from_numpy(scales).cuda()
+    V.vlc_score(shape, q_win, k, sm, 0.01, scores, row_max, row_sum, nnz, ws)
+    again, nnz2 = new(B, L, Hkv, m), torch.full_like(nnz, 77)
+    V.vlc_score_from_stats(shape, q_win, k, sm, 0.01, row_max, row_sum, again, nnz2)
     torch.cuda.synchronize()
     for b, cfg in enumerate(cfgs):
-        assert torch.all(scores[b, :, :, cfg.m:] == 0), "keys beyond the request's prompt score zero"
         assert torch.all(torch.isnan(row_max[b, :, :, cfg.tau:])), "window rows beyond the request's are left untouched"
         for l in range(L):
-            t, what = host[b, l], f"b={b} l={l}"
+            t = host[b, l]
             psi, _, M, Z = O.score(t["q_win"], t["k"], scales[l])
-            assert_close(scores[b, l, :, : cfg.m].cpu().numpy(), psi, what=what + " scores", **SCORE_TOL)
-            assert_close(row_max[b, l, :, : cfg.tau].cpu().numpy(), M, atol=2e-5, rtol=2e-6, what=what + " row_max")
-            assert_close(row_sum[b, l, :, : cfg.tau].cpu().numpy(), Z, atol=0, rtol=5e-5, what=what + " row_sum")
-            check_nnz(nnz[b, l].cpu().numpy(), t["q_win"], t["k"], scales[l], 0.01, what + " nnz")
+            assert_close(row_max[b, l, :, : cfg.tau].cpu().numpy(), M, atol=2e-5, rtol=2e-6, what=f"b={b} l={l} row_max")
+            assert_close(row_sum[b, l, :, : cfg.tau].cpu().numpy(), Z, atol=0, rtol=5e-5, what=f"b={b} l={l} row_sum")
+            for got, counts, what in ((scores, nnz, f"b={b} l={l}"), (again, nnz2, f"b={b} l={l} from statistics")):
+                assert torch.all(got[b, l, :, cfg.m:] == 0), "keys beyond the request's prompt score zero"
+                assert_close(got[b, l, :, : cfg.m].cpu().numpy(), psi, what=what + " scores", **SCORE_TOL)
+                check_nnz(counts[b, l].cpu().numpy(), t["q_win"], t["k"], scales[l], 0.01, what + " nnz")
 
 
 def _upload(dtype, d, L, Hq, Hkv, m, tau, cid):
@@ -205,7 +239,7 @@ def test_few_groups_of_long_prompts_are_merged_by_a_kernel_of_their_own(dtype, d
     """Fewer than 8 KV groups and more than 32 x 256 keys: more key splits than the column sweep merges itself.  Scores,
     statistics and counts against the oracle, and the counts of the standalone sparsity sweep."""
     import paper_2410_23317_amd as V
-    test_sweeps_match_the_oracle(dtype, d, Hq, 1, lens)
+    _check_sweeps(dtype, d, Hq, 1, lens)
     m, tau = lens[0]
     _, (q, k, _), scales = _upload(dtype, d, 2, Hq, 1, m, tau, 823)
     sm = torch.from_numpy(scales).cuda()
