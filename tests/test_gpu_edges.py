@@ -156,9 +156,9 @@ def test_recent_fraction_extremes():
                     assert want.tolist() == list(range(m - int(kk[0, l]), m))
 
 
-@pytest.mark.parametrize("m", [4096, 4097, 12288, 12289, 32768, 32769, 40001])
+@pytest.mark.parametrize("m", [4096, 4097, 6144, 6145, 12288, 12289, 32768, 32769, 40001])
 def test_topk_row_lengths_around_the_register_resident_limits(m):
-    """The selection keeps a row's keys in registers up to 32768 positions (8, 24 or 64 per lane)
+    """The selection keeps a row's keys in registers up to 32768 positions (8, 12, 24 or 64 per lane)
     and streams longer rows; each variant, with heavy ties and a ragged tail, against the oracle."""
     V = _V()
     r = np.random.default_rng(m)
