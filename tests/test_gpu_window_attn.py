@@ -90,12 +90,16 @@ def test_window_attn_and_scores_from_its_statistics_match_the_oracle(cid, B, L, 
     assert_close(row_sum.cpu().numpy(), Z2.cpu().numpy(), atol=0, rtol=5e-5, what=f"cid={cid} row_sum vs vlc_score")
 
 
-def test_window_attn_ragged_batch_reads_nothing_beyond_each_request():
+@pytest.mark.parametrize("Hq,Hkv,lens", [
+    (8, 2, [(900, 40), (333, 7), (1200, 64), (64, 64)]),
+    (4, 1, [(600, 100), (500, 64), (257, 20)]),         # 16, 8 and 4 row blocks: a second attention launch for the first request alone
+    (8, 1, [(700, 70), (300, 33), (65, 5)]),            # 24, 16 and 8: three, two and one; the column sweep takes two
+])
+def test_window_attn_ragged_batch_reads_nothing_beyond_each_request(Hq, Hkv, lens):
     import paper_2410_23317_amd as V
-    lens = [(900, 40), (333, 7), (1200, 64), (64, 64)]
-    Hq, Hkv, L, d = 8, 2, 2, 128
+    L, d = 2, 128
     cfgs = [_cfg(420 + i, 1, L, Hq, Hkv, m, tau) for i, (m, tau) in enumerate(lens)]
-    B, m_max, tau_max = len(lens), 1200, 64
+    B, m_max, tau_max = len(lens), max(x[0] for x in lens), max(x[1] for x in lens)
     dt = torch.bfloat16
     q_win = torch.full((B, L, Hq, tau_max, d), float("nan"), dtype=dt, device="cuda")
     k = torch.full((B, L, Hkv, m_max, d), float("nan"), dtype=dt, device="cuda")
@@ -155,7 +159,7 @@ def test_a_layers_logit_scale_may_be_zero_or_negative(plain):
 
 
 def test_score_from_stats_takes_the_statistics_as_given_fp32_storage():
-    """Plain-ALU sweeps (fp32 storage, d = 64): statistics computed on the host by the oracle, handed in."""
+    """Column sweep of fp32 storage, d = 64: statistics computed on the host by the oracle, handed in."""
     import paper_2410_23317_amd as V
     cfg = _cfg(430, 1, 2, 4, 2, 300, 20, dtype="f32", d=64)
     q_win = torch.empty((1, 2, 4, 20, 64), dtype=torch.float32, device="cuda")
