@@ -87,6 +87,8 @@ def test_fixed_sliding_window_scoring_policy(w):
 @pytest.mark.parametrize("kw", [
     dict(cid=98, dtype="bf16", d=128, Hq=8, Hkv=2, m=1500, tau=24, lead_text=16, n_visual=1460, L=3, B=2, sinks=6),
     dict(cid=99, dtype="f32", d=64, Hq=4, Hkv=2, m=333, tau=7, lead_text=5, n_visual=320, L=2, B=1, sinks=3),
+    # 5000 positions: the selection's form for 12 keys per lane; six heads share the row block of the one-row window
+    dict(cid=104, dtype="bf16", d=64, Hq=6, Hkv=1, m=5000, tau=9, lead_text=5, n_visual=4980, L=2, B=1, sinks=5),
 ])
 def test_cache_hit_rate_against_the_first_decode_query(kw):
     """Def. 3.1 on the GPU: psi* from the first decode query (the scoring kernels with a one-row
@@ -133,7 +135,7 @@ def test_cache_hit_rate_against_the_first_decode_query(kw):
     dict(cid=101, dtype="bf16", d=128, Hq=7, Hkv=1, m=900, tau=100, lead_text=10, n_visual=800, L=2, B=2, sinks=4),
     # 17 row blocks: a second launch with a single row block (the 4-wave kernels with three idle waves)
     dict(cid=102, dtype="bf16", d=128, Hq=1, Hkv=1, m=700, tau=530, lead_text=10, n_visual=100, L=1, B=1, sinks=2),
-    # fp32 storage takes the plain-ALU sweeps, which stage 32 window rows at a time: 19 stages
+    # fp32 storage: 38 row blocks, three launches of its own matrix-core sweeps
     dict(cid=103, dtype="f32", d=64, Hq=2, Hkv=1, m=800, tau=600, lead_text=10, n_visual=100, L=1, B=2, sinks=2),
 ])
 def test_windows_longer_than_one_launch_of_row_blocks(kw):

@@ -26,7 +26,7 @@ def _requests(dtype, d, Hq, Hkv, L, lens, cid0):
 @pytest.mark.parametrize("dtype,d,Hq,Hkv,L,lens", [
     ("bf16", 128, 8, 2, 3, [(900, 40), (333, 7), (1200, 64), (64, 64)]),       # matrix-core sweeps, 8-wave blocks
     ("bf16", 128, 4, 1, 2, [(257, 1), (700, 33)]),                             # window rows padded to 64 per head
-    ("f32", 64, 4, 2, 2, [(300, 20), (123, 9), (511, 31)]),                    # plain-ALU sweeps
+    ("f32", 64, 4, 2, 2, [(300, 20), (123, 9), (511, 31)]),                    # fp32 storage: sweeps with Q' in LDS
 ])
 def test_ragged_batch_matches_the_oracle_request_by_request(dtype, d, Hq, Hkv, L, lens):
     _ragged_case(dtype, d, Hq, Hkv, L, lens)
