@@ -80,9 +80,9 @@ typedef struct {
     int32_t reserved;          /* 0 */
 } vlc_shape;
 
-/* vlc_shape.flags: take the plain-ALU scoring sweeps, and the generic window-attention kernel, even where the
- * matrix-core kernels cover the shape (bf16, d = 128).  Same results to the stated tolerances; a cross-check
- * for tests.  The workspace queries and the calls read the flag from the same shape, so a size query and the
+/* vlc_shape.flags: take the plain-ALU scoring sweeps, which every dtype and d has, instead of the matrix-core ones
+ * (without the flag they serve fp32 shapes of one or two window rows per KV head only), and the generic window-attention
+ * kernel even for bf16 with d = 128.  Same results to the stated tolerances; a cross-check for tests.  The workspace queries and the calls read the flag from the same shape, so a size query and the
  * call it is for always agree. */
 #define VLC_SHAPE_SCORE_PLAIN_ALU 1
 
@@ -103,7 +103,7 @@ size_t vlc_workspace_bytes(const vlc_shape* shape);
  *
  * q_win   [B,L,Hq,tau,d]  in   storage dtype
  * k       [B,L,Hkv,m,d]   in   storage dtype
- * sm_scale[L] float       in   per-layer logit scale, or NULL for 1/sqrt(d)
+ * sm_scale[L] float       in   per-layer logit scale, any finite number, or NULL for 1/sqrt(d)
  * p                       in   threshold in (0,1); ignored when nnz == NULL
  * scores  [B,L,Hkv,m]     out  fp32
  * row_max [B,L,Hq,tau]    out  fp32, M_i (natural-log domain)

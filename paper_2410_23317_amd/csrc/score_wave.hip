@@ -13,16 +13,15 @@
 // blocks of a request are those of its own window length, so a short window in a ragged batch costs what it holds.
 // Windows of up to 16 rows (one row where the cache's hit rate is asked for) share a block between heads instead, each
 // head padded to a power of two; a row then counts its own entries of Eq. 1.  64 KV groups of 4 heads, 4096 keys, one row,
-// both sweeps and sweep 2 alone: the plain ALU 70.5
-// and 17.5 us, a block per head 85.5 and 42.0, shared 34.8 and 17.5 (fp32, d = 64); 121 and 32, 147 and 74.5, 55.1 and 27.1
-// (fp32, d = 128); 50.3 and 11.8, 25.2 and 12.4, 16.1 and 7.3 (bf16).
+// both sweeps and sweep 2 alone: the plain ALU 70.5 and 17.5 us, a block per head 85.5 and 42.0, shared 34.8 and 17.5 (fp32,
+// d = 64); 121 and 32, 147 and 74.5, 55.1 and 27.1 (fp32, d = 128); 50.3 and 11.8, 25.2 and 12.4, 16.1 and 7.3 (bf16).
 //
 // What bounds them: at d = 64 in bf16 the vector unit (about 330 issue cycles per tile beside 128 of matrix work), in
 // fp32 the matrix cores (64 cycles per instruction and 2 contraction indexes), and for the smallest problems the
-// chain of launch, first loads and merge.  Measured against one thread per key on the
-// plain ALU: bf16, 2 x 24 layers of 16 (4 KV) heads of 64 over 4096 keys with 50 window rows, 717 + 9 + 417 us -> 56 + 61 us;
-// fp32, 2 layers of 4 (2 KV) heads of 64 over 512 keys with 32 rows, 30 + 4 + 31 us -> 11.5 + 9.4 us (6.5 with sweep 2's shorter splits).  Errors against
-// 64-bit arithmetic are those of the plain-ALU sweeps or smaller (scores 0.5-3e-7 relative, row sums 1-4e-7).
+// chain of launch, first loads and merge.  Profiled against one thread per key on the plain ALU: bf16, 2 x 24 layers of 16
+// (4 KV) heads of 64 over 4096 keys with 50 window rows, 717 + 9 + 417 us -> 56 + 61 us; fp32, 2 layers of 4 (2 KV) heads
+// of 64 over 512 keys with 32 rows, 30 + 4 + 31 us -> 11.0 + 7.1 us.  Errors against 64-bit arithmetic are those of the
+// plain-ALU sweeps or smaller (logits up to 20: scores 0.8-3e-7 relative, row maxima 0.5-2e-7, row sums 2-8e-7).
 #include "common.h"
 #include "internal.h"
 #include "score_tiles.h"     // acc_row, as_frag

@@ -13,9 +13,9 @@
 namespace vlc {
 namespace {
 
-// One block for the whole batch (B*L is a few hundred entries): clears the sticky status, validates
-// the budgets, lays the slabs of each request out back to back, and builds the decode work list.
-// Everything is staged in LDS so that the serial prefix sums never wait on global memory.
+// The layout of the whole batch (B*L is a few hundred entries): clears the sticky status, validates the budgets, lays the
+// slabs of each request out back to back, and builds the work lists of decode and gather.  Every block does it for all
+// entries, staged in LDS so that the serial prefix sums never wait on global memory, and writes its share of the result.
 constexpr int kLayoutMaxBL = 2048;     // B*L entries staged in LDS (the shape check admits no larger batch)
 
 struct LayoutArgs {
@@ -39,7 +39,8 @@ __device__ __forceinline__ RowUnits row_units(int kk, int T_max, int ub, int us)
 // once budgets and slab offsets are known, and those are cheap, so every block derives them.  A block builds the lists
 // of the bit mask `lists`, and of those the records of every shares-th group of rows, from its own `share` on (the
 // prefix sums are repeated in each block, the records are what takes the time: 58,000 of 64 bytes for one prompt
-// of 131,072 tokens, 44 us with one block per list, 12 with sixteen; four prompts of 10,368, 22 -> 15).  The first block of list 0 also writes out budgets and offsets, zeroes the counters and reports errors.
+// of 131,072 tokens, 44 us with one block per list, 12 with sixteen; four prompts of 10,368, 22 -> 15).  The first block of
+// list 0 also writes out budgets and offsets, zeroes the counters and reports errors.
 template <int NT>
 __device__ void layout_body(const LayoutArgs& a, CacheDev dev, int lists, int share, int shares) {
     const int32_t* __restrict__ k = a.k;
@@ -685,7 +686,8 @@ hipError_t launch_topk_compact(const vlc_cache& c, const int32_t* lens, const fl
     const int rows = s.B * s.L * s.Hkv;
     LayoutArgs la{k, lens, s.B, s.L, s.Hkv, s.m, s.tau, s.d, c.T_max, c.slots_per_request};
     // values per lane of a wave's segment (an eighth of the row, rounded up to whole wave loads); a form for 12 because
-    // every pass visits all register slots (2048 rows of 4099 scores, 9 per lane: 62 us in the form for 24, 45 in this)
+    // every pass visits all register slots (2048 rows of 4099 scores, 9 per lane: 62 us in the form for 24, 45 in this).
+    // Rows of 12289 to about 20000 scores leave as many slots of the form for 64 empty; a form between is not built.
     const int per_lane = (((s.m + kSelWaves - 1) / kSelWaves + 63) / 64);
     // the layout as one more block of the selection (short rows only), or as a kernel of its own
     const bool fold = c.opt.select_fold == 2 && per_lane <= 8;
