@@ -399,7 +399,8 @@ static vlc_status cache_layout(const vlc_shape* s, int32_t T_max, int64_t sum_k_
             return fail(VLC_ERR_SHAPE, "cache of %lld decode units: budgets plus reserved appends are too large", (long long)plan->cap[i]);
     plan->opt = o;
     const int g = s->Hq / s->Hkv;
-    const int64_t cap_max = plan->cap[0] > plan->cap[1] ? plan->cap[0] : plan->cap[1];      // the gather's list leaves no partial results
+    // partial results of decode: a row has at most one unit per kMinUnitSlots slots of its slab, and one for the remainder
+    const int64_t partials = (int64_t)s->B * spr * s->Hkv / vlc::kMinUnitSlots + (int64_t)BL * s->Hkv;
     size_t off = 0;
     lay->status_off = off;      off = align_up(off + 4 * sizeof(int32_t), 256);
     lay->slot_off_off = off;    off = align_up(off + BL * sizeof(int64_t), 256);
@@ -413,7 +414,7 @@ static vlc_status cache_layout(const vlc_shape* s, int32_t T_max, int64_t sum_k_
         plan->layer_start_off[i] = off;  off = align_up(off + (size_t)(s->L + 2) * sizeof(int32_t), 256);
         plan->row_first_off[i] = off;    off = align_up(off + BL * s->Hkv * sizeof(int32_t), 256);
     }
-    plan->partials_off = off;     off = align_up(off + (size_t)cap_max * g * (s->d + 2) * sizeof(float), 256);
+    plan->partials_off = off;     off = align_up(off + (size_t)partials * vlc::partial_floats(g, s->d) * sizeof(float), 256);
     plan->counters_off = off;     off = align_up(off + BL * s->Hkv * sizeof(int32_t), 256);
     plan->readers_off = off;      off = align_up(off + (size_t)(s->L + 1) * vlc::kReaderStride * sizeof(int32_t), 256);
     plan->lens_off = off;         off = align_up(off + (size_t)s->B * 2 * sizeof(int32_t), 256);

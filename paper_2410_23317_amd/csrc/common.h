@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace vlc {
 
 constexpr float kLog2e = 1.4426950408889634f;
@@ -151,13 +153,11 @@ __device__ __forceinline__ uint2 quantize_row_e4m3(const uint4& v, float& scale)
     return make_uint2((uint32_t)lo, (uint32_t)hi);
 }
 
-// 8 E4M3 codes -> 8 bf16 values (exact: E4M3 has 3 mantissa bits), packed like a 16-byte bf16 chunk.
+// 8 E4M3 codes -> 8 bf16 values (exact: E4M3 has 3 mantissa bits), packed like a 16-byte bf16 chunk.  The scaled conversion
+// with a scale of 1 gives the same bits as v_cvt_pk_f32_fp8 and a cut for all 256 codes, in half the instructions.
 __device__ __forceinline__ uint4 e4m3x8_to_bf16x8(const uint2& r) {
-    const auto a = __builtin_amdgcn_cvt_pk_f32_fp8((int)r.x, false), b = __builtin_amdgcn_cvt_pk_f32_fp8((int)r.x, true);
-    const auto c = __builtin_amdgcn_cvt_pk_f32_fp8((int)r.y, false), d = __builtin_amdgcn_cvt_pk_f32_fp8((int)r.y, true);
-    // upper halves of two fp32 words -> one word of two bf16 (first element in the low half)
-    auto pack = [](float lo, float hi) { return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u); };
-    return make_uint4(pack(a[0], a[1]), pack(b[0], b[1]), pack(c[0], c[1]), pack(d[0], d[1]));
+    auto two = [](uint32_t w, auto hi) { return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, 1.0f, decltype(hi)::value)); };
+    return make_uint4(two(r.x, std::false_type{}), two(r.x, std::true_type{}), two(r.y, std::false_type{}), two(r.y, std::true_type{}));
 }
 
 __device__ __forceinline__ float wave_allreduce_max(float x) {

@@ -420,7 +420,7 @@ def test_decode_merges_across_units(opt, per_layer):
     run_and_check(cfg, (1, 2), 3, options=opt, per_layer_decode=per_layer)
 
 
-def _direct_cache(V, cfg, kk, T_max, options):
+def _direct_cache(V, cfg, kk, T_max, options, fill=None):
     """A cache filled by vlc_topk_compact with GIVEN budgets kk [B, L] (scores are the workload's own); returns
     the path-like pieces and, per (b, l), the lists of kept K and V rows: the rows at the positions the cache holds,
     after those positions have been checked against the oracle's ranking (equal sets, except swaps among scores
@@ -429,6 +429,8 @@ def _direct_cache(V, cfg, kk, T_max, options):
     from paper_2410_23317_amd.pipeline import VLCachePath, cache_layer_view
     dev = upload(cfg)
     path = VLCachePath(make_shape(cfg), alpha=(1, 2), T_max=T_max, options=V.make_options(**options))
+    if fill is not None:
+        path.cache.arena.fill_(fill)            # bytes that the compaction does not write keep this value
     path.score(dev["q_win"], dev["k"], dev["sm_scale"])
     path.topk_compact(dev["k"], dev["v"], k=torch.from_numpy(kk.astype(np.int32)).cuda())
     path.status()
@@ -488,6 +490,39 @@ def test_rows_that_grow_across_a_unit_boundary_during_decode(unit, merge, order)
             _oracle_step(cfg, caches, scales, d_host, out.float().cpu().numpy(), step, f"unit={unit} per_layer={per_layer}")
             crossed |= (unit - 2 + step + 1) > unit
         assert crossed
+        path.status()
+
+
+@pytest.mark.parametrize("fp8", [False, True], ids=["bf16-cache", "fp8-cache"])
+@pytest.mark.parametrize("g,d", [(1, 64), (2, 128), (3, 64), (5, 128), (6, 64), (8, 128)])
+def test_decode_tiles_at_their_edges_for_every_number_of_heads(g, d, fp8):
+    """Rows that end just before, on and behind a 32-slot tile and a 128-slot unit, grown over those edges by three
+    appends (the appended row is attended over beside the tiles, by the last wave of its unit, which may hold no tile at
+    all), with all bytes of the arena set beforehand: what a cache does not hold reads as NaN if a tile lets it through.
+    Every step against the oracle, over all layers and per layer, to the decode tolerance."""
+    V = _V()
+    kk = np.array([[1, 30, 31, 32, 33, 64, 95, 126, 127, 128, 129, 255]])
+    cfg = _small_cfg(cid=97, m=520, n_visual=440, L=kk.shape[1], B=1, Hq=2 * g, Hkv=2, d=d)
+    T = 3
+    for per_layer in (False, True):
+        path, dev, caches, scales = _direct_cache(V, cfg, kk, T, dict(unit_slots=128, layer_unit_slots=128, kv_fp8=int(fp8)), fill=255)
+        if fp8:                                                  # the oracle attends over what the FP8 cache holds
+            for key, (kc, vc) in caches.items():
+                caches[key] = ([O.dequantize_e4m3_rows(*O.quantize_e4m3_rows(x)) for x in kc], [O.dequantize_e4m3_rows(*O.quantize_e4m3_rows(x)) for x in vc])
+        out = torch.empty((cfg.L, cfg.B, cfg.Hq, cfg.d), dtype=torch.bfloat16, device="cuda")
+        for step in range(T):
+            d_host = W.decode_step_inputs(cfg, step)
+            dd = {n: torch.from_numpy(x).to(torch.bfloat16).cuda() for n, x in d_host.items()}
+            if per_layer:
+                for l in range(cfg.L):
+                    path.decode(l, l + 1, dd["q"][l], dd["k_new"][l], dd["v_new"][l], dev["sm_scale"], out[l])
+            else:
+                path.decode(0, cfg.L, dd["q"], dd["k_new"], dd["v_new"], dev["sm_scale"], out)
+            torch.cuda.synchronize()
+            if fp8:
+                d_host = dict(d_host, k_new=O.dequantize_e4m3_rows(*O.quantize_e4m3_rows(d_host["k_new"])),
+                              v_new=O.dequantize_e4m3_rows(*O.quantize_e4m3_rows(d_host["v_new"])))
+            _oracle_step(cfg, caches, scales, d_host, out.float().cpu().numpy(), step, f"g={g} d={d} fp8={fp8} per_layer={per_layer}")
         path.status()
 
 
