@@ -12,8 +12,12 @@
 //           Eq. 1 test is one compare on the exponent argument.
 // Q' fragments of a block's rows live in registers for the whole sweep; K streams through LDS in
 // chunks of 128 keys (global -> registers -> LDS, the next chunk in flight while the current one is
-// multiplied).  Each head's tau window rows are padded to a multiple of 32 so that every 32-row
-// block belongs to one query head; padded rows carry a +inf offset and vanish from every sum.
+// multiplied).  Sweep 1 packs the window rows of the group's heads into 32-row blocks one after the other (a lane
+// owns a row whatever block it is in, so the statistics have the same bits).  In sweep 2 each head's tau rows are padded to a
+// multiple of 32 so that every 32-row block belongs to one query head, and its sums keep their order; padded rows carry a
+// +inf offset and vanish from every sum, and groups of eight rows that are all padding are left out (the exponentials are
+// what costs power here, and power bounds both sweeps).  256 KV groups of 131072 keys, 4 heads of 50 rows (7 blocks instead of
+// 8, 7 of 8 row groups): both sweeps 5990 -> 5600 us; 8 ragged requests of up to 100 rows 1325 -> 1270.
 // In a ragged batch the blocks are those of the request's own window length, dealt to the waves from the first on (and
 // round-robin where a wave takes two), so a shorter window costs the blocks it holds: the waves beyond it only
 // help to stage K; in large batches whose longest window takes the 16-block forms, requests of up to 8 blocks get a launch
@@ -47,9 +51,9 @@ struct MfmaArgs {
     int accumulate;          // sweep 2: add to scores instead of overwriting (row groups after the first)
 };
 
-// Whether a launch takes the requests with RP padded window rows per KV group (block-uniform).
-__device__ __forceinline__ bool in_class(const MfmaArgs& a, int RP) {
-    const int nrb = RP / 32 - a.rb0;
+// Whether a launch takes the requests with so many 32-row blocks per KV group (block-uniform).
+__device__ __forceinline__ bool in_class(const MfmaArgs& a, int row_blocks) {
+    const int nrb = row_blocks - a.rb0;
     return nrb > a.rb_above && nrb <= a.rb_upto;
 }
 
@@ -66,22 +70,22 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 0) void rowstats_mfma_
     const bf16_t* kg = a.k + (size_t)group * a.m * kD;
     const ReqLen rl = request_len(a.lens, bl / a.L, a.m, a.tau);
     const int mb = rl.m, tb = rl.tau;                       // this request's prompt and window length
-    const int tauP = padded_rows(tb), RP = a.g * tauP;      // and its padded rows, the launch's (a.RP) or fewer
+    const int R = a.g * tb;                                 // window rows of its KV groups, head after head
     const int k_begin = split * a.keys_per_split;
     const int k_end = min(mb, k_begin + a.keys_per_split);
 
     if (a.nnz && split == 0 && a.rb0 == 0 && (int)threadIdx.x < a.g)
         a.nnz[(size_t)bl * a.Hq + (size_t)hkv * a.g + threadIdx.x] = 0;      // sweep 2 adds into these
-    if (!in_class(a, RP)) return;                           // this request's window is another launch's work
+    if (!in_class(a, (R + 31) / 32)) return;                // this request's window is another launch's work
     uint4 qf[RB][kKSteps];
-    load_q_frags<RB, WAVES>(a, bl, hkv, a.rb0 + wave, lane, tb, tauP, qf);      // row blocks rb0 + wave + WAVES * rb
+    load_q_frags<RB, WAVES>(a, bl, hkv, a.rb0 + wave, lane, tb, tb, qf);        // row blocks rb0 + wave + WAVES * rb
     // this lane's query row per row block, and the last key it may see (causal mask of Alg. 1)
     int jlim[RB];
     float m_run[RB], z_run[RB];
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb) {
         const int r = (a.rb0 + wave + WAVES * rb) * 32 + (lane & 31);
-        jlim[rb] = mb - tb + (r % tauP);
+        jlim[rb] = mb - tb + (r % tb);
         m_run[rb] = -INFINITY;
         z_run[rb] = 0.f;
     }
@@ -102,7 +106,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 0) void rowstats_mfma_
             load_k_frags(sK, t, lane, kf);
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {
-                if ((a.rb0 + wave + WAVES * rb) * 32 >= RP) continue;       // wave-uniform: no rows here
+                if ((a.rb0 + wave + WAVES * rb) * 32 >= R) continue;        // wave-uniform: no rows here
                 f32x16_t acc = {0};
 #pragma unroll
                 for (int ks = 0; ks < kKSteps; ++ks)
@@ -139,7 +143,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 0) void rowstats_mfma_
         if (m_run[rb] > -INFINITY) z += z_run[rb] * exp2_fast(m_run[rb] - mm);
         if (mo > -INFINITY) z += zo * exp2_fast(mo - mm);
         const int r = (a.rb0 + wave + WAVES * rb) * 32 + (lane & 31);
-        if (lane < 32 && r < RP) a.part[((size_t)group * a.nsplit + split) * a.RP + r] = make_float2(mm, z);
+        if (lane < 32 && r < R) a.part[((size_t)group * a.nsplit + split) * a.RP + r] = make_float2(mm, z);
     }
 }
 
@@ -158,7 +162,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 4) void colsweep_mfma_
     const ReqLen rl = request_len(a.lens, bl / a.L, a.m, a.tau);
     const int mb = rl.m, tb = rl.tau;                       // this request's prompt and window length
     const int tauP = padded_rows(tb), RP = a.g * tauP;      // and its padded rows, the launch's (a.RP) or fewer
-    if (!in_class(a, RP)) return;                           // this request's window is another launch's work
+    if (!in_class(a, RP / 32)) return;                      // this request's window is another launch's work
     const int k_begin = split * a.keys_per_split;
     const int k_end = min(mb, k_begin + a.keys_per_split);
 
@@ -168,11 +172,12 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 4) void colsweep_mfma_
     constexpr int kSplitRegs = 4;               // splits whose partials a thread holds at once (more are merged in rounds)
     float2 pin[kSplitRegs];
     const int r_mine = a.rb0 * 32 + (int)threadIdx.x;       // the row whose statistics this thread merges (first round)
-    const bool mine = a.part_in && (int)threadIdx.x < WAVES * RB * 32 && r_mine < RP;
+    const bool mine = a.part_in && (int)threadIdx.x < WAVES * RB * 32 && r_mine < RP && r_mine % tauP < tb;
     if (mine) {
+        const int at = r_mine / tauP * tb + r_mine % tauP;  // sweep 1 packs the heads' rows
 #pragma unroll
         for (int sp = 0; sp < kSplitRegs; ++sp)
-            pin[sp] = sp < a.nsplit ? a.part_in[((size_t)group * a.nsplit + sp) * a.RP + r_mine] : make_float2(-INFINITY, 0.f);
+            pin[sp] = sp < a.nsplit ? a.part_in[((size_t)group * a.nsplit + sp) * a.RP + at] : make_float2(-INFINITY, 0.f);
     }
     KStage<THREADS> st;
     if (k_begin < k_end) st.load(kg, k_begin, mb);
@@ -196,7 +201,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 4) void colsweep_mfma_
                     if (sp0 > 0 || t != (int)threadIdx.x) {          // beyond what was requested at the start
 #pragma unroll
                         for (int sp = 0; sp < kSplitRegs; ++sp)
-                            pin[sp] = sp0 + sp < a.nsplit ? a.part_in[((size_t)group * a.nsplit + sp0 + sp) * a.RP + r] : make_float2(-INFINITY, 0.f);
+                            pin[sp] = sp0 + sp < a.nsplit ? a.part_in[((size_t)group * a.nsplit + sp0 + sp) * a.RP + hl * tb + iw] : make_float2(-INFINITY, 0.f);
                     }
                     float Mn = M;
 #pragma unroll
@@ -259,31 +264,41 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 4) void colsweep_mfma_
             load_k_frags(sK, t, lane, kf);
             const int key = kc + t * 32 + (lane & 31);          // this lane's key (column of the tile)
             float col = 0.f;
+            auto add = [&](float product, int rb, int i) {
+                const float ea = fmaf(product, c, -mc[rb][i]);
+                col = fmaf(exp2_fast(ea), iz[rb][i], col);
+                cnt[rb] += (uint32_t)__popcll(__ballot(ea >= a.log2p));   // wave-wide count on the scalar unit
+            };
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {
-                if ((a.rb0 + wave + WAVES * rb) * 32 >= RP) continue;
+                const int base = (a.rb0 + wave + WAVES * rb) * 32;
+                if (base >= RP) continue;
+                const int rows = tb - base % tauP;          // of the block that exist: the rest adds nothing, eight rows at a time
                 f32x16_t acc = {0};
 #pragma unroll
                 for (int ks = 0; ks < kKSteps; ++ks)
                     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(qf[rb][ks]), as_frag(kf[ks]), acc, 0, 0, 0);
                 // acc[i] = <q_row, k_key>, row = row block base + acc_row(i), key = this lane's
                 if (masked) {
-                    const int base = mb - tb + ((a.rb0 + wave + WAVES * rb) * 32) % tauP;
+                    const int last = mb - tb + base % tauP;
 #pragma unroll
                     for (int i = 0; i < 16; ++i) {
-                        const bool valid = key <= base + acc_row(i, lane);
+                        const bool valid = key <= last + acc_row(i, lane);
                         const float ea = fmaf(acc[i], c, -mc[rb][i]);
                         const float e = valid ? exp2_fast(ea) : 0.f;
                         col = fmaf(e, iz[rb][i], col);
-                        cnt[rb] += (uint32_t)__popcll(__ballot(valid && ea >= a.log2p));   // wave-wide count on the scalar unit
+                        cnt[rb] += (uint32_t)__popcll(__ballot(valid && ea >= a.log2p));
                     }
+                } else if (rows > 24) {
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) add(acc[i], rb, i);
                 } else {
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const float ea = fmaf(acc[i], c, -mc[rb][i]);
-                        col = fmaf(exp2_fast(ea), iz[rb][i], col);
-                        cnt[rb] += (uint32_t)__popcll(__ballot(ea >= a.log2p));
-                    }
+                    for (int q = 0; q < 3; ++q)
+                        if (8 * q < rows) {                 // wave-uniform
+#pragma unroll
+                            for (int i = 4 * q; i < 4 * q + 4; ++i) add(acc[i], rb, i);
+                        }
                 }
             }
             {   // the lane halves hold different rows of the same key: lane l + lane l ^ 32, with the lane-swap
@@ -398,7 +413,7 @@ hipError_t launch_rowstats_mfma(const ScoreArgs& a) {
     // splits of a group run on one XCD and share its Q' rows in that XCD's L2 (cfg1: 44.7 -> 42.3 us, sweep 2
     // 49.5 -> 45.5 us; no change for shapes whose splits are dispatched rounds apart).
     dim3 grid(groups, p.nsplit);
-    const int total_rb = p.RP / 32;
+    const int total_rb = (m.g * s.tau + 31) / 32;           // the heads' rows are packed
     for (int rb0 = 0; rb0 < total_rb; rb0 += kMaxRowBlocksPerLaunch) {
         const int nrb = total_rb - rb0 < kMaxRowBlocksPerLaunch ? total_rb - rb0 : kMaxRowBlocksPerLaunch;
         m.rb0 = rb0; m.rb_above = 0;

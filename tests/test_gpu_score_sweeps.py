@@ -55,6 +55,18 @@ def test_sweeps_match_the_oracle(dtype, d, Hq, Hkv, lens):
     _check_sweeps(dtype, d, Hq, Hkv, lens)
 
 
+@pytest.mark.parametrize("Hq,lens", [
+    (4, [(300, 8), (300, 9), (290, 16), (133, 17), (300, 24), (300, 25), (64, 1)]),      # one to four groups of eight rows in the only block of a head
+    (3, [(400, 33), (400, 40), (390, 41), (257, 56), (400, 57), (33, 33)]),              # the same in its second block, heads packed across blocks
+    (7, [(300, 50), (280, 63)]),                                                         # 11 packed blocks, 14 padded
+    (8, [(420, 90), (300, 89)]),                                                         # 23 packed blocks in two launches, 24 padded
+    (1, [(200, 100), (101, 97)]),
+])
+def test_window_rows_that_do_not_fill_their_blocks(Hq, lens):
+    """bf16, d = 128: sweep 1 packs the heads' rows, sweep 2 leaves out groups of eight rows that are all padding."""
+    _check_sweeps("bf16", 128, Hq, 1, lens)
+
+
 @pytest.mark.parametrize("dtype,d,Hq,Hkv,lens", [
     ("bf16", 64, 4, 1, [(31, 1), (33, 33)]),
     ("bf16", 64, 14, 2, [(600, 50)]),
