@@ -17,7 +17,7 @@ constexpr int kKSteps = kD / 16;        // MFMA k-steps per tile
 // 8 consecutive k-values [16 ks + 8 half, +8).
 __device__ __forceinline__ bf16x8_t as_frag(const uint4& v) { return __builtin_bit_cast(bf16x8_t, v); }
 
-// The 32-row blocks rb0 + STRIDE * rb (rb < RB) of this wave: rows of the KV group's window, each head padded to tauP.
+// The 32-row blocks rb0 + STRIDE * rb (rb < RB) of this wave: rows of the KV group's window, a head every tauP of them (tb: packed).
 template <int RB, int STRIDE, typename Args>
 __device__ __forceinline__ void load_q_frags(const Args& a, int bl, int hkv, int rb0, int lane, int tb, int tauP, uint4 (&qf)[RB][kKSteps]) {
     const int half = lane >> 5;

@@ -47,6 +47,7 @@ struct SweepArgs {
     float log2p, default_scale;
     int L, Hq, Hkv, g, m, tau, keys_per_split, nsplit;
     int head_shift;          // shared blocks: log2 of the rows a head is padded to
+    int packed;              // sweep 1: the heads' rows follow each other, a block may hold rows of several heads
     int rb0;                 // first 32-row block of this launch
     int accumulate;          // sweep 2: add to scores instead of overwriting (row groups after the first)
 };
@@ -93,7 +94,7 @@ __device__ __forceinline__ Where locate(const SweepArgs& a, int group, int split
     const ReqLen rl = request_len(a.lens, w.bl / a.L, a.m, a.tau);
     w.mb = rl.m; w.tb = rl.tau;                             // this request's prompt and window length
     w.nb = (w.tb + 31) >> 5;
-    w.nrb = F::SHARED ? ((a.g << a.head_shift) + 31) >> 5 : min(a.g * w.nb - a.rb0, F::NRB);
+    w.nrb = F::SHARED ? ((a.g << a.head_shift) + 31) >> 5 : a.packed ? (a.g * w.tb + 31) >> 5 : min(a.g * w.nb - a.rb0, F::NRB);
     w.k_begin = split * a.keys_per_split;
     w.k_end = min(w.mb, w.k_begin + a.keys_per_split);
     w.nt = w.k_end > w.k_begin ? (w.k_end - w.k_begin + 31) >> 5 : 0;
@@ -126,6 +127,12 @@ __device__ __forceinline__ Row window_row(const SweepArgs& a, const Where& w, in
         o.hl = r >> a.head_shift;
         o.iw = r - (o.hl << a.head_shift);
         o.real = o.hl < a.g && o.iw < w.tb;
+        return o;
+    }
+    if (a.packed) {
+        o.hl = r / w.tb;
+        o.iw = r - o.hl * w.tb;
+        o.real = o.hl < a.g;
         return o;
     }
     const int rb = a.rb0 + (r >> 5);
@@ -235,7 +242,8 @@ __global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void rowstats_wave_k
                 if (masked) {                               // last key this lane's row may see (causal mask of Alg. 1)
                     int rbg = a.rb0 + rb;
                     asm volatile("" : "+s"(rbg));           // computed here: hoisted, the limits of all row blocks would take registers
-                    const int jlim = min(w.mb - w.tb + lane_row<F>(a, rbg % w.nb, lane), w.mb - 1) - key0;
+                    const int iw = a.packed ? (rbg * 32 + (lane & 31)) % w.tb : lane_row<F>(a, rbg % w.nb, lane);
+                    const int jlim = min(w.mb - w.tb + iw, w.mb - 1) - key0;
 #pragma unroll
                     for (int i = 0; i < 16; ++i) v[i] = acc_row(i, lane) <= jlim ? v[i] : -INFINITY;
                 }
@@ -518,7 +526,7 @@ SweepArgs make_args(const ScoreArgs& a, const Plan& p) {
     m.L = s.L; m.Hq = s.Hq; m.Hkv = s.Hkv; m.g = s.Hq / s.Hkv; m.m = s.m; m.tau = s.tau;
     m.keys_per_split = p.keys_per_split; m.nsplit = p.nsplit;
     m.head_shift = p.head_shift;
-    m.rb0 = 0; m.accumulate = 0;
+    m.packed = 0; m.rb0 = 0; m.accumulate = 0;
     return m;
 }
 
@@ -537,6 +545,11 @@ hipError_t launch_sweep(SweepArgs m, const Plan& p, const vlc_shape& s, hipStrea
     m.keys_per_split = SWEEP1 ? p.keys_per_split : p.keys_per_split2;
     const dim3 grid(s.B * s.L * s.Hkv, s.m / m.keys_per_split + (s.m % m.keys_per_split != 0));
     const int step = max_row_blocks(s);
+    // Sweep 1 of a window that one launch holds: a lane owns a row whatever block it is in, so the heads' rows may follow each
+    // other (with the form, and with it each row's order of additions, chosen as for blocks of one head).  192 KV groups of 4096
+    // keys, 4 heads of 50 rows of 64 in bf16, 7 blocks instead of 8: a
+    // whole compression 152.1 -> 146.5 us.
+    m.packed = SWEEP1 && p.head_shift < 0 && p.nrb <= step;
     for (int rb0 = 0; rb0 < p.nrb; rb0 += step) {
         const int nrb = p.nrb - rb0 < step ? p.nrb - rb0 : step;
         m.rb0 = rb0;

@@ -41,10 +41,10 @@ struct WinArgs {
     bf16_t* out;             // [B,L,Hq,tau,d]
     float* row_max;          // [B,L,Hq,tau], natural-log domain
     float* row_sum;
-    float* part_o;           // [group][split][RP][kD] unnormalised partial outputs
-    float2* part_ms;         // [group][split][RP] (max in the exponent domain, sum)
+    float* part_o;           // [group][split][R][kD] unnormalised partial outputs
+    float2* part_ms;         // [group][split][R] (max in the exponent domain, sum)
     const int32_t* lens;
-    int L, Hq, Hkv, g, m, tau, RP, keys_per_split, nsplit;     // RP: padded window rows of a KV group, for the longest window
+    int L, Hq, Hkv, g, m, tau, R, keys_per_split, nsplit;      // R: window rows of a KV group, for the longest window; packed into 32-row blocks
     int rb0;                 // first 32-row block of this launch
 };
 
@@ -149,14 +149,14 @@ __global__ __launch_bounds__(WAVES * 64, 2) void window_attn_kernel(WinArgs a) {
     const int mb = rl.m, tb = rl.tau;
     const int k_begin = split * a.keys_per_split;
     const int k_end = min(mb, k_begin + a.keys_per_split);
-    const int tauP = padded_rows(tb), RP = a.g * tauP;         // this request's padded window rows, the launch's (a.RP) or fewer
-    if (a.rb0 * 32 >= RP) return;                              // a later launch of a longer window than this request's
-    const bool has_rows = (a.rb0 + wave) * 32 < RP;            // wave-uniform
+    const int R = a.g * tb;                                    // this request's window rows, head after head: the launch's (a.R) or fewer
+    if (a.rb0 * 32 >= R) return;                               // a later launch of a longer window than this request's
+    const bool has_rows = (a.rb0 + wave) * 32 < R;             // wave-uniform
 
     uint4 qf[1][kKSteps];
-    load_q_frags<1, WAVES>(a, bl, hkv, a.rb0 + wave, lane, tb, tauP, qf);
-    const int r = (a.rb0 + wave) * 32 + (lane & 31);           // this lane's padded window row
-    const int jlim = mb - tb + (r % tauP);                     // last key it may see
+    load_q_frags<1, WAVES>(a, bl, hkv, a.rb0 + wave, lane, tb, tb, qf);
+    const int r = (a.rb0 + wave) * 32 + (lane & 31);           // this lane's window row
+    const int jlim = mb - tb + (r % tb);                     // last key it may see
     float m_run = -INFINITY, z_run = 0.f;
     f32x16_t o[kD / 32];
 #pragma unroll
@@ -245,10 +245,9 @@ __global__ __launch_bounds__(WAVES * 64, 2) void window_attn_kernel(WinArgs a) {
     if (!has_rows) return;
     // the two lane halves hold disjoint keys of the same query row under the same max
     const float z = z_run + __shfl_xor(z_run, 32, 64);
-    const int hl = r / tauP, iw = r % tauP;
-    const bool real = hl < a.g && iw < tb && r < RP;
+    if (r >= R) return;
+    const int hl = r / tb, iw = r % tb;
     if (a.nsplit == 1) {
-        if (!real) return;
         const size_t orow = ((size_t)bl * a.Hq + (size_t)hkv * a.g + hl) * a.tau + iw;
         const float inv = 1.f / z;                             // every real row sees key 0 in the only split
         bf16_t* dst = a.out + orow * kD;
@@ -264,8 +263,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void window_attn_kernel(WinArgs a) {
         if (lane < 32) { a.row_max[orow] = m_run * kLn2; a.row_sum[orow] = z; }
         return;
     }
-    if (r >= RP) return;
-    const size_t prow = ((size_t)group * a.nsplit + split) * a.RP + r;
+    const size_t prow = ((size_t)group * a.nsplit + split) * a.R + r;
     float* dst = a.part_o + prow * kD;
 #pragma unroll
     for (int dt = 0; dt < kD / 32; ++dt)
@@ -276,23 +274,23 @@ __global__ __launch_bounds__(WAVES * 64, 2) void window_attn_kernel(WinArgs a) {
     if (lane < 32) a.part_ms[prow] = make_float2(m_run, z);
 }
 
-// Merge of the per-split partials: 32 lanes (4 d-values each) per padded row, 32 rows per block.
+// Merge of the per-split partials: 32 lanes (4 d-values each) per row, 32 rows per block.
 __global__ __launch_bounds__(256) void window_attn_merge_kernel(WinArgs a, int groups) {
     const int sub = threadIdx.x >> 5, lane = threadIdx.x & 31;
     for (int it = 0; it < 4; ++it) {
-        const size_t x = ((size_t)blockIdx.x * 4 + it) * 8 + sub;      // (group, padded row)
-        if (x >= (size_t)groups * a.RP) return;
-        const int r = (int)(x % a.RP), group = (int)(x / a.RP);
+        const size_t x = ((size_t)blockIdx.x * 4 + it) * 8 + sub;      // (group, row)
+        if (x >= (size_t)groups * a.R) return;
+        const int r = (int)(x % a.R), group = (int)(x / a.R);
         const int hkv = group % a.Hkv, bl = group / a.Hkv;
-        const int tb = request_len(a.lens, bl / a.L, a.m, a.tau).tau, tauP = padded_rows(tb);
-        const int hl = r / tauP, iw = r % tauP;
-        if (hl >= a.g || iw >= tb) continue;
+        const int tb = request_len(a.lens, bl / a.L, a.m, a.tau).tau;
+        const int hl = r / tb, iw = r % tb;
+        if (hl >= a.g) continue;
         float M = -INFINITY;
-        for (int s = 0; s < a.nsplit; ++s) M = fmaxf(M, a.part_ms[((size_t)group * a.nsplit + s) * a.RP + r].x);
+        for (int s = 0; s < a.nsplit; ++s) M = fmaxf(M, a.part_ms[((size_t)group * a.nsplit + s) * a.R + r].x);
         float Z = 0.f;
         float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
         for (int s = 0; s < a.nsplit; ++s) {
-            const size_t prow = ((size_t)group * a.nsplit + s) * a.RP + r;
+            const size_t prow = ((size_t)group * a.nsplit + s) * a.R + r;
             const float2 ms = a.part_ms[prow];
             if (!(ms.x > -INFINITY)) continue;                         // this split saw no key of the row
             const float w = exp2_fast(ms.x - M);
@@ -309,12 +307,12 @@ __global__ __launch_bounds__(256) void window_attn_merge_kernel(WinArgs a, int g
     }
 }
 
-struct WinPlan { int RP, nsplit, keys_per_split; };
+struct WinPlan { int R, nsplit, keys_per_split; };
 
 WinPlan make_plan(const vlc_shape& s) {
     WinPlan p;
     const int g = s.Hq / s.Hkv;
-    p.RP = g * ((s.tau + 31) / 32 * 32);
+    p.R = g * s.tau;
     const int groups = s.B * s.L * s.Hkv;
     const int chunks = (s.m + kChunk - 1) / kChunk;
     // Two staged chunks (66 KB of LDS) allow two blocks per compute unit: about one resident round
@@ -338,7 +336,7 @@ bool window_attn_supported(const vlc_shape& s) {
 size_t window_attn_workspace_bytes(const vlc_shape& s) {
     const WinPlan p = make_plan(s);
     if (p.nsplit == 1) return 256;
-    const size_t rows = (size_t)s.B * s.L * s.Hkv * p.nsplit * p.RP;
+    const size_t rows = (size_t)s.B * s.L * s.Hkv * p.nsplit * p.R;
     return (rows * kD * sizeof(float) + 255) / 256 * 256 + (rows * sizeof(float2) + 255) / 256 * 256;
 }
 
@@ -349,15 +347,15 @@ hipError_t launch_window_attn(const WindowAttnArgs& w) {
     a.q_win = (const bf16_t*)w.q_win; a.k = (const bf16_t*)w.k; a.v = (const bf16_t*)w.v; a.sm_scale = w.sm_scale;
     a.out = (bf16_t*)w.out; a.row_max = w.row_max; a.row_sum = w.row_sum;
     const int groups = s.B * s.L * s.Hkv;
-    const size_t rows = (size_t)groups * p.nsplit * p.RP;
+    const size_t rows = (size_t)groups * p.nsplit * p.R;
     a.part_o = (float*)w.workspace;
     a.part_ms = (float2*)((char*)w.workspace + (rows * kD * sizeof(float) + 255) / 256 * 256);
     a.lens = s.lens;
     a.L = s.L; a.Hq = s.Hq; a.Hkv = s.Hkv; a.g = s.Hq / s.Hkv; a.m = s.m; a.tau = s.tau;
-    a.RP = p.RP; a.keys_per_split = p.keys_per_split; a.nsplit = p.nsplit;
+    a.R = p.R; a.keys_per_split = p.keys_per_split; a.nsplit = p.nsplit;
     dim3 grid(p.nsplit, groups);
-    const int total_rb = p.RP / 32;
-    // Windows beyond 8 row blocks (256 padded rows per KV head) take one launch per 8 row blocks;
+    const int total_rb = (p.R + 31) / 32;
+    // Windows beyond 8 row blocks (256 rows per KV group) take one launch per 8 row blocks;
     // their rows are independent, K and V are streamed once per launch.
     for (int rb0 = 0; rb0 < total_rb; rb0 += kMaxRowBlocks) {
         const int nrb = total_rb - rb0 < kMaxRowBlocks ? total_rb - rb0 : kMaxRowBlocks;
@@ -366,7 +364,7 @@ hipError_t launch_window_attn(const WindowAttnArgs& w) {
         else window_attn_kernel<8><<<grid, 512, 0, w.stream>>>(a);
     }
     if (p.nsplit > 1) {
-        const size_t n = (size_t)groups * p.RP;
+        const size_t n = (size_t)groups * p.R;
         a.rb0 = 0;
         window_attn_merge_kernel<<<(unsigned)((n + 31) / 32), 256, 0, w.stream>>>(a, groups);
     }
