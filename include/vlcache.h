@@ -205,6 +205,14 @@ vlc_status vlc_allocate(const vlc_shape* shape, const uint64_t* nnz,
                         int32_t* k_out, float* beta_out, vlc_stream stream);
 
 /*
+ * vlc_sparsity_allocate -- vlc_sparsity from given counts (gamma may be NULL) and vlc_allocate in one launch: the same
+ * results as the two calls.
+ */
+vlc_status vlc_sparsity_allocate(const vlc_shape* shape, const uint64_t* nnz, float* gamma,
+                                 int64_t alpha_num, int64_t alpha_den,
+                                 int32_t* k_out, float* beta_out, vlc_stream stream);
+
+/*
  * The compressed cache.  The caller owns one device arena; the library lays out inside it
  * the ragged per-layer K/V slabs (layer l of request b holds k[b][l] + T_max slots per KV
  * head), the kept indices, per-layer offsets, and the split-KV scratch of decode.

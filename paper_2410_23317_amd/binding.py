@@ -76,6 +76,8 @@ def _load() -> C.CDLL:
     lib.vlc_score_from_stats.argtypes = [shp, vp, vp, vp, f32, vp, vp, vp, vp, vp]
     lib.vlc_allocate.restype = C.c_int
     lib.vlc_allocate.argtypes = [shp, vp, i64, i64, vp, vp, vp]
+    lib.vlc_sparsity_allocate.restype = C.c_int
+    lib.vlc_sparsity_allocate.argtypes = [shp, vp, vp, i64, i64, vp, vp, vp]
     lib.vlc_cache_bytes.restype = sz
     lib.vlc_cache_bytes.argtypes = [shp, i32, i64]
     lib.vlc_cache_create.restype = C.c_int
@@ -197,6 +199,11 @@ def vlc_score_from_stats(shape, q_win, k, sm_scale, p, row_max, row_sum, scores,
 def vlc_allocate(shape, nnz, alpha_num, alpha_den, k_out, beta_out) -> None:
     _check(lib.vlc_allocate(C.byref(shape), _ptr(nnz), int(alpha_num), int(alpha_den), _ptr(k_out),
                             _ptr(beta_out), _stream()))
+
+
+def vlc_sparsity_allocate(shape, nnz, gamma, alpha_num, alpha_den, k_out, beta_out) -> None:
+    _check(lib.vlc_sparsity_allocate(C.byref(shape), _ptr(nnz), _ptr(gamma), int(alpha_num), int(alpha_den), _ptr(k_out),
+                                     _ptr(beta_out), _stream()))
 
 
 def vlc_cache_bytes(shape, T_max, sum_k_max) -> int:

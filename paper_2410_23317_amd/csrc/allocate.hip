@@ -21,9 +21,10 @@ __device__ __forceinline__ uint64_t block_sum(uint64_t v, uint64_t* red) {
 // One block per request.  A chain of a few loads and two block sums is all there is, so latency is what it costs: eight lanes
 // share a layer's counts (all in flight together), then thread t owns layers t, t + 256, ...  (L <= kMaxLayers).
 // Profiled, 32 layers of 32 heads 8.3 -> 5.4 us, 60 of 56 heads 11.4 -> 9.4 (a thread per layer, eight barriers per sum before).
+// gamma, if asked for, is written from the counts as they come by: a launch of its own for it costs about 3 us.
 __global__ __launch_bounds__(256) void allocate_kernel(const uint64_t* __restrict__ nnz, int L, int Hq, int m_max, int tau,
                                                        uint64_t alpha_num, uint64_t alpha_den,
-                                                       const int32_t* __restrict__ lens, int32_t* __restrict__ k_out,
+                                                       const int32_t* __restrict__ lens, float* __restrict__ gamma, int32_t* __restrict__ k_out,
                                                        float* __restrict__ beta_out) {
     __shared__ uint64_t n_l[kMaxLayers];
     __shared__ uint64_t rem[kMaxLayers];
@@ -31,14 +32,20 @@ __global__ __launch_bounds__(256) void allocate_kernel(const uint64_t* __restric
     __shared__ uint64_t red[4];
     const int b = blockIdx.x;
     const int t = threadIdx.x;
-    const int m = request_len(lens, b, m_max, tau).m;                       // this request's prompt length
+    const ReqLen rl = request_len(lens, b, m_max, tau);
+    const int m = rl.m;                                                     // this request's prompt length
     const uint64_t B_tot = alpha_num * (uint64_t)L * (uint64_t)m / alpha_den;   // floor(alpha L m) tokens for the request
     uint64_t local = 0;
     for (int l0 = 0; l0 < L; l0 += 32) {                    // block-uniform
         const int l = l0 + (t >> 3);
         uint64_t s = 0;
         if (l < L)
-            for (int h = t & 7; h < Hq; h += 8) s += nnz[((size_t)b * L + l) * Hq + h];
+            for (int h = t & 7; h < Hq; h += 8) {
+                const size_t x = ((size_t)b * L + l) * Hq + h;
+                const uint64_t n = nnz[x];
+                s += n;
+                if (gamma) gamma[x] = gamma_of(n, rl);
+            }
         for (int o = 4; o >= 1; o >>= 1) s += (uint64_t)__shfl_xor((unsigned long long)s, o, 64);
         if (l < L && (t & 7) == 0) { n_l[l] = s; local += s; }
     }
@@ -54,11 +61,14 @@ __global__ __launch_bounds__(256) void allocate_kernel(const uint64_t* __restric
     }
     const uint64_t extra = B_tot - block_sum(local, red);   // < L tokens left after the floor quotas
     const int lo = max(1, (m + 99) / 100);
-    for (int l = t; l < L; l += blockDim.x) {
+    for (int l0 = 0; l0 < L; l0 += 32) {                    // block-uniform: again eight lanes per layer
+        const int l = min(l0 + (t >> 3), L - 1);
         // rank of layer l by (remainder descending, layer ascending)
-        uint64_t rank = 0;
+        uint32_t rank = 0;
         const uint64_t r = rem[l];
-        for (int x = 0; x < L; ++x) rank += (rem[x] > r || (rem[x] == r && x < l)) ? 1u : 0u;
+        for (int x = t & 7; x < L; x += 8) rank += (rem[x] > r || (rem[x] == r && x < l)) ? 1u : 0u;
+        for (int o = 4; o >= 1; o >>= 1) rank += (uint32_t)__shfl_xor((int)rank, o, 64);
+        if (l0 + (t >> 3) >= L || (t & 7)) continue;
         uint64_t q = quo[l] + (rank < extra ? 1u : 0u);
         if (q < (uint64_t)lo) q = lo;
         if (q > (uint64_t)m) q = m;
@@ -69,9 +79,9 @@ __global__ __launch_bounds__(256) void allocate_kernel(const uint64_t* __restric
 
 }  // namespace
 
-hipError_t launch_allocate(const vlc_shape& s, const uint64_t* nnz, int64_t alpha_num, int64_t alpha_den, int32_t* k_out,
-                           float* beta_out, hipStream_t st) {
-    allocate_kernel<<<s.B, 256, 0, st>>>(nnz, s.L, s.Hq, s.m, s.tau, (uint64_t)alpha_num, (uint64_t)alpha_den, s.lens,
+hipError_t launch_allocate(const vlc_shape& s, const uint64_t* nnz, int64_t alpha_num, int64_t alpha_den, float* gamma,
+                           int32_t* k_out, float* beta_out, hipStream_t st) {
+    allocate_kernel<<<s.B, 256, 0, st>>>(nnz, s.L, s.Hq, s.m, s.tau, (uint64_t)alpha_num, (uint64_t)alpha_den, s.lens, gamma,
                                          k_out, beta_out);
     return hipGetLastError();
 }

@@ -273,21 +273,29 @@ vlc_status vlc_score_from_stats(const vlc_shape* shape, const void* q_win, const
     return VLC_OK;
 }
 
-vlc_status vlc_allocate(const vlc_shape* shape, const uint64_t* nnz, int64_t alpha_num, int64_t alpha_den,
-                        int32_t* k_out, float* beta_out, vlc_stream stream) {
+static vlc_status allocate_common(const char* who, const vlc_shape* shape, const uint64_t* nnz, int64_t alpha_num, int64_t alpha_den,
+                                  float* gamma, int32_t* k_out, float* beta_out, vlc_stream stream) {
     if (vlc_status st = check_shape(shape)) return st;
-    if (!nnz || !k_out) return fail(VLC_ERR_INVALID_ARG, "vlc_allocate: nnz and k_out must not be NULL");
+    if (!nnz || !k_out) return fail(VLC_ERR_INVALID_ARG, "%s: nnz and k_out must not be NULL", who);
     if (alpha_num < 1 || alpha_den < 1 || alpha_num > alpha_den)
-        return fail(VLC_ERR_INVALID_ARG, "vlc_allocate: alpha = %lld/%lld is outside (0, 1]", (long long)alpha_num, (long long)alpha_den);
+        return fail(VLC_ERR_INVALID_ARG, "%s: alpha = %lld/%lld is outside (0, 1]", who, (long long)alpha_num, (long long)alpha_den);
     const double lm = (double)shape->L * shape->m;
-    if ((double)alpha_num * lm > 9.0e18) return fail(VLC_ERR_INVALID_ARG, "vlc_allocate: alpha_num * L * m overflows");
+    if ((double)alpha_num * lm > 9.0e18) return fail(VLC_ERR_INVALID_ARG, "%s: alpha_num * L * m overflows", who);
     const int64_t B_tot = (alpha_num * (int64_t)shape->L * shape->m) / alpha_den;
     // n_l * B_tot must fit 64 bits: n_l <= Hq * region size
     if ((double)shape->Hq * region_size(*shape) * (double)B_tot > 1.8e19)
-        return fail(VLC_ERR_SHAPE, "vlc_allocate: Hq * region * budget exceeds 64-bit arithmetic");
-    hipError_t e = vlc::launch_allocate(*shape, nnz, alpha_num, alpha_den, k_out, beta_out, (hipStream_t)stream);
-    if (e != hipSuccess) return hip_fail(e, "vlc_allocate");
+        return fail(VLC_ERR_SHAPE, "%s: Hq * region * budget exceeds 64-bit arithmetic", who);
+    hipError_t e = vlc::launch_allocate(*shape, nnz, alpha_num, alpha_den, gamma, k_out, beta_out, (hipStream_t)stream);
+    if (e != hipSuccess) return hip_fail(e, who);
     return VLC_OK;
+}
+vlc_status vlc_allocate(const vlc_shape* shape, const uint64_t* nnz, int64_t alpha_num, int64_t alpha_den,
+                        int32_t* k_out, float* beta_out, vlc_stream stream) {
+    return allocate_common("vlc_allocate", shape, nnz, alpha_num, alpha_den, nullptr, k_out, beta_out, stream);
+}
+vlc_status vlc_sparsity_allocate(const vlc_shape* shape, const uint64_t* nnz, float* gamma, int64_t alpha_num, int64_t alpha_den,
+                                 int32_t* k_out, float* beta_out, vlc_stream stream) {
+    return allocate_common("vlc_sparsity_allocate", shape, nnz, alpha_num, alpha_den, gamma, k_out, beta_out, stream);
 }
 
 struct ArenaPlan {

@@ -186,6 +186,12 @@ __device__ __forceinline__ ReqLen request_len(const int32_t* __restrict__ lens, 
     return r;
 }
 
+// Sparsity of a head from its count of entries that pass the filter (Eq. 2 over the causal region of Alg. 1).
+__device__ __forceinline__ float gamma_of(uint64_t nnz, const ReqLen& rl) {
+    const double region = (double)rl.tau * (rl.m - rl.tau) + (double)rl.tau * (rl.tau + 1) / 2.0;
+    return (float)(1.0 - (double)nnz / region);
+}
+
 // Device-visible sticky error: first writer wins.
 __device__ __forceinline__ void set_sticky(int32_t* status, int code, int b, int l, int detail) {
     if (atomicCAS(status, 0, code) == 0) { status[1] = b; status[2] = l; status[3] = detail; }

@@ -140,7 +140,8 @@ hipError_t launch_window_attn(const WindowAttnArgs& a);
 hipError_t launch_window_attn_simple(const WindowAttnArgs& a);      // any dtype and d (window_attn_simple.hip); no workspace
 
 // ---- allocation ----
-hipError_t launch_allocate(const vlc_shape& s, const uint64_t* nnz, int64_t alpha_num, int64_t alpha_den,
+// gamma: null, or written beside the budgets
+hipError_t launch_allocate(const vlc_shape& s, const uint64_t* nnz, int64_t alpha_num, int64_t alpha_den, float* gamma,
                            int32_t* k_out, float* beta_out, hipStream_t st);
 
 // ---- eviction ----

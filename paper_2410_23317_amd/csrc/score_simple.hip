@@ -181,9 +181,7 @@ __global__ void gamma_kernel(const uint64_t* __restrict__ nnz, float* __restrict
                              const int32_t* __restrict__ lens, int LHq, int m, int tau) {
     const size_t x = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (x >= n) return;
-    const ReqLen rl = request_len(lens, (int)(x / LHq), m, tau);
-    const double region = (double)rl.tau * (rl.m - rl.tau) + (double)rl.tau * (rl.tau + 1) / 2.0;   // entries of the causal region, Alg. 1
-    gamma[x] = (float)(1.0 - (double)nnz[x] / region);
+    gamma[x] = gamma_of(nnz[x], request_len(lens, (int)(x / LHq), m, tau));
 }
 
 template <typename T, int D>

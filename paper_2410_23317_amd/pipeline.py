@@ -1,6 +1,7 @@
 """Sequencing of the hot path over the C-ABI calls: buffers and call order only, no arithmetic.
 
-After prefill:  vlc_score -> vlc_sparsity (finalise) -> vlc_allocate -> vlc_topk_compact.
+After prefill:  vlc_score -> vlc_sparsity (finalise) -> vlc_allocate -> vlc_topk_compact; compress() takes the two
+in the middle in one launch (vlc_sparsity_allocate).
 Fused route for the scores: vlc_window_attn (attention of the window rows + row statistics) ->
 vlc_score_from_stats (column sweep only).
 Every decode step: vlc_decode_attn over a layer range of the compressed cache.
@@ -84,8 +85,7 @@ class VLCachePath:
 
     def compress(self, q_win, k, v, sm_scale) -> None:
         self.score(q_win, k, sm_scale)
-        self.sparsity()
-        self.allocate()
+        V.vlc_sparsity_allocate(self.shape, self.nnz, self.gamma, self.alpha[0], self.alpha[1], self.k, self.beta)
         self.topk_compact(k, v)
 
     # -- every decode step -----------------------------------------------------------------

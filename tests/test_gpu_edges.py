@@ -48,6 +48,26 @@ def test_allocate_bit_exact_on_random_counts_including_clips():
     assert k.cpu().numpy().tolist() == [O.allocate(np.zeros((4, 2), dtype=np.int64), 1000, 1, 10)[0].tolist()]
 
 
+@pytest.mark.parametrize("B,L,Hq,ragged", [(1, 1, 1, False), (3, 33, 7, True), (2, 32, 32, False), (1, 60, 56, True), (2, 257, 9, False)])
+def test_sparsity_and_allocation_in_one_launch_equal_the_two_calls(B, L, Hq, ragged):
+    """Whole numbers and bits: gamma, budgets and beta of vlc_sparsity_allocate against vlc_sparsity and vlc_allocate, with
+    layers beyond the 32 that a block takes at a time, and counts that tie."""
+    V = _V()
+    m, tau = 5000, 40
+    r = np.random.default_rng(L)
+    lens = torch.tensor([[m - 7 * b, tau - b] for b in range(B)], dtype=torch.int32, device="cuda") if ragged else None
+    shape = V.make_shape(B, L, Hq, Hq, 128, m, tau, "bf16", lens=lens)
+    nnz = torch.from_numpy(r.integers(tau, 90 * tau, size=(B, L, Hq)) // 50 * 50).cuda()
+    out = [[torch.full((B, L, Hq), -7.0, device="cuda"), torch.full((B, L), -7, dtype=torch.int32, device="cuda"), torch.full((B, L), -7.0, device="cuda")] for _ in range(3)]
+    V.vlc_sparsity(shape, None, None, None, None, 0.01, nnz, out[0][0], None)
+    V.vlc_allocate(shape, nnz, 1, 10, out[0][1], out[0][2])
+    V.vlc_sparsity_allocate(shape, nnz, out[1][0], 1, 10, out[1][1], out[1][2])
+    V.vlc_sparsity_allocate(shape, nnz, None, 1, 10, out[2][1], None)
+    for x, y in zip(out[0], out[1]):
+        assert torch.equal(x, y)
+    assert torch.equal(out[0][1], out[2][1]) and bool((out[2][0] == -7).all()) and bool((out[2][2] == -7).all())
+
+
 def _topk_case(V, scores, kk, n_recent, m, Hkv=2, L=1, B=1, T_max=2, d=64, options=None):
     """Run vlc_topk_compact alone on given scores [B,L,Hkv,m] and budgets [B,L]; returns (path-like cache, idx_out, K, Vv)."""
     from paper_2410_23317_amd.pipeline import cache_layer_view
