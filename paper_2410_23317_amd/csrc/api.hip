@@ -301,7 +301,7 @@ vlc_status vlc_sparsity_allocate(const vlc_shape* shape, const uint64_t* nnz, fl
 struct ArenaPlan {
     vlc_cache_layout lay;
     vlc_cache_options opt;      // resolved
-    size_t items_off[vlc::kNumLists], layer_start_off[vlc::kNumLists], row_first_off[vlc::kNumLists], partials_off, counters_off, readers_off, lens_off;
+    size_t items_off[vlc::kNumLists], layer_start_off[vlc::kNumLists], row_first_off[vlc::kNumLists], heads_off, partials_off, counters_off, readers_off, lens_off;
     int64_t cap[vlc::kNumLists];
 };
 
@@ -422,6 +422,7 @@ static vlc_status cache_layout(const vlc_shape* s, int32_t T_max, int64_t sum_k_
         plan->layer_start_off[i] = off;  off = align_up(off + (size_t)(s->L + 2) * sizeof(int32_t), 256);
         plan->row_first_off[i] = off;    off = align_up(off + BL * s->Hkv * sizeof(int32_t), 256);
     }
+    plan->heads_off = off;        off = align_up(off + (size_t)s->L * vlc::kHeadUnits * sizeof(vlc::WorkItem), 256);
     plan->partials_off = off;     off = align_up(off + (size_t)partials * vlc::partial_floats(g, s->d) * sizeof(float), 256);
     plan->counters_off = off;     off = align_up(off + BL * s->Hkv * sizeof(int32_t), 256);
     plan->readers_off = off;      off = align_up(off + (size_t)(s->L + 1) * vlc::kReaderStride * sizeof(int32_t), 256);
@@ -496,6 +497,7 @@ static vlc_status cache_create_common(const char* who, const vlc_shape* shape, i
         c->layout.list_by_size[i] = c->dev.list[i].by_size;
     }
     c->layout.list_reserved = 0;
+    c->dev.heads = (vlc::WorkItem*)(c->arena + plan.heads_off);
     c->dev.partials = (float*)(c->arena + plan.partials_off);
     c->dev.counters = (int32_t*)(c->arena + plan.counters_off);
     c->dev.readers = (int32_t*)(c->arena + plan.readers_off);

@@ -37,6 +37,7 @@ struct DecodeParams {
     const void* v_new;
     void* out;
     const float* sm_scale;   // [L], or null: default_scale for every layer
+    const WorkItem* heads;   // launches over one layer: copies of its first records (of kHeadUnits), else null
     WorkList wl;             // the work list this launch walks
     // of the cache, as in CacheDev
     const int32_t* kept;
@@ -579,6 +580,36 @@ __global__ __launch_bounds__(256, (IsBf16<T>::value ? (D == 64 && !Q8 ? 4 : 3) :
     const int begin = P.layer_begin ? layer_start[P.layer_begin] : 0;
     const int end = layer_start[P.layer_begin + P.n_layers];
     const int appended = P.appended[P.layer_begin];
+    // ---- the unit of this block.  One block-unit per block: the hardware dispatcher balances the ragged units.  The grid is
+    // a host-side upper bound on the units of the layer range, surplus blocks leave at once.
+    // The record is read word by word.  A layer's first records (launches over one layer) are requested together with the
+    // values above, the others, whose place depends on them, a round trip later.
+    static_assert(offsetof(WorkItem, row_abs) == 0 && offsetof(WorkItem, key0) == 4 && offsetof(WorkItem, kept) == 8 &&
+                  offsetof(WorkItem, unit) == 12 && offsetof(WorkItem, kbase) == 16 && offsetof(WorkItem, idx_base) == 24 &&
+                  offsetof(WorkItem, b) == 32 && offsetof(WorkItem, l) == 36 &&
+                  offsetof(WorkItem, ucap) == 44 && offsetof(WorkItem, hkv) == 48 && offsetof(WorkItem, layer_units) == 52,
+                  "the record is read as 16 words");
+    int rec[14];
+    auto read = [&](const WorkItem* item) {
+#pragma unroll
+        for (int i = 0; i < 14; ++i) rec[i] = ((IndexPtr)item)[i];
+    };
+    int w = blockIdx.x;
+    bool listed = true;
+    if (P.heads && w < kHeadUnits) {
+        read(P.heads + w);
+        w += begin;
+    } else {
+        const bool odd = ((appended + (P.append_mode && appended < P.T_max ? 1 : 0)) & 1) != 0;
+        if (P.wl.by_size && P.zigzag > 2 && odd) {  // size-class order, odd step: the whole units are walked backwards, so that
+            const int nf = min(layer_start[P.L + 1], (int)gridDim.x);   // what the memory-side cache kept of the last step comes first
+            const int nf8 = nf & ~7;            // whole groups of 8 change places, so a unit stays on its XCD (and its L2)
+            if (w < nf8) w = nf8 - 8 - (w & ~7) + (w & 7);
+        }
+        w += begin;
+        listed = w < P.wl.cap;
+        if (listed) read(P.wl.items + w);
+    }
     int mode = P.append_mode;
     // more steps than slots were reserved (only a replayed graph gets here): attend over what the cache holds,
     // append nothing, count nothing, and report it (after the block's first unit: a store in front of the unit
@@ -587,8 +618,6 @@ __global__ __launch_bounds__(256, (IsBf16<T>::value ? (D == 64 && !Q8 ? 4 : 3) :
     if (over) mode = 0;
     const bool appending = mode == 1;
     const int step = appended + (mode ? 1 : 0); // appends the cache holds once this launch is done
-    // One block-unit per block: the hardware dispatcher balances the ragged units.  The grid is a host-side upper bound on
-    // the units of the layer range, surplus blocks leave at once.
     auto process_unit = [&]() {
         // The block that holds the last ticket of its layer, and then of the launch, publishes the new count.
         auto finish = [&](int ticket, int il, int n_layer) {
@@ -600,21 +629,7 @@ __global__ __launch_bounds__(256, (IsBf16<T>::value ? (D == 64 && !Q8 ? 4 : 3) :
             }
             for (int l = P.layer_begin; l < P.layer_begin + P.n_layers; ++l) store_agent(P.appended + l, step);
         };
-        int w = blockIdx.x;
-        if (P.wl.by_size && P.zigzag > 2 && (step & 1)) {   // size-class order, odd step: the whole units are walked backwards, so that
-            const int nf = min(((IndexPtr)P.wl.layer_start)[P.L + 1], (int)gridDim.x);   // what the memory-side cache kept of the last step comes first
-            const int nf8 = nf & ~7;            // whole groups of 8 change places, so a unit stays on its XCD (and its L2)
-            if (w < nf8) w = nf8 - 8 - (w & ~7) + (w & 7);
-        }
-        w += begin;
-        if (w >= P.wl.cap) return;
-        // the unit record, word by word (requested together with the bounds of the slice)
-        static_assert(offsetof(WorkItem, row_abs) == 0 && offsetof(WorkItem, key0) == 4 && offsetof(WorkItem, kept) == 8 &&
-                      offsetof(WorkItem, unit) == 12 && offsetof(WorkItem, kbase) == 16 && offsetof(WorkItem, idx_base) == 24 &&
-                      offsetof(WorkItem, b) == 32 && offsetof(WorkItem, l) == 36 &&
-                      offsetof(WorkItem, ucap) == 44 && offsetof(WorkItem, hkv) == 48 && offsetof(WorkItem, layer_units) == 52,
-                      "the record is read as 16 words");
-        const IndexPtr rec = (IndexPtr)(P.wl.items + w);
+        if (!listed) return;
         const int row_abs = rec[0], key0 = rec[1], kept = rec[2], unit = rec[3];
         const int64_t kbase = (int64_t)(((uint64_t)(uint32_t)rec[5] << 32) | (uint32_t)rec[4]);
         const int64_t idx_base = (int64_t)(((uint64_t)(uint32_t)rec[7] << 32) | (uint32_t)rec[6]);
@@ -965,6 +980,7 @@ hipError_t launch_decode(const DecodeArgs& a) {
     // (fine units in layer order, so that one layer of the batch still fills the chip).
     const bool all_layers = a.layer_begin == 0 && a.n_layers == s.L;
     P.wl = c.dev.list[all_layers ? 1 : 0];
+    P.heads = !all_layers && a.n_layers == 1 ? c.dev.heads + (size_t)a.layer_begin * kHeadUnits : nullptr;
     P.ub_shift = log2i(P.wl.u_big); P.us_shift = log2i(P.wl.u_small);
     P.B = s.B; P.L = s.L; P.Hq = s.Hq; P.Hkv = s.Hkv; P.m = s.m;
     P.layer_begin = a.layer_begin; P.n_layers = a.n_layers; P.T_max = c.T_max;

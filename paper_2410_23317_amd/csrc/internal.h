@@ -46,6 +46,7 @@ constexpr int kMaxUnitSlots = 2048;     // largest block-unit of a work list (th
 // floats of a unit's partial result: g unnormalised outputs of d values, then g pairs (max, sum); whole 16-byte pieces
 constexpr int partial_floats(int g, int d) { return (g * (d + 2) + 3) & ~3; }
 constexpr int kNumLists = 3;
+constexpr int kHeadUnits = 256;         // units of a layer whose records of list 0 are also kept at a place of their own (CacheDev::heads)
 constexpr int kGatherUnit = 256;        // slots per unit of the gather's list
 
 struct WorkList {
@@ -63,6 +64,7 @@ struct CacheDev {                      // device pointers into the caller's aren
     int32_t* kept;                     // [B*L]
     char* kv;
     int32_t* idx;
+    WorkItem* heads;                  // [L][kHeadUnits] copies of the first records of each layer in list 0: found without the layer index
     WorkList list[kNumLists];         // 0: launches over a layer range, 1: launches over all layers, 2: the gather
     float* partials;                   // [a unit per kMinUnitSlots slots, and one per row][partial_floats(g, d)]
     int32_t* counters;                 // [B*L*Hkv] units of a row that have left their partial result

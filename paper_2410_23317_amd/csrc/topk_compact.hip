@@ -37,7 +37,7 @@ __device__ __forceinline__ RowUnits row_units(int kk, int T_max, int ub, int us)
 
 // Runs in several blocks of NT threads (every thread of a block must enter): the lists are independent of each other
 // once budgets and slab offsets are known, and those are cheap, so every block derives them.  A block builds the lists
-// of the bit mask `lists`, and of those the records of every shares-th group of rows, from its own `share` on (the
+// of the bit mask `lists` (8: the copies of list 0's first records), and of those the records of every shares-th group of rows, from its own `share` on (the
 // prefix sums are repeated in each block, the records are what takes the time: 58,000 of 64 bytes for one prompt
 // of 131,072 tokens, 44 us with one block per list, 12 with sixteen; four prompts of 10,368, 22 -> 15).  The first block of
 // list 0 also writes out budgets and offsets, zeroes the counters and reports errors.
@@ -111,7 +111,9 @@ __device__ void layout_body(const LayoutArgs& a, CacheDev dev, int lists, int sh
     // a run of consecutive entries, the run totals are scanned across the block, then every thread
     // walks its run again from its offset.
     // (one instance of the code per list, so that each list's description stays in scalar registers)
-    auto build_list = [&](const WorkList& wl) {
+    // heads: not the list, but the copies of each layer's first records
+    auto build_list = [&](const WorkList& wl, WorkItem* heads) {
+        const bool owner = share == 0 && !heads;            // writes what there is one of
         const int ub = wl.u_big, us = wl.u_small;
         __syncthreads();                        // the staging arrays of the previous list are no longer read
         if (tid == 0) sBad = 0;
@@ -142,17 +144,17 @@ __device__ void layout_body(const LayoutArgs& a, CacheDev dev, int lists, int sh
         if (tid == 0) { sTotals[0] = (int)(total2 >> 32); sTotals[1] = (int)(total2 & 0xffffffff); }
         if (total > wl.cap) {                   // cannot happen for budgets that passed the capacity check
             if (tid == 0) {
-                if (share == 0) set_sticky(dev.status, VLC_ERR_CAPACITY, -1, -1, -1);
+                if (owner) set_sticky(dev.status, VLC_ERR_CAPACITY, -1, -1, -1);
                 sBad = 1;
             }
-            if (share == 0)
+            if (owner)
                 for (int l = tid; l <= L + 1; l += NT) wl.layer_start[l] = 0;
         } else {
             int64_t acc = inc - run, acc2 = inc2 - run2;
             for (int y = y0; y < y1; ++y) {
                 const int l = y / B, b = y % B;
                 const RowUnits ru = row_units(sKept[b * L + l], T_max, ub, us);
-                if (b == 0 && share == 0) wl.layer_start[l] = (int)acc;
+                if (b == 0 && owner) wl.layer_start[l] = (int)acc;
                 sFirst[b * L + l] = (int)acc;
                 sBigFirst[b * L + l] = (int)(acc2 >> 32);
                 sLiveFirst[b * L + l] = (int)(acc2 & 0xffffffff);
@@ -160,7 +162,7 @@ __device__ void layout_body(const LayoutArgs& a, CacheDev dev, int lists, int sh
                 acc += (int64_t)ru.total * Hkv;
                 acc2 += ((int64_t)ru.big * Hkv << 32) | (int64_t)(ru.live * Hkv);
             }
-            if (tid == 0 && share == 0) wl.layer_start[L] = (int)total;
+            if (tid == 0 && owner) wl.layer_start[L] = (int)total;
         }
         __syncthreads();
         if (sBad) return;
@@ -219,7 +221,7 @@ __device__ void layout_body(const LayoutArgs& a, CacheDev dev, int lists, int sh
             __syncthreads();
         }
         const int n_big = sTotals[0], n_live = sTotals[1];
-        if (tid == 0 && share == 0) wl.layer_start[L + 1] = n_big;               // decode reverses the walk over the u_big units on odd steps
+        if (tid == 0 && owner) wl.layer_start[L + 1] = n_big;               // decode reverses the walk over the u_big units on odd steps
         // rows of many units: sixteen lanes per row, a record each; else a lane per row (where the lanes are few, the
         // sixteen would walk the rows too many times: folded, 256 rows of 3 units, 10.5 -> 12.9 us)
         const int lg = total > (shares > 1 ? 4 : 16) * BL * Hkv ? 4 : 0, ul = tid & ((1 << lg) - 1);
@@ -238,7 +240,7 @@ __device__ void layout_body(const LayoutArgs& a, CacheDev dev, int lists, int sh
             const int w0 = sFirst[bl] + h * ru.total;
             // units of the third class that precede this row's in the list (all units before it minus big and live)
             const int res0 = n_big + n_live + sResFirst[bl] + h * nres;
-            if (ul == 0) wl.row_first[x] = w0;
+            if (ul == 0 && !heads) wl.row_first[x] = w0;
             for (int u = ul; u < ru.total; u += 1 << lg) {
                 it.unit = u;
                 it.key0 = u < ru.big ? u * ub : ru.big * ub + (u - ru.big) * us;
@@ -250,13 +252,15 @@ __device__ void layout_body(const LayoutArgs& a, CacheDev dev, int lists, int sh
                     else if (u < ru.big + ru.live) ws = n_big + sLiveFirst[bl] + h * ru.live + (u - ru.big);
                     else ws = res0 + (u - ru.big - ru.live);
                 }
-                wl.items[ws] = it;
+                if (!heads) wl.items[ws] = it;
+                else if (w0 + u - sFirst[l] < kHeadUnits) heads[l * kHeadUnits + w0 + u - sFirst[l]] = it;
             }
         }
     };
-    if (lists & 1) build_list(dev.list[0]);
-    if (lists & 2) build_list(dev.list[1]);
-    if (lists & 4) build_list(dev.list[2]);
+    if (lists & 1) build_list(dev.list[0], nullptr);
+    if (lists & 2) build_list(dev.list[1], nullptr);
+    if (lists & 4) build_list(dev.list[2], nullptr);
+    if (lists & 8) build_list(dev.list[0], dev.heads);
     static_assert(kNumLists == 3, "one call per list");
 }
 
@@ -267,7 +271,8 @@ __host__ __device__ __forceinline__ bool own_gather_list(const CacheDev& dev) {
 
 constexpr int kLayoutShares = 16;       // blocks per list
 __global__ __launch_bounds__(256) void layout_kernel(LayoutArgs a, CacheDev dev) {
-    layout_body<256>(a, dev, 1 << (blockIdx.x / kLayoutShares), blockIdx.x % kLayoutShares, kLayoutShares);
+    const int part = blockIdx.x / kLayoutShares;            // list 0, list 1, the copies of list 0, list 2 where it is one of its own
+    layout_body<256>(a, dev, part < 2 ? 1 << part : part == 2 ? 8 : 4, blockIdx.x % kLayoutShares, kLayoutShares);
 }
 
 // Order-preserving map float -> uint32 (larger float, larger key).
@@ -277,6 +282,7 @@ __device__ __forceinline__ uint32_t order_key(float f) {
 }
 
 constexpr int kSelThreads = 512;
+constexpr int kFoldBlocks = 3;          // blocks of a folded launch that do the layout
 constexpr int kSelWaves = kSelThreads / 64;
 
 // Visit the candidates of this wave's segment [j0, j1): f(position, key, inside).  Every lane calls f
@@ -315,8 +321,8 @@ __device__ __forceinline__ void for_keys(const uint32_t (&key)[NK > 0 ? NK : 1],
 // decode-query attention, the top-k set S* is found the same way with the cache's own budget and no
 // recent window, and instead of emitting it the block counts how many positions the cache already holds
 // lie in S*: hits_out[row] = |kept ∩ S*|.
-// FOLD = true (small batches, where a one-block kernel and its launch gap show): the grid has one block more
-// than there are rows, and block 0 does the layout kernel's work while the others select.  A selecting
+// FOLD = true (small batches, where a one-block kernel and its launch gap show): the grid has a few blocks more
+// than there are rows, and the first of them do the layout kernel's work while the others select.  A selecting
 // block then cannot read the layout's results: it derives its row's budget and slab offset from the caller's
 // budgets by the layout's own rules (a budget outside [1, m_b] keeps nothing; a request whose slabs do not
 // fit keeps nothing).
@@ -343,12 +349,12 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const float* __rest
     __shared__ uint32_t sel_count, n_cand;
     __shared__ uint32_t cnt_gt[kSelWaves], cnt_eq[kSelWaves];
     if constexpr (FOLD) {
-        if (blockIdx.x < 2) {                        // first, so that they start with the first rows
-            layout_body<kSelThreads>(la, dev, blockIdx.x == 0 ? 1 : own_gather_list(dev) ? 6 : 2, 0, 1);
+        if (blockIdx.x < kFoldBlocks) {              // first, so that they start with the first rows
+            layout_body<kSelThreads>(la, dev, blockIdx.x == 0 ? 1 : blockIdx.x == 2 ? 8 : own_gather_list(dev) ? 6 : 2, 0, 1);
             return;
         }
     }
-    const int row = FOLD ? (int)blockIdx.x - 2 : (int)blockIdx.x;
+    const int row = FOLD ? (int)blockIdx.x - kFoldBlocks : (int)blockIdx.x;
     const int hkv = row % Hkv, bl = row / Hkv;
     int kk, mb;
     int64_t slot_off;
@@ -691,9 +697,9 @@ hipError_t launch_topk_compact(const vlc_cache& c, const int32_t* lens, const fl
     const int per_lane = (((s.m + kSelWaves - 1) / kSelWaves + 63) / 64);
     // the layout as one more block of the selection (short rows only), or as a kernel of its own
     const bool fold = c.opt.select_fold == 2 && per_lane <= 8;
-    if (!fold) layout_kernel<<<kLayoutShares * (own_gather_list(c.dev) ? 3 : 2), 256, 0, st>>>(la, c.dev);
+    if (!fold) layout_kernel<<<kLayoutShares * (own_gather_list(c.dev) ? 4 : 3), 256, 0, st>>>(la, c.dev);
 #define VLC_SELECT(NK) select_kernel<NK, false, false><<<rows, kSelThreads, 0, st>>>(scores, c.dev, s.L, s.Hkv, s.m, lens != nullptr, c.T_max, n_recent, recent_num, recent_den, idx_out, nullptr, nullptr, la)
-    if (fold) select_kernel<8, false, true><<<rows + 2, kSelThreads, 0, st>>>(scores, c.dev, s.L, s.Hkv, s.m, lens != nullptr, c.T_max, n_recent, recent_num, recent_den, idx_out, nullptr, nullptr, la);
+    if (fold) select_kernel<8, false, true><<<rows + kFoldBlocks, kSelThreads, 0, st>>>(scores, c.dev, s.L, s.Hkv, s.m, lens != nullptr, c.T_max, n_recent, recent_num, recent_den, idx_out, nullptr, nullptr, la);
     else if (per_lane <= 8) VLC_SELECT(8);
     else if (per_lane <= 12) VLC_SELECT(12);
     else if (per_lane <= 24) VLC_SELECT(24);

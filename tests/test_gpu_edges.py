@@ -546,6 +546,26 @@ def test_decode_tiles_at_their_edges_for_every_number_of_heads(g, d, fp8):
         path.status()
 
 
+def test_one_layer_with_more_units_than_its_heads_hold():
+    """Launches over one layer read the records of its first 256 units from a place of their own, the others from the list:
+    48 rows of 8 units and 12 of 1 to 3 in a layer, and a layer of fewer.  Every step against the oracle."""
+    V = _V()
+    cfg = _small_cfg(cid=98, m=1900, n_visual=1800, L=3, B=6, Hq=8, Hkv=8, d=64, tau=16)
+    kk = np.array([[940, 3, 900], [940, 130, 1], [930, 255, 5], [930, 256, 129], [935, 1, 257], [935, 64, 33]])
+    T = 2
+    path, dev, caches, scales = _direct_cache(V, cfg, kk, T, dict(layer_unit_slots=128))
+    assert len(_read_list(path, 0, cfg.L)[0]) > 256
+    out = torch.empty((cfg.L, cfg.B, cfg.Hq, cfg.d), dtype=torch.bfloat16, device="cuda")
+    for step in range(T):
+        d_host = W.decode_step_inputs(cfg, step)
+        dd = {n: torch.from_numpy(x).to(torch.bfloat16).cuda() for n, x in d_host.items()}
+        for l in range(cfg.L):
+            path.decode(l, l + 1, dd["q"][l], dd["k_new"][l], dd["v_new"][l], dev["sm_scale"], out[l])
+        torch.cuda.synchronize()
+        _oracle_step(cfg, caches, scales, d_host, out.float().cpu().numpy(), step, "heads")
+    path.status()
+
+
 @pytest.mark.parametrize("B,L,m", [(6, 5, 800), (40, 13, 800), (128, 16, 400)], ids=["30-entries", "520-entries", "2048-entries"])
 def test_size_class_walk_with_budgets_of_every_length(B, L, m):
     """The size-class work list puts the partly filled units longest first (a sort of the (request, layer) entries
