@@ -11,7 +11,7 @@
 //           query rows of ONE key: the sum over the window rows of Sec. 3.2 is in-lane too, and the
 //           Eq. 1 test is one compare on the exponent argument.
 // Q' fragments of a block's rows live in registers for the whole sweep; K streams through LDS in
-// chunks of 128 keys (global -> registers -> LDS, the next chunk in flight while the current one is
+// chunks of 32 to 128 keys (global -> registers -> LDS, the next chunk in flight while the current one is
 // multiplied).  Sweep 1 packs the window rows of the group's heads into 32-row blocks one after the other (a lane
 // owns a row whatever block it is in, so the statistics have the same bits).  In sweep 2 each head's tau rows are padded to a
 // multiple of 32 so that every 32-row block belongs to one query head, and its sums keep their order; padded rows carry a
@@ -59,10 +59,15 @@ __device__ __forceinline__ bool in_class(const MfmaArgs& a, int row_blocks) {
 
 // ------------------------------------------------------------------------------------------------
 // Sweep 1: partial row statistics of one key range of one KV group.
-template <int WAVES, int RB>
-__global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 0) void rowstats_mfma_kernel(MfmaArgs a) {   // 4-wave blocks: registers for 3 blocks per CU, accumulators stay out of the AGPRs
+// CHUNK: keys staged at once.  Small chunks start a block sooner, and their registers (16 for 128 keys) make room for a third
+// 8-wave block per CU; with two row blocks per wave there is none to be had.  Chunks of 128 / 64 / 32 keys, profiled: 4 waves
+// (256 KV groups of 2944 keys, 128 rows) 41 / 38 / 35 us, 8 waves (1024 groups of 10368, 256 rows) 934 / 905 / 818, (256 of 131072,
+// 200 rows) 2512 / 2450 / 2350, 8 waves of two row blocks (1920 of 10368, 448 rows) 2888 / 2866 / 2867, (ragged, up to 400)
+// 467 / 451 / 459.  Two LDS buffers and one barrier per chunk instead: 37.3, 853, 2389, 3051, 496.
+template <int WAVES, int RB, int CHUNK>
+__global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : RB == 1 ? 6 : 0) void rowstats_mfma_kernel(MfmaArgs a) {   // 4-wave blocks: registers for 3 blocks per CU, accumulators stay out of the AGPRs
     constexpr int THREADS = WAVES * 64;
-    __shared__ __align__(16) bf16_t sK[kChunk * kPitch];
+    __shared__ __align__(16) bf16_t sK[CHUNK * kPitch];
     const int group = blockIdx.x, split = blockIdx.y;       // group-major: see the launch
     const int hkv = group % a.Hkv, bl = group / a.Hkv, l = bl % a.L;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;     // wave index in a scalar register
@@ -90,17 +95,17 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 0) void rowstats_mfma_
         z_run[rb] = 0.f;
     }
 
-    KStage<THREADS> st;
+    KStage<THREADS, CHUNK> st;
     if (k_begin < k_end) st.load(kg, k_begin, mb);
     sign_q_frags(qf, scale);
-    for (int kc = k_begin; kc < k_end; kc += kChunk) {
+    for (int kc = k_begin; kc < k_end; kc += CHUNK) {
         __syncthreads();                                   // previous chunk fully consumed
         st.store(sK);
         __syncthreads();
-        if (kc + kChunk < k_end) st.load(kg, kc + kChunk, mb);
-        const bool masked = kc + kChunk > mb - tb + 1;     // chunk reaches past the first window key
+        if (kc + CHUNK < k_end) st.load(kg, kc + CHUNK, mb);
+        const bool masked = kc + CHUNK > mb - tb + 1;     // chunk reaches past the first window key
 #pragma unroll 1
-        for (int t = 0; t < kChunk / 32; ++t) {
+        for (int t = 0; t < CHUNK / 32; ++t) {
             if (kc + t * 32 >= k_end) break;
             uint4 kf[kKSteps];
             load_k_frags(sK, t, lane, kf);
@@ -149,11 +154,13 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 0) void rowstats_mfma_
 
 // ------------------------------------------------------------------------------------------------
 // Sweep 2: column sums of the softmax over all window rows of the KV group, and per-head counts.
-template <int WAVES, int RB>
+// CHUNK as above, but every chunk ends in a sum over the waves: 4 waves 44.5 / 43.6 / 43.2 us for 128 / 64 / 32 keys, 8 waves
+// 933 / 970 / 995, 2795 / 3060 / 3300, 16 waves 3100 / 3180 for 128 / 64.
+template <int WAVES, int RB, int CHUNK>
 __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 4) void colsweep_mfma_kernel(MfmaArgs a) {   // waves per SIMD: 2 blocks of 8 waves, or 3 of 4
     constexpr int THREADS = WAVES * 64;
-    __shared__ __align__(16) bf16_t sK[kChunk * kPitch];
-    __shared__ float sCol[WAVES][kChunk];
+    __shared__ __align__(16) bf16_t sK[CHUNK * kPitch];
+    __shared__ float sCol[WAVES][CHUNK];
     const int group = blockIdx.x, split = blockIdx.y;       // group-major: see the launch
     const int hkv = group % a.Hkv, bl = group / a.Hkv, l = bl % a.L;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;     // wave index in a scalar register
@@ -179,7 +186,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 4) void colsweep_mfma_
         for (int sp = 0; sp < kSplitRegs; ++sp)
             pin[sp] = sp < a.nsplit ? a.part_in[((size_t)group * a.nsplit + sp) * a.RP + at] : make_float2(-INFINITY, 0.f);
     }
-    KStage<THREADS> st;
+    KStage<THREADS, CHUNK> st;
     if (k_begin < k_end) st.load(kg, k_begin, mb);
     uint4 qf[RB][kKSteps];
     load_q_frags<RB, WAVES>(a, bl, hkv, a.rb0 + wave, lane, tb, tauP, qf);      // row blocks rb0 + wave + WAVES * rb
@@ -250,16 +257,16 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 4) void colsweep_mfma_
         }
     }
 
-    for (int kc = k_begin; kc < k_end; kc += kChunk) {
+    for (int kc = k_begin; kc < k_end; kc += CHUNK) {
         // no barrier in front of the store: the one that follows the tiles of the previous chunk (below) already
         // orders every wave's reads of sK before it, and the readers of sCol pass the barrier after the store
         // before any wave writes sCol again
         st.store(sK);
         __syncthreads();
-        if (kc + kChunk < k_end) st.load(kg, kc + kChunk, mb);
-        const bool masked = kc + kChunk > mb - tb + 1;
+        if (kc + CHUNK < k_end) st.load(kg, kc + CHUNK, mb);
+        const bool masked = kc + CHUNK > mb - tb + 1;
 #pragma unroll 1
-        for (int t = 0; t < kChunk / 32; ++t) {
+        for (int t = 0; t < CHUNK / 32; ++t) {
             uint4 kf[kKSteps];
             load_k_frags(sK, t, lane, kf);
             const int key = kc + t * 32 + (lane & 31);          // this lane's key (column of the tile)
@@ -309,7 +316,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 4) void colsweep_mfma_
             if (lane < 32) sCol[wave][t * 32 + lane] = col;
         }
         __syncthreads();
-        if (a.scores && threadIdx.x < kChunk && kc + threadIdx.x < k_end) {
+        if (a.scores && threadIdx.x < CHUNK && kc + threadIdx.x < k_end) {
             float s = 0.f;
 #pragma unroll
             for (int w = 0; w < WAVES; ++w) s += sCol[w][threadIdx.x];
@@ -417,15 +424,15 @@ hipError_t launch_rowstats_mfma(const ScoreArgs& a) {
     for (int rb0 = 0; rb0 < total_rb; rb0 += kMaxRowBlocksPerLaunch) {
         const int nrb = total_rb - rb0 < kMaxRowBlocksPerLaunch ? total_rb - rb0 : kMaxRowBlocksPerLaunch;
         m.rb0 = rb0; m.rb_above = 0;
-        if (nrb <= 4) rowstats_mfma_kernel<4, 1><<<grid, 256, 0, a.stream>>>(m);
-        else if (nrb <= 8) rowstats_mfma_kernel<8, 1><<<grid, 512, 0, a.stream>>>(m);
+        if (nrb <= 4) rowstats_mfma_kernel<4, 1, 32><<<grid, 256, 0, a.stream>>>(m);
+        else if (nrb <= 8) rowstats_mfma_kernel<8, 1, 32><<<grid, 512, 0, a.stream>>>(m);
         else {
             if (launch_per_class(s)) {          // the requests with short windows in the form for them
                 m.rb_upto = 8;
-                rowstats_mfma_kernel<8, 1><<<grid, 512, 0, a.stream>>>(m);
+                rowstats_mfma_kernel<8, 1, 32><<<grid, 512, 0, a.stream>>>(m);
                 m.rb_above = 8; m.rb_upto = INT32_MAX;
             }
-            rowstats_mfma_kernel<8, 2><<<grid, 512, 0, a.stream>>>(m);        // measured faster than 16 x 1 for this sweep
+            rowstats_mfma_kernel<8, 2, 64><<<grid, 512, 0, a.stream>>>(m);        // measured faster than 16 x 1 for this sweep
         }
     }
     return hipGetLastError();
@@ -442,15 +449,15 @@ hipError_t launch_colsweep_mfma(const ScoreArgs& a, bool merge_partials) {
         const int nrb = total_rb - rb0 < kMaxRowBlocksPerLaunch ? total_rb - rb0 : kMaxRowBlocksPerLaunch;
         m.rb0 = rb0; m.rb_above = 0;
         m.accumulate = rb0 > 0;                 // launches of one stream run in order: the column sums add up deterministically
-        if (nrb <= 4) colsweep_mfma_kernel<4, 1><<<grid, 256, 0, a.stream>>>(m);
-        else if (nrb <= 8) colsweep_mfma_kernel<8, 1><<<grid, 512, 0, a.stream>>>(m);
+        if (nrb <= 4) colsweep_mfma_kernel<4, 1, 32><<<grid, 256, 0, a.stream>>>(m);
+        else if (nrb <= 8) colsweep_mfma_kernel<8, 1, kChunk><<<grid, 512, 0, a.stream>>>(m);
         else {
             if (launch_per_class(s)) {
                 m.rb_upto = 8;
-                colsweep_mfma_kernel<8, 1><<<grid, 512, 0, a.stream>>>(m);
+                colsweep_mfma_kernel<8, 1, kChunk><<<grid, 512, 0, a.stream>>>(m);
                 m.rb_above = 8; m.rb_upto = INT32_MAX;
             }
-            colsweep_mfma_kernel<16, 1><<<grid, 1024, 0, a.stream>>>(m);
+            colsweep_mfma_kernel<16, 1, kChunk><<<grid, 1024, 0, a.stream>>>(m);
         }
     }
     return hipGetLastError();

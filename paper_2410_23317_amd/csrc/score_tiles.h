@@ -58,12 +58,12 @@ __device__ __forceinline__ float exp_scale(float scale) { return (scale == 0.f ?
 __device__ __forceinline__ int padded_rows(int tb) { return (tb + 31) & ~31; }
 
 // K chunk staging: global -> registers -> LDS.  Keys at or beyond m are zero-filled.
-template <int THREADS>
+template <int THREADS, int CHUNK = kChunk>
 struct KStage {
-    static constexpr int N = kChunk * (kD / 8) / THREADS;      // 16-byte pieces per thread
+    static constexpr int N = CHUNK * (kD / 8) / THREADS;      // 16-byte pieces per thread
     uint4 r[N];
     __device__ __forceinline__ void load(const bf16_t* kg, int key0, int m) {
-        if (key0 + kChunk <= m) {               // block-uniform: a whole chunk needs no per-row test
+        if (key0 + CHUNK <= m) {               // block-uniform: a whole chunk needs no per-row test
             const uint4* src = reinterpret_cast<const uint4*>(kg + (size_t)key0 * kD) + threadIdx.x;
 #pragma unroll
             for (int u = 0; u < N; ++u) r[u] = src[THREADS * u];
@@ -82,7 +82,7 @@ struct KStage {
     template <int P, int PARTS>
     __device__ __forceinline__ void load_part(const bf16_t* kg, int key0, int m) {
         static_assert(N % PARTS == 0, "pieces per thread must divide evenly");
-        const bool whole = key0 + kChunk <= m;
+        const bool whole = key0 + CHUNK <= m;
 #pragma unroll
         for (int u = P * (N / PARTS); u < (P + 1) * (N / PARTS); ++u) {
             const int x = threadIdx.x + THREADS * u;
