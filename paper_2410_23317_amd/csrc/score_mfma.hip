@@ -22,6 +22,8 @@
 // round-robin where a wave takes two), so a shorter window costs the blocks it holds: the waves beyond it only
 // help to stage K; in large batches whose longest window takes the 16-block forms, requests of up to 8 blocks get a launch
 // of their own.
+#include <type_traits>
+
 #include "common.h"
 #include "internal.h"
 #include "score_tiles.h"
@@ -60,12 +62,15 @@ __device__ __forceinline__ bool in_class(const MfmaArgs& a, int row_blocks) {
 // ------------------------------------------------------------------------------------------------
 // Sweep 1: partial row statistics of one key range of one KV group.
 // CHUNK: keys staged at once.  Small chunks start a block sooner, and their registers (16 for 128 keys) make room for a third
-// 8-wave block per CU; with two row blocks per wave there is none to be had.  Chunks of 128 / 64 / 32 keys, profiled: 4 waves
-// (256 KV groups of 2944 keys, 128 rows) 41 / 38 / 35 us, 8 waves (1024 groups of 10368, 256 rows) 934 / 905 / 818, (256 of 131072,
-// 200 rows) 2512 / 2450 / 2350, 8 waves of two row blocks (1920 of 10368, 448 rows) 2888 / 2866 / 2867, (ragged, up to 400)
-// 467 / 451 / 459.  Two LDS buffers and one barrier per chunk instead: 37.3, 853, 2389, 3051, 496.
+// 8-wave block per CU.  Chunks of 128 / 64 / 32 keys, profiled: 4 waves (256 KV groups of 2944 keys, 128 rows) 41 / 38 / 35 us,
+// 8 waves (1024 groups of 10368, 256 rows) 934 / 905 / 818, (256 of 131072, 200 rows) 2512 / 2450 / 2350.  Two LDS buffers and
+// one barrier per chunk instead: 37.3, 853, 2389.
+// Two row blocks per wave: a K fragment is used for both as it arrives, instead of all eight fragments of a tile being held
+// while one block's chain of products runs and then the other's.  That fits the registers of two blocks per CU: (1920 groups
+// of 10368 keys, 448 rows) 2943 -> 2720 us, (ragged, up to 400 rows) 485 -> 377; within the old registers 3250 and 503.
+// For up to 8 row blocks one per wave stays the better: 830 against 930, 2460 against 2550 with two in blocks of 4 waves.
 template <int WAVES, int RB, int CHUNK>
-__global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : RB == 1 ? 6 : 0) void rowstats_mfma_kernel(MfmaArgs a) {   // 4-wave blocks: registers for 3 blocks per CU, accumulators stay out of the AGPRs
+__global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : RB == 1 ? 6 : 4) void rowstats_mfma_kernel(MfmaArgs a) {   // 4-wave blocks: registers for 3 blocks per CU, accumulators stay out of the AGPRs
     constexpr int THREADS = WAVES * 64;
     __shared__ __align__(16) bf16_t sK[CHUNK * kPitch];
     const int group = blockIdx.x, split = blockIdx.y;       // group-major: see the launch
@@ -108,14 +113,34 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : RB == 1 ? 6 : 0) void 
         for (int t = 0; t < CHUNK / 32; ++t) {
             if (kc + t * 32 >= k_end) break;
             uint4 kf[kKSteps];
-            load_k_frags(sK, t, lane, kf);
+            f32x16_t accs[RB];
+            if constexpr (RB == 1) {
+                load_k_frags(sK, t, lane, kf);
+            } else {
+                const bf16_t* row = sK + (t * 32 + (lane & 31)) * kPitch + (lane >> 5) * 8;
+                auto products = [&](auto countc) {              // of this wave's first row blocks
+#pragma unroll
+                    for (int ks = 0; ks < kKSteps; ++ks) {
+                        const uint4 k1 = *reinterpret_cast<const uint4*>(row + ks * 16);
+#pragma unroll
+                        for (int rb = 0; rb < decltype(countc)::value; ++rb)
+                            accs[rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(k1), as_frag(qf[rb][ks]), accs[rb], 0, 0, 0);
+                    }
+                };
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) accs[rb] = f32x16_t{0};
+                if ((a.rb0 + wave + WAVES * (RB - 1)) * 32 < R) products(std::integral_constant<int, RB>{});     // wave-uniform
+                else if ((a.rb0 + wave) * 32 < R) products(std::integral_constant<int, 1>{});
+            }
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) {
                 if ((a.rb0 + wave + WAVES * rb) * 32 >= R) continue;        // wave-uniform: no rows here
                 f32x16_t acc = {0};
+                if constexpr (RB > 1) acc = accs[rb];
+                else
 #pragma unroll
-                for (int ks = 0; ks < kKSteps; ++ks)
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(kf[ks]), as_frag(qf[rb][ks]), acc, 0, 0, 0);
+                    for (int ks = 0; ks < kKSteps; ++ks)
+                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(kf[ks]), as_frag(qf[rb][ks]), acc, 0, 0, 0);
                 // acc[i] = <k_key, q_row>, key = kc + 32 t + acc_row(i), row = this lane's
                 float v[16];
                 if (masked) {
@@ -432,7 +457,7 @@ hipError_t launch_rowstats_mfma(const ScoreArgs& a) {
                 rowstats_mfma_kernel<8, 1, 32><<<grid, 512, 0, a.stream>>>(m);
                 m.rb_above = 8; m.rb_upto = INT32_MAX;
             }
-            rowstats_mfma_kernel<8, 2, 64><<<grid, 512, 0, a.stream>>>(m);        // measured faster than 16 x 1 for this sweep
+            rowstats_mfma_kernel<8, 2, 32><<<grid, 512, 0, a.stream>>>(m);        // measured faster than 16 x 1 for this sweep
         }
     }
     return hipGetLastError();
