@@ -345,7 +345,8 @@ static vlc_status cache_layout(const vlc_shape* s, int32_t T_max, int64_t sum_k_
     const int64_t mean_row = sum_k_max / s->L + T_max / 2;    // slots of an average row half-way through decode
     // ---- the library's own choices
     // Launches over all layers (measured on the ragged budgets of the 7B and 34B shapes at batch 1 to 64, on an
-    // MI355X: 256 CUs, three blocks of this kernel per CU, two when a KV head serves more than four query heads).
+    // MI355X: 256 CUs; "resident" is three blocks per CU, two when a KV head serves more than four query heads: with the
+    // matrix-core tiles three fit there too, and the lines were measured again and stayed the best).
     // The walk is by size class with the partly filled units longest first, so balance comes from the order; what
     // the unit size trades is the cost of a unit's start, merge and cross-block chain against having enough units.
     //   rows >= 4 x the resident blocks: 2048-slot units (most rows are one unit: no partials at all);
@@ -506,14 +507,6 @@ static vlc_status cache_create_common(const char* who, const vlc_shape* shape, i
     c->kv_fp8 = plan.opt.kv_fp8 != 0;
     c->ragged = false;
     c->compacted = false;
-    {
-        int dev = 0, cus = 0;
-        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) {
-            (void)hipGetLastError();
-            cus = 256;
-        }
-        c->num_cus = cus;
-    }
     *out = c;
     return VLC_OK;
 }

@@ -12,9 +12,10 @@
 // the XCDs' L2 caches by themselves, so no cache-wide release/acquire fence is needed (those cost tens of
 // microseconds here).
 // What bounds a launch: large ones the memory (about 5 TB/s); a launch over one layer is a chain of dependent steps, timed
-// with shader-clock stamps on the 7B shape (rows of 50 to 700 slots, 5.9 us per launch): 1.2 us between two launches, 0.8
+// with shader-clock stamps on the 7B shape (rows of 50 to 700 slots, 5.7 us per launch): 1.2 us between two launches, 0.5
 // until the unit's record is there, 0.6 to 1 to request a tile (a CU takes 64 bytes per clock of a load), 1 until it is
-// multiplied, 0.6 merge of the waves, 0.9 partial acknowledged and counted, 1.2 merge of the row.
+// multiplied, 0.6 merge of the waves, 0.9 partial acknowledged and counted, 1.0 merge of the row.
+//
 // Nothing that changes from step to step is a launch parameter: the number of appends a layer has
 // received is read from the cache (dev.appended), and the launch that appends leaves count + 1 behind.
 // Every block takes a ticket (dev.readers) right after it has read the count; the block that holds the
@@ -990,10 +991,9 @@ hipError_t launch_decode(const DecodeArgs& a) {
     P.zigzag = c.opt.decode_zigzag;
     P.kv_fp8 = c.kv_fp8 ? 1 : 0;
     const int rows = a.n_layers * s.B * s.Hkv;
-    // Upper bound on the block-units of the layer range: every row at the full prompt length, and never more
-    // than the whole work list.  A launch over a layer range is capped at one resident round of blocks (3 per
-    // CU); its blocks walk the slice with the grid as stride.  The budgets, and with them the true number of
-    // units, are known on the device only.
+    // One block per unit.  The budgets, and with them the true number of units, are known on the device only: the grid is
+    // the upper bound, every row at the full prompt length and never more than the whole work list, and blocks beyond the
+    // slice leave at once (grids of 64 to 768 blocks for the same few units measured the same).
     int64_t grid = (int64_t)rows * (((int64_t)s.m + c.T_max) / P.wl.u_small + 1);
     if (grid > P.wl.cap) grid = P.wl.cap;
     if (grid < 1) grid = 1;
