@@ -92,12 +92,13 @@ struct KStage {
             else r[u] = (key < m) ? *reinterpret_cast<const uint4*>(kg + (size_t)key * kD + piece * 8) : make_uint4(0, 0, 0, 0);
         }
     }
+    template <int PITCH = kPitch>
     __device__ __forceinline__ void store(bf16_t* sK) const {
 #pragma unroll
         for (int u = 0; u < N; ++u) {
             const int x = threadIdx.x + THREADS * u;
             const int row = x >> 4, piece = x & 15;
-            *reinterpret_cast<uint4*>(sK + row * kPitch + piece * 8) = r[u];
+            *reinterpret_cast<uint4*>(sK + row * PITCH + piece * 8) = r[u];
         }
     }
 };

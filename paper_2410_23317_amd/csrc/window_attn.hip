@@ -11,9 +11,10 @@
 // logits a lane holds belong to ONE query row and the online softmax stays in the lane (the two
 // lane halves share their running max once per tile).  The probabilities, rounded to bf16, are
 // then already laid out as the B operand of O^T += V^T P^T (lane = query row, 8 keys per lane
-// half), provided V^T is read with the keys in the accumulator's order: V is staged transposed in
-// LDS ([d][key], keys permuted inside each group of 16, 16-byte granules XOR-swizzled so that both
-// the transposing 4-byte writes and the 16-byte fragment reads are free of bank conflicts).
+// half), provided V^T is read with the keys in the accumulator's order.  V is staged as it lies in memory, and the LDS read
+// transposes (ds_read_b64_tr_b16).  Transposing on the way into LDS instead, two keys' words permuted and written 4
+// bytes at a time, took 4 % longer: 1.88 against 1.81 ms (1024 KV groups of 10368 keys, 256
+// rows); the bits are the same.
 // A lane's 64 output accumulators belong to its query row too, so the rescale when a running
 // max moves is a per-lane factor; it is skipped for tiles in which no max of the wave moved.
 // The key range is split across blocks as in the scoring sweeps; partial outputs (unnormalised,
@@ -30,7 +31,9 @@ namespace {
 
 using namespace tiles;
 
-constexpr int kVtRowBytes = kChunk * 2;         // one d-row of the transposed V chunk: 128 keys, no padding
+// bf16 elements per row of V in LDS.  A transposing read takes 64 bytes of each of four rows per lane half: 320 bytes put the four on
+// the 64 banks once.
+constexpr int kVPitch = kD + 32;
 constexpr int kMaxRowBlocks = 8;                // 32-row blocks per launch (one per wave)
 
 struct WinArgs {
@@ -48,84 +51,18 @@ struct WinArgs {
     int rb0;                 // first 32-row block of this launch
 };
 
-// Position of chunk-local key kappa inside its d-row of the transposed chunk: inside each group of
-// 16 keys the order is the one in which a lane half holds them in a 32x32 accumulator
-// (keys {0..3, 8..11} for half 0, {4..7, 12..15} for half 1).
-__device__ __forceinline__ int vt_pos(int kappa) {
-    const int k16 = kappa & 15;
-    return (kappa & ~15) | (((k16 >> 2) & 1) << 3) | ((k16 >> 3) << 2) | (k16 & 3);
-}
-// Byte offset of the 16-byte granule `gran` of d-row `d`.
-__device__ __forceinline__ int vt_granule_offset(int d, int gran) {
-    return d * kVtRowBytes + ((gran ^ ((d >> 3) ^ d)) & 15) * 16;
-}
-
-// V chunk staging: global -> registers -> LDS, transposed.  A thread holds the same 8 d-values of two
-// consecutive keys, so that each LDS write is a 4-byte pair of keys.  Keys at or beyond m are zero.
-template <int THREADS>
-struct VStage {
-    static constexpr int NP = (kChunk / 2) / (THREADS / 16);    // key pairs per thread
-    uint4 ra[NP], rb[NP];
-    __device__ __forceinline__ void load(const bf16_t* vg, int key0, int m) {
-        const int piece = threadIdx.x & 15;
-        if (key0 + kChunk <= m) {               // block-uniform: a whole chunk needs no per-key test
-#pragma unroll
-            for (int u = 0; u < NP; ++u) {
-                const int key = key0 + 2 * ((threadIdx.x >> 4) + (THREADS / 16) * u);
-                const uint4* src = reinterpret_cast<const uint4*>(vg + (size_t)key * kD + piece * 8);
-                ra[u] = src[0];
-                rb[u] = src[kD / 8];
-            }
-            return;
-        }
-#pragma unroll
-        for (int u = 0; u < NP; ++u) {
-            const int key = key0 + 2 * ((threadIdx.x >> 4) + (THREADS / 16) * u);
-            const uint4* src = reinterpret_cast<const uint4*>(vg + (size_t)key * kD + piece * 8);
-            ra[u] = (key < m) ? src[0] : make_uint4(0, 0, 0, 0);
-            rb[u] = (key + 1 < m) ? src[kD / 8] : make_uint4(0, 0, 0, 0);
-        }
-    }
-    // The same in 4 instalments: the 2 NP requests of a thread, numbered 2 u + (second key of the pair).
-    template <int P>
-    __device__ __forceinline__ void load_part(const bf16_t* vg, int key0, int m) {
-        static_assert((2 * NP) % 4 == 0, "requests per thread must divide evenly");
-        const int piece = threadIdx.x & 15;
-        const bool whole = key0 + kChunk <= m;
-#pragma unroll
-        for (int j = P * (NP / 2); j < (P + 1) * (NP / 2); ++j) {
-            const int u = j >> 1, second = j & 1;
-            const int key = key0 + 2 * ((threadIdx.x >> 4) + (THREADS / 16) * u) + second;
-            const uint4* src = reinterpret_cast<const uint4*>(vg + (size_t)key * kD + piece * 8);
-            const uint4 val = (whole || key < m) ? *src : make_uint4(0, 0, 0, 0);
-            if (second) rb[u] = val; else ra[u] = val;
-        }
-    }
-    __device__ __forceinline__ void store(uint8_t* sVt) const {
-        const int piece = threadIdx.x & 15;
-#pragma unroll
-        for (int u = 0; u < NP; ++u) {
-            const int kappa = 2 * ((threadIdx.x >> 4) + (THREADS / 16) * u);
-            const int pos = vt_pos(kappa);                     // even: the pair (kappa, kappa + 1) is one aligned word
-            const uint32_t a[4] = {ra[u].x, ra[u].y, ra[u].z, ra[u].w};
-            const uint32_t b[4] = {rb[u].x, rb[u].y, rb[u].z, rb[u].w};
-#pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                const uint32_t even = __builtin_amdgcn_perm(b[w], a[w], 0x05040100u);   // (a.lo, b.lo): element 2w of both keys
-                const uint32_t odd = __builtin_amdgcn_perm(b[w], a[w], 0x07060302u);    // (a.hi, b.hi): element 2w + 1
-                const int d0 = piece * 8 + 2 * w;
-                *reinterpret_cast<uint32_t*>(sVt + vt_granule_offset(d0, pos >> 3) + (pos & 7) * 2) = even;
-                *reinterpret_cast<uint32_t*>(sVt + vt_granule_offset(d0 + 1, pos >> 3) + (pos & 7) * 2) = odd;
-            }
-        }
-    }
-};
-
-// A-operand fragment of V^T for d-tile dt, tile t of the chunk, k-step s: lane (l % 32) owns d-row
-// 32 dt + l % 32, lane half l / 32 the 8 keys that half holds in accumulator slots [8 s, 8 s + 8).
-__device__ __forceinline__ uint4 load_vt_frag(const uint8_t* sVt, int dt, int t, int s, int lane) {
-    const int d = dt * 32 + (lane & 31);
-    return *reinterpret_cast<const uint4*>(sVt + vt_granule_offset(d, t * 4 + s * 2 + (lane >> 5)));
+// A-operand fragment of V^T for d-tile dt, tile t of the chunk, k-step s: lane (l % 32) owns d-row 32 dt + l % 32, lane half
+// l / 32 the 8 keys that half holds in accumulator slots [8 s, 8 s + 8): 16 s + 4 (l / 32) + {0..3, 8..11}.  V lies in LDS as it
+// does in memory.  ds_read_b64_tr_b16 transposes within 16 lanes: lane 4 j + c names 4 elements of key j at d = 4 c, and lane i is
+// given d = i of the four keys.
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) s16x4_t lds_s16x4_t;
+__device__ __forceinline__ uint4 load_vt_frag(const bf16_t* sV, int dt, int t, int s, int lane) {
+    const bf16_t* at = sV + (t * 32 + s * 16 + (lane >> 5) * 4 + ((lane >> 2) & 3)) * kVPitch + dt * 32 + (lane & 16) + (lane & 3) * 4;
+    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)at);
+    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_t*)(at + 8 * kVPitch));
+    const uint2 a = __builtin_bit_cast(uint2, lo), b = __builtin_bit_cast(uint2, hi);
+    return make_uint4(a.x, a.y, b.x, b.y);
 }
 
 // Maximum over the two lanes l and l ^ 32 (v_permlane32_swap: no trip through the LDS queue).
@@ -138,7 +75,7 @@ template <int WAVES>
 __global__ __launch_bounds__(WAVES * 64, 2) void window_attn_kernel(WinArgs a) {   // two waves per SIMD: two 4-wave blocks or one 8-wave block per compute unit
     constexpr int THREADS = WAVES * 64;
     __shared__ __align__(16) bf16_t sK[kChunk * kPitch];
-    __shared__ __align__(16) uint8_t sVt[kD * kVtRowBytes];
+    __shared__ __align__(16) bf16_t sV[kChunk * kVPitch];
     const int group = blockIdx.y, split = blockIdx.x;
     const int hkv = group % a.Hkv, bl = group / a.Hkv, l = bl % a.L;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -163,13 +100,13 @@ __global__ __launch_bounds__(WAVES * 64, 2) void window_attn_kernel(WinArgs a) {
     for (int dt = 0; dt < kD / 32; ++dt) o[dt] = f32x16_t{0};
 
     KStage<THREADS> ks_;
-    VStage<THREADS> vs_;
+    KStage<THREADS> vs_;
     if (k_begin < k_end) { ks_.load(kg, k_begin, mb); vs_.load(vg, k_begin, mb); }
     sign_q_frags(qf, scale);
     for (int kc = k_begin; kc < k_end; kc += kChunk) {
         __syncthreads();                                       // previous chunk fully consumed
         ks_.store(sK);
-        vs_.store(sVt);
+        vs_.template store<kVPitch>(sV);
         __syncthreads();
         const bool next = kc + kChunk < k_end;                 // block-uniform
         const bool masked = kc + kChunk > mb - tb + 1;         // chunk reaches past the first window key
@@ -184,7 +121,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void window_attn_kernel(WinArgs a) {
             if constexpr (part >= 0) {
                 if (next) {
                     ks_.template load_part<part, kChunk / 32>(kg, kc + kChunk, mb);
-                    vs_.template load_part<part>(vg, kc + kChunk, mb);
+                    vs_.template load_part<part, kChunk / 32>(vg, kc + kChunk, mb);
                 }
             }
             uint4 kf[kKSteps];
@@ -230,7 +167,7 @@ __global__ __launch_bounds__(WAVES * 64, 2) void window_attn_kernel(WinArgs a) {
             for (int dt = 0; dt < kD / 32; ++dt)
 #pragma unroll
                 for (int s = 0; s < 2; ++s)
-                    o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(load_vt_frag(sVt, dt, t, s, lane)), pf[s], o[dt], 0, 0, 0);
+                    o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(as_frag(load_vt_frag(sV, dt, t, s, lane)), pf[s], o[dt], 0, 0, 0);
         };
         if constexpr (SPREAD) {
             tile(std::integral_constant<int, 0>{}, 0);
