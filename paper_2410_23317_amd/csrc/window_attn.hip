@@ -13,7 +13,7 @@
 // then already laid out as the B operand of O^T += V^T P^T (lane = query row, 8 keys per lane
 // half), provided V^T is read with the keys in the accumulator's order.  V is staged as it lies in memory, and the LDS read
 // transposes (ds_read_b64_tr_b16).  Transposing on the way into LDS instead, two keys' words permuted and written 4
-// bytes at a time, took 4 % longer: 1.88 against 1.81 ms (1024 KV groups of 10368 keys, 256
+// bytes at a time, took 3 % longer: 1.82 against 1.77 ms (1024 KV groups of 10368 keys, 256
 // rows); the bits are the same.
 // A lane's 64 output accumulators belong to its query row too, so the rescale when a running
 // max moves is a per-lane factor; it is skipped for tiles in which no max of the wave moved.
