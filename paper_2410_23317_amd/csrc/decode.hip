@@ -18,8 +18,9 @@
 //
 // Nothing that changes from step to step is a launch parameter: the number of appends a layer has
 // received is read from the cache (dev.appended), and the launch that appends leaves count + 1 behind.
-// Every block takes a ticket (dev.readers) right after it has read the count; the block that holds the
-// last ticket of the launch knows that every other block has read the count and writes the new one.
+// Every block takes a ticket (dev.readers) once each of its waves has read the count (a barrier stands between the reads and
+// the ticket, which one thread takes); the block that holds the last ticket of the launch knows that every wave of every
+// block that holds a unit has read the count and writes the new one.
 // A HIP graph that holds one decode step can therefore be replayed step after step.
 #include <stddef.h>
 #include <stdlib.h>
@@ -641,12 +642,16 @@ __global__ __launch_bounds__(256, (IsBf16<T>::value ? (D == 64 && !Q8 ? 4 : 3) :
         const int lr = il - P.layer_begin;
         // The ticket: taken at once by a unit that has nothing to read, else behind the loads of the unit's first
         // tile (returns come back in issue order: in front of them it would hold up the first tile).  A block takes it only
-        // after it has read the append count: the operand of the atomic add is produced by a statement that consumes the count.
-        auto take_ticket = [&]() {
-            int one = 1;
-            asm volatile("" : "+s"(one) : "s"(appended));
-            return (mode && tid == 0) ? add_agent(P.readers + il * kReaderStride, one) : -1;
-        };
+        // after all of its waves have read the append count, or a wave could still meet the new one: each wave's read is consumed
+        // in front of the barrier, and the operand of the atomic add is produced behind it.  (The bare barrier: it waits for no
+        // memory request.  The waves come here together, right behind the record.)
+        int one = 1;
+        if (P.append_mode) {
+            asm volatile("" : : "s"(appended));
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" : "+s"(one));
+        }
+        auto take_ticket = [&]() { return (mode && tid == 0) ? add_agent(P.readers + il * kReaderStride, one) : -1; };
         T* outp = reinterpret_cast<T*>(P.out) + ((size_t)(lr * P.B + ib) * P.Hq + (size_t)hkv * G) * D;
         const int len = kept + step;
         if (__builtin_expect(kept == 0 || key0 >= len, 0)) {    // a request rejected at compaction (defined output, no reads), or a unit reserved for later appends
