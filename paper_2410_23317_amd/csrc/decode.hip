@@ -22,6 +22,7 @@
 // the ticket, which one thread takes); the block that holds the last ticket of the launch knows that every wave of every
 // block that holds a unit has read the count and writes the new one.
 // A HIP graph that holds one decode step can therefore be replayed step after step.
+#include <float.h>
 #include <stddef.h>
 #include <stdlib.h>
 
@@ -164,6 +165,10 @@ __device__ __forceinline__ int64_t uniform64(int64_t v) {
 template <typename T> struct IsBf16 { static constexpr bool value = false; };
 template <> struct IsBf16<bf16_t> { static constexpr bool value = true; };
 
+// Running maxima start at the lowest finite number: slots whose logits are all -inf (keys masked by infinite entries, or
+// products that overflow) then weigh nothing in the tiles as in the merges; from -inf they would give -inf - -inf.
+constexpr float kNoMax = -FLT_MAX;
+
 // ---- tiles ------------------------------------------------------------------------------------------
 // What a unit's waves know of its row.
 template <typename T>
@@ -217,7 +222,7 @@ struct TileMfma {
         const bf16_t* row = r.q + (size_t)min(lane & 15, G - 1) * D;
 #pragma unroll
         for (int s = 0; s < KST; ++s) qf[s] = *reinterpret_cast<const uint4*>(row + k_elem(s, lane >> 4));
-        m_run = -INFINITY; l_run = 0.f;
+        m_run = kNoMax; l_run = 0.f;
 #pragma unroll
         for (int e = 0; e < EV; ++e) acc[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
@@ -298,7 +303,7 @@ struct TileMfma {
     }
     // Running max, accumulators and sum brought to the new maximum over the logits held by all lanes of a head.
     __device__ __forceinline__ void raise_max(float mt) {
-        const float m_new = fmaxf(m_run, max_over_groups(mt));       // finite: there is at least one slot
+        const float m_new = fmaxf(m_run, max_over_groups(mt));
         if (__ballot(m_new > m_run)) {
             const float corr = exp2_fast(m_run - m_new);
             l_run *= corr;
@@ -405,7 +410,7 @@ struct TileF32 {
 #pragma unroll
         for (int h = 0; h < G; ++h) qv[h] = *reinterpret_cast<const float4*>(r.q + (size_t)h * D + (lane % LPR) * 4);
 #pragma unroll
-        for (int hh = 0; hh < HR; ++hh) { m_run[hh] = -INFINITY; l_run[hh] = 0.f; }
+        for (int hh = 0; hh < HR; ++hh) { m_run[hh] = kNoMax; l_run[hh] = 0.f; }
 #pragma unroll
         for (int h = 0; h < G; ++h)
 #pragma unroll
@@ -478,7 +483,7 @@ struct TileF32 {
             mt = fmaxf(mt, dpp_mov<kDppRowRor(4)>(mt));
             mt = fmaxf(mt, dpp_mov<kDppRowRor(2)>(mt));
             mt = fmaxf(mt, dpp_mov<kDppRowRor(1)>(mt));
-            const float m_new = fmaxf(m_run[hh], mt);            // finite for real heads: the tile holds >= 1 slot
+            const float m_new = fmaxf(m_run[hh], mt);
             float ps = 0.f;
 #pragma unroll
             for (int kk = 0; kk < KK; ++kk) {
