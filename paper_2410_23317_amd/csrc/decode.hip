@@ -86,6 +86,20 @@ __device__ __forceinline__ int32_t add_agent(int32_t* p, int32_t v) {
 // (Rows follow each other in the slot order, so the ranges of two rows never meet, whatever the unit sizes.)
 __device__ __forceinline__ int64_t first_partial(int64_t idx_base, int row_abs) { return idx_base / kMinUnitSlots + row_abs; }
 
+// 1 / l and o / l as the outputs of type T want them: to the last bit where they keep 32, and by v_rcp_f32, which is within an
+// ulp of that, where they are rounded to bf16.
+template <typename T> struct Quotient;
+template <> struct Quotient<float> {
+    float l;
+    __device__ __forceinline__ explicit Quotient(float sum) : l(sum) {}
+    __device__ __forceinline__ float operator()(float o) const { return o / l; }
+};
+template <> struct Quotient<bf16_t> {
+    float inv;
+    __device__ __forceinline__ explicit Quotient(float sum) : inv(__builtin_amdgcn_rcpf(sum)) {}
+    __device__ __forceinline__ float operator()(float o) const { return o * inv; }
+};
+
 // Merge the nu partials of one row, one element per thread.
 template <typename T, int D, int G, int THREADS>
 __device__ __forceinline__ void merge_partials(const float* part, T* outp, int nu, int tid) {
@@ -808,8 +822,8 @@ __global__ __launch_bounds__(256, (IsBf16<T>::value ? (D == 64 && !Q8 ? 4 : 3) :
                     lt = fmaf(ml[wv].y, wgt, lt);
                 }
                 if (whole) {
-                    const float inv = __builtin_amdgcn_rcpf(lt);    // within an ulp of the quotient: far inside the output's rounding
-                    store_pair(outp + h * D + e, o0 * inv, o1 * inv);
+                    const Quotient<T> by_sum(lt);
+                    store_pair(outp + h * D + e, by_sum(o0), by_sum(o1));
                 } else {                                            // device-scope stores: see below
                     store_agent2(part + h * D + e, o0, o1);
                     if (e == 0) store_agent2(part + G * D + h * 2, mt, lt);
@@ -855,8 +869,8 @@ __global__ __launch_bounds__(256, (IsBf16<T>::value ? (D == 64 && !Q8 ? 4 : 3) :
                         const float wgt = (ml[j].x > -INFINITY) ? exp2_fast(ml[j].x - mt) : 0.f;
                         o0 = fmaf(ov[j].x, wgt, o0); o1 = fmaf(ov[j].y, wgt, o1); lt = fmaf(ml[j].y, wgt, lt);
                     }
-                    const float inv = __builtin_amdgcn_rcpf(lt);
-                    store_pair(outp + x, o0 * inv, o1 * inv);
+                    const Quotient<T> by_sum(lt);
+                    store_pair(outp + x, by_sum(o0), by_sum(o1));
                 }
             } else if (sLast) {
                 // More: they are dealt to the waves; a lane holds NP times four neighbouring outputs and the weight

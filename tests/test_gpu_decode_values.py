@@ -110,3 +110,36 @@ def test_infinite_values_and_nan_keys_stay_where_they_belong(dtype, d, g, fp8):
             want = O.decode_attn(dq[l, 0, :g], k[:1], v[:1], cfg.d ** -0.5)
             rest = np.arange(d) != 5
             assert_close(out[l, 0, :g][:, rest], want[:, rest], what=f"step {t} row of {ROWS[l]}", **out_tol(cfg))
+
+
+@pytest.mark.parametrize("merge", [1, 2], ids=["in-kernel", "merge-kernel"])
+@pytest.mark.parametrize("d,g", [(64, 1), (64, 4), (128, 2), (128, 7)])
+def test_fp32_outputs_are_the_rounded_quotient(d, g, merge):
+    """A query of zeros: every probability is 1, the sums are whole numbers below 2^24 and exact, so the output has to be their
+    quotient to the last bit; rows of one unit, of two to eight, and of more."""
+    import paper_2410_23317_amd as V
+    from paper_2410_23317_amd.pipeline import VLCachePath
+    rows = [1, 7, 100, 129, 300, 500, 900, 1023, 1025, 1200, 1290]
+    cfg = W.custom_config(cid=82, name="quotient", dtype="f32", d=d, Hq=2 * g, Hkv=2, m=1400, tau=16, lead_text=9, n_visual=1300,
+                          L=len(rows), B=1, sinks=6, alphas=((1, 5),))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(g)
+    k = torch.randn((1, cfg.L, 2, cfg.m, d), generator=gen, device="cuda")
+    v = torch.randint(-8000, 8001, (1, cfg.L, 2, cfg.m, d), generator=gen, device="cuda").float()
+    vn = torch.randint(-8000, 8001, (cfg.L, 1, 2, d), generator=gen, device="cuda").float()
+    path = VLCachePath(make_shape(cfg), alpha=(1, 1), T_max=2,
+                       options=V.make_options(unit_slots=128, layer_unit_slots=128, decode_merge=merge))
+    path.scores.copy_(torch.arange(cfg.m, 0, -1, device="cuda").float().expand(path.scores.shape))
+    path.topk_compact(k, v, k=torch.tensor([rows], dtype=torch.int32, device="cuda"))
+    q = torch.zeros((cfg.L, 1, cfg.Hq, d), device="cuda")
+    out = torch.empty_like(q)
+    for l0, l1 in [(0, cfg.L)] + [(l, l + 1) for l in range(cfg.L)]:
+        appends = l0 == 0 and l1 == cfg.L                           # then once more per layer, over the same rows
+        path.decode(l0, l1, q[l0:l1], k[0, l0:l1, :, 0].unsqueeze(1).contiguous() if appends else None, vn[l0:l1] if appends else None, None, out[l0:l1])
+        torch.cuda.synchronize()
+        for l in range(l0, l1):
+            _, vals = _rows(path, l, appended=1)
+            want = (vals.sum(1).astype(np.float32) / np.float32(rows[l] + 1)).astype(np.float32)
+            got = out[l, 0].cpu().numpy().reshape(2, g, d)
+            assert np.array_equal(got, np.repeat(want[:, None], g, 1)), (l0, l1, rows[l], int((got != want[:, None]).sum()))
+    path.status()
