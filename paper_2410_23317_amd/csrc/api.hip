@@ -507,6 +507,14 @@ static vlc_status cache_create_common(const char* who, const vlc_shape* shape, i
     c->kv_fp8 = plan.opt.kv_fp8 != 0;
     c->ragged = false;
     c->compacted = false;
+    {
+        int dev = 0, cus = 0;
+        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) {
+            (void)hipGetLastError();
+            cus = 256;
+        }
+        c->num_cus = cus;
+    }
     *out = c;
     return VLC_OK;
 }

@@ -574,7 +574,9 @@ struct TileF32 {
 // being appended is quantised by the wave that attends over it, which stores it too.
 // Blocks of four waves, several per CU: the blocks of a CU overlap each other's start-up and merge phases.  One wide block
 // per row (12 waves, no merge across blocks) measured no faster: the row's loads then queue at a single CU's address path.
-template <typename T, int D, int G, bool Q8>
+// WALK: the grid is smaller than the slice may be (launches over a layer range, see launch_decode), a block takes further
+// units with the grid as stride.
+template <typename T, int D, int G, bool Q8, bool WALK>
 __global__ __launch_bounds__(256, (IsBf16<T>::value ? (D == 64 && !Q8 ? 4 : 3) : G <= 4 && D == 64 ? 3 : 2)) void decode_kernel(DecodeParams P) {
     constexpr int NW = 4;                       // waves per block
     constexpr int THREADS = NW * 64;
@@ -590,8 +592,7 @@ __global__ __launch_bounds__(256, (IsBf16<T>::value ? (D == 64 && !Q8 ? 4 : 3) :
     __shared__ __align__(16) float sL[BF ? 1 : NW][TK][pad_pow2(G)];      // fp32 storage: the waves' logits and probabilities
     __shared__ int sLast;
 
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = uniform(tid >> 6);
+    const int tid = threadIdx.x;
     // The work list and its layer index, budgets and slab offsets were written by the compaction, in an earlier launch:
     // they are constant while this kernel runs and are read as such, which puts their (block-uniform) loads on the scalar unit.
     typedef const __attribute__((address_space(4))) int32_t* IndexPtr;
@@ -601,8 +602,9 @@ __global__ __launch_bounds__(256, (IsBf16<T>::value ? (D == 64 && !Q8 ? 4 : 3) :
     const int begin = P.layer_begin ? layer_start[P.layer_begin] : 0;
     const int end = layer_start[P.layer_begin + P.n_layers];
     const int appended = P.appended[P.layer_begin];
-    // ---- the unit of this block.  One block-unit per block: the hardware dispatcher balances the ragged units.  The grid is
-    // a host-side upper bound on the units of the layer range, surplus blocks leave at once.
+    // ---- the unit of this block.  One block-unit per block while the grid covers the slice: the hardware dispatcher balances
+    // the ragged units.  The grid is a host-side upper bound on the units of the layer range, or a cap below it, and blocks
+    // beyond the slice leave at once.
     // The record is read word by word.  A layer's first records (launches over one layer) are requested together with the
     // values above, the others, whose place depends on them, a round trip later.
     static_assert(offsetof(WorkItem, row_abs) == 0 && offsetof(WorkItem, key0) == 4 && offsetof(WorkItem, kept) == 8 &&
@@ -639,16 +641,17 @@ __global__ __launch_bounds__(256, (IsBf16<T>::value ? (D == 64 && !Q8 ? 4 : 3) :
     if (over) mode = 0;
     const bool appending = mode == 1;
     const int step = appended + (mode ? 1 : 0); // appends the cache holds once this launch is done
-    auto process_unit = [&]() {
+    auto process_unit = [&](const auto& A, int tid) {
+        const int lane = tid & 63, wave = uniform(tid >> 6);
         // The block that holds the last ticket of its layer, and then of the launch, publishes the new count.
         auto finish = [&](int ticket, int il, int n_layer) {
             if (ticket != n_layer - 1) return;
-            store_agent(P.readers + il * kReaderStride, 0);
-            if (P.n_layers > 1) {
-                if (add_agent(P.readers + P.L * kReaderStride, 1) != P.n_layers - 1) return;
-                store_agent(P.readers + P.L * kReaderStride, 0);
+            store_agent(A.readers + il * kReaderStride, 0);
+            if (A.n_layers > 1) {
+                if (add_agent(A.readers + A.L * kReaderStride, 1) != A.n_layers - 1) return;
+                store_agent(A.readers + A.L * kReaderStride, 0);
             }
-            for (int l = P.layer_begin; l < P.layer_begin + P.n_layers; ++l) store_agent(P.appended + l, step);
+            for (int l = A.layer_begin; l < A.layer_begin + A.n_layers; ++l) store_agent(A.appended + l, step);
         };
         if (!listed) return;
         const int row_abs = rec[0], key0 = rec[1], kept = rec[2], unit = rec[3];
@@ -656,22 +659,22 @@ __global__ __launch_bounds__(256, (IsBf16<T>::value ? (D == 64 && !Q8 ? 4 : 3) :
         const int64_t idx_base = (int64_t)(((uint64_t)(uint32_t)rec[7] << 32) | (uint32_t)rec[6]);
         const int ib = rec[8], il = rec[9], ucap = rec[11], hkv = rec[12], n_layer = rec[13];
         if (w >= end) return;
-        const int nbig = kept >> P.ub_shift;    // units of this row that hold slots now: the whole ones, and the small ones up to len
-        const int nu = nbig + ((kept + step - (nbig << P.ub_shift) + (1 << P.us_shift) - 1) >> P.us_shift);
-        const int lr = il - P.layer_begin;
+        const int nbig = kept >> A.ub_shift;    // units of this row that hold slots now: the whole ones, and the small ones up to len
+        const int nu = nbig + ((kept + step - (nbig << A.ub_shift) + (1 << A.us_shift) - 1) >> A.us_shift);
+        const int lr = il - A.layer_begin;
         // The ticket: taken at once by a unit that has nothing to read, else behind the loads of the unit's first
         // tile (returns come back in issue order: in front of them it would hold up the first tile).  A block takes it only
         // after all of its waves have read the append count, or a wave could still meet the new one: each wave's read is consumed
         // in front of the barrier, and the operand of the atomic add is produced behind it.  (The bare barrier: it waits for no
         // memory request.  The waves come here together, right behind the record.)
         int one = 1;
-        if (P.append_mode) {
+        if (A.append_mode) {
             asm volatile("" : : "s"(appended));
             __builtin_amdgcn_s_barrier();
             asm volatile("" : "+s"(one));
         }
-        auto take_ticket = [&]() { return (mode && tid == 0) ? add_agent(P.readers + il * kReaderStride, one) : -1; };
-        T* outp = reinterpret_cast<T*>(P.out) + ((size_t)(lr * P.B + ib) * P.Hq + (size_t)hkv * G) * D;
+        auto take_ticket = [&]() { return (mode && tid == 0) ? add_agent(A.readers + il * kReaderStride, one) : -1; };
+        T* outp = reinterpret_cast<T*>(A.out) + ((size_t)(lr * A.B + ib) * A.Hq + (size_t)hkv * G) * D;
         const int len = kept + step;
         if (__builtin_expect(kept == 0 || key0 >= len, 0)) {    // a request rejected at compaction (defined output, no reads), or a unit reserved for later appends
             if (kept == 0)
@@ -680,22 +683,22 @@ __global__ __launch_bounds__(256, (IsBf16<T>::value ? (D == 64 && !Q8 ? 4 : 3) :
             if (mode && tid == 0) finish(ticket, il, n_layer);
             return;
         }
-        const int cap = kept + P.T_max;
+        const int cap = kept + A.T_max;
         const int new_slot = appending ? len - 1 : -1;
         const int held = BF && appending ? len - 1 : len;                       // slots the tiles cover
         const int lim = min(held, key0 + ucap);                                 // end of the unit's slots
         RowRefs<T> row;
-        row.K = P.kv + kbase * (Q8 ? 1 : (int)sizeof(T));
-        row.V = row.K + (int64_t)P.Hkv * cap * RB;
-        row.Ksc = P.scales + kbase / D;
-        row.Vsc = row.Ksc + (int64_t)P.Hkv * cap;
-        row.q = reinterpret_cast<const T*>(P.q) + ((size_t)(lr * P.B + ib) * P.Hq + (size_t)hkv * G) * D;
-        row.knew = reinterpret_cast<const T*>(P.k_new) + ((size_t)(lr * P.B + ib) * P.Hkv + hkv) * D;
-        row.vnew = reinterpret_cast<const T*>(P.v_new) + ((size_t)(lr * P.B + ib) * P.Hkv + hkv) * D;
+        row.K = A.kv + kbase * (Q8 ? 1 : (int)sizeof(T));
+        row.V = row.K + (int64_t)A.Hkv * cap * RB;
+        row.Ksc = A.scales + kbase / D;
+        row.Vsc = row.Ksc + (int64_t)A.Hkv * cap;
+        row.q = reinterpret_cast<const T*>(A.q) + ((size_t)(lr * A.B + ib) * A.Hq + (size_t)hkv * G) * D;
+        row.knew = reinterpret_cast<const T*>(A.k_new) + ((size_t)(lr * A.B + ib) * A.Hkv + hkv) * D;
+        row.vnew = reinterpret_cast<const T*>(A.v_new) + ((size_t)(lr * A.B + ib) * A.Hkv + hkv) * D;
         row.len = len;
         row.held = appending ? len - 1 : len;
         row.new_slot = new_slot;
-        row.scale2 = (P.sm_scale ? ((ScalePtr)P.sm_scale)[il] : P.default_scale) * kLog2e;
+        row.scale2 = (A.sm_scale ? ((ScalePtr)A.sm_scale)[il] : A.default_scale) * kLog2e;
         Tile tile;
         if constexpr (!BF) {
             tile.sL = sL[wave];
@@ -707,7 +710,7 @@ __global__ __launch_bounds__(256, (IsBf16<T>::value ? (D == 64 && !Q8 ? 4 : 3) :
         // larger than an L2 then finds the tiles it touched last in the previous step first in this one.
         const int tw0 = key0 + wave * TK;
         const int nt_w = tw0 < lim ? (lim - tw0 + NW * TK - 1) / (NW * TK) : 0;    // tiles of this wave that hold slots
-        const bool rev = P.zigzag > 1 && (step & 1);
+        const bool rev = A.zigzag > 1 && (step & 1);
         int t0 = tw0 + (rev ? nt_w - 1 : 0) * NW * TK;
         const int stride = rev ? -NW * TK : NW * TK;
         // the last wave of the unit that holds the new slot (it has the fewest rows) also attends over and stores the new row
@@ -773,7 +776,7 @@ __global__ __launch_bounds__(256, (IsBf16<T>::value ? (D == 64 && !Q8 ? 4 : 3) :
                         for (int w = 0; w < D / 32; ++w) reinterpret_cast<uint32_t*>(vdst)[lane * (D / 32) + w] = nv[w];
                     }
                 }
-                if (lane == 0) P.idx[idx_base + new_slot] = P.m + appended;
+                if (lane == 0) A.idx[idx_base + new_slot] = A.m + appended;
                 tile.add_new(row, nk, nv, sk, sv, lane);
             }
         }
@@ -793,7 +796,7 @@ __global__ __launch_bounds__(256, (IsBf16<T>::value ? (D == 64 && !Q8 ? 4 : 3) :
         if (!BF && appending && new_slot >= key0 && new_slot < key0 + ucap && tid < RB / 16) {
             reinterpret_cast<uint4*>(const_cast<char*>(row.K) + (int64_t)new_slot * RB)[tid] = reinterpret_cast<const uint4*>(row.knew)[tid];
             reinterpret_cast<uint4*>(const_cast<char*>(row.V) + (int64_t)new_slot * RB)[tid] = reinterpret_cast<const uint4*>(row.vnew)[tid];
-            if (tid == 0) P.idx[idx_base + new_slot] = P.m + appended;
+            if (tid == 0) A.idx[idx_base + new_slot] = A.m + appended;
         }
 
         // ---- merge the 4 waves through LDS
@@ -801,7 +804,7 @@ __global__ __launch_bounds__(256, (IsBf16<T>::value ? (D == 64 && !Q8 ? 4 : 3) :
         __syncthreads();
         // every thread merges two neighbouring output elements of one head over the waves' shares in sMerge: one weight
         // per wave, one store; into the output, or into the unit's partial
-        float* part = P.partials + (first_partial(idx_base, row_abs) + unit) * PS;
+        float* part = A.partials + (first_partial(idx_base, row_abs) + unit) * PS;
         auto merge_waves = [&](bool whole) {
             for (int x = tid; x < G * D / 2; x += THREADS) {
                 const int h = x / (D / 2), e = (x % (D / 2)) * 2;
@@ -831,7 +834,7 @@ __global__ __launch_bounds__(256, (IsBf16<T>::value ? (D == 64 && !Q8 ? 4 : 3) :
             }
         };
         merge_waves(nu == 1);
-        if (nu > 1 && P.merge_mode == 1) {
+        if (nu > 1 && A.merge_mode == 1) {
             // Publication of the partials.  They were written with device-scope stores, which go through to the
             // memory side of the XCDs' L2 caches.  Every thread first waits until its own stores have been
             // acknowledged (a workgroup barrier alone does not drain another wave's outstanding stores), then
@@ -840,7 +843,7 @@ __global__ __launch_bounds__(256, (IsBf16<T>::value ? (D == 64 && !Q8 ? 4 : 3) :
             // memory; it reads them with device-scope loads, which do not hit a stale line of its own L2.
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
-            int32_t* counter = P.counters + row_abs;
+            int32_t* counter = A.counters + row_abs;
             if (tid == 0) sLast = (add_agent(counter, 1) == nu - 1) ? 1 : 0;
             __syncthreads();
             // The last unit merges.  Few partials: a thread merges two neighbouring outputs over all of them, without a word to
@@ -932,7 +935,24 @@ __global__ __launch_bounds__(256, (IsBf16<T>::value ? (D == 64 && !Q8 ? 4 : 3) :
         }
         if (mode && tid == 0) finish(ticket, il, n_layer);
     };
-    process_unit();
+    if constexpr (!WALK) {
+        process_unit(P, tid);
+    } else {
+        // Loop invariants would be held in registers, and spill: the thread's index and the parameters are read anew for
+        // each unit, the latter through a pointer to the kernel's arguments that the compiler cannot see through.
+        typedef const __attribute__((address_space(4))) DecodeParams* ParamsPtr;
+#pragma unroll 1
+        for (;;) {
+            ParamsPtr Q = (ParamsPtr)__builtin_amdgcn_kernarg_segment_ptr();
+            int t = threadIdx.x;
+            asm volatile("" : "+s"(Q), "+v"(t));
+            process_unit(*Q, t);
+            w += (int)gridDim.x;                // the list of a layer range is in its own order
+            if (w >= end) break;
+            __syncthreads();                    // the previous unit's merge buffers are free again
+            read(P.wl.items + w);
+        }
+    }
     if (over && blockIdx.x == 0 && tid == 0) set_sticky(P.status, VLC_ERR_CAPACITY, -3, P.layer_begin, appended);
 }
 
@@ -957,30 +977,32 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(DecodeParams P) {
 }
 
 template <typename T, int D, int G>
-hipError_t launch_one(const DecodeParams& P, int grid, int rows, hipStream_t st) {
+hipError_t launch_one(const DecodeParams& P, int grid, bool walk, int rows, hipStream_t st) {
     bool done = false;
     if constexpr (IsBf16<T>::value) {
         if (P.kv_fp8) {
-            decode_kernel<T, D, G, true><<<grid, 256, 0, st>>>(P);
+            if (walk) decode_kernel<T, D, G, true, true><<<grid, 256, 0, st>>>(P);
+            else decode_kernel<T, D, G, true, false><<<grid, 256, 0, st>>>(P);
             done = true;
         }
     }
-    if (!done) decode_kernel<T, D, G, false><<<grid, 256, 0, st>>>(P);
+    if (!done && walk) decode_kernel<T, D, G, false, true><<<grid, 256, 0, st>>>(P);
+    else if (!done) decode_kernel<T, D, G, false, false><<<grid, 256, 0, st>>>(P);
     if (P.merge_mode == 2) decode_merge_kernel<T, D, G><<<rows, 256, 0, st>>>(P);
     return hipGetLastError();
 }
 
 template <typename T, int D>
-hipError_t launch_g(const DecodeParams& P, int g, int grid, int rows, hipStream_t st) {
+hipError_t launch_g(const DecodeParams& P, int g, int grid, bool walk, int rows, hipStream_t st) {
     switch (g) {
-        case 1: return launch_one<T, D, 1>(P, grid, rows, st);
-        case 2: return launch_one<T, D, 2>(P, grid, rows, st);
-        case 3: return launch_one<T, D, 3>(P, grid, rows, st);
-        case 4: return launch_one<T, D, 4>(P, grid, rows, st);
-        case 5: return launch_one<T, D, 5>(P, grid, rows, st);
-        case 6: return launch_one<T, D, 6>(P, grid, rows, st);
-        case 7: return launch_one<T, D, 7>(P, grid, rows, st);
-        case 8: return launch_one<T, D, 8>(P, grid, rows, st);
+        case 1: return launch_one<T, D, 1>(P, grid, walk, rows, st);
+        case 2: return launch_one<T, D, 2>(P, grid, walk, rows, st);
+        case 3: return launch_one<T, D, 3>(P, grid, walk, rows, st);
+        case 4: return launch_one<T, D, 4>(P, grid, walk, rows, st);
+        case 5: return launch_one<T, D, 5>(P, grid, walk, rows, st);
+        case 6: return launch_one<T, D, 6>(P, grid, walk, rows, st);
+        case 7: return launch_one<T, D, 7>(P, grid, walk, rows, st);
+        case 8: return launch_one<T, D, 8>(P, grid, walk, rows, st);
     }
     return hipErrorInvalidValue;
 }
@@ -1017,14 +1039,20 @@ hipError_t launch_decode(const DecodeArgs& a) {
     const int rows = a.n_layers * s.B * s.Hkv;
     // One block per unit.  The budgets, and with them the true number of units, are known on the device only: the grid is
     // the upper bound, every row at the full prompt length and never more than the whole work list, and blocks beyond the
-    // slice leave at once (grids of 64 to 768 blocks for the same few units measured the same).
+    // slice leave at once.  Where the bound is beyond eight resident rounds (three blocks per CU) these cost more than the walk does:
+    // a launch over a layer range then gets one resident round, which walks.  us per launch over one layer, 7B shape, covering
+    // grid / walk: 32 prompts of 4096 tokens at 1 % (8448 blocks, 256 to 512 units) 8.7 / 6.3, 64 of 2944 at 1 % (12288) 13.9 / 8.3,
+    // 64 of 2944 at 10 % 27.8 / 26.8; 8 of 32768 at 1 % (a bound of 5504) 7.9 / 8.1, 16 of 2944 at 10 % (3072) 10.1 / 10.3.
     int64_t grid = (int64_t)rows * (((int64_t)s.m + c.T_max) / P.wl.u_small + 1);
     if (grid > P.wl.cap) grid = P.wl.cap;
+    const int64_t round = 3 * (int64_t)c.num_cus;
+    const bool walk = !all_layers && grid > 8 * round;
+    if (walk) grid = round;
     if (grid < 1) grid = 1;
     const int g = s.Hq / s.Hkv;
     if (s.dtype == VLC_F32)
-        return s.d == 64 ? launch_g<float, 64>(P, g, (int)grid, rows, a.stream) : launch_g<float, 128>(P, g, (int)grid, rows, a.stream);
-    return s.d == 64 ? launch_g<bf16_t, 64>(P, g, (int)grid, rows, a.stream) : launch_g<bf16_t, 128>(P, g, (int)grid, rows, a.stream);
+        return s.d == 64 ? launch_g<float, 64>(P, g, (int)grid, walk, rows, a.stream) : launch_g<float, 128>(P, g, (int)grid, walk, rows, a.stream);
+    return s.d == 64 ? launch_g<bf16_t, 64>(P, g, (int)grid, walk, rows, a.stream) : launch_g<bf16_t, 128>(P, g, (int)grid, walk, rows, a.stream);
 }
 
 }  // namespace vlc

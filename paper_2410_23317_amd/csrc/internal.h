@@ -87,6 +87,7 @@ struct vlc_cache {
     vlc::CacheDev dev;
     bool compacted;
     bool kv_fp8;                       // rows stored as E4M3 codes + per-row scale
+    int32_t num_cus;                   // compute units of the device the cache was created on
     bool ragged;                       // the last compaction had per-request lengths (dev.lens is valid)
     int32_t appended[vlc::kMaxLayers]; // decode appends enqueued so far, per layer (the device keeps the count the kernels use)
 };
