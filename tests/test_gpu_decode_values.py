@@ -14,7 +14,7 @@ ROWS = [1, 30, 31, 32, 33, 63, 64, 127, 128, 129, 300, 500, 1290]
 PER_LAYER = [False, True]
 
 
-def _setup(dtype, d, g, fp8, T, mask=None):
+def _setup(dtype, d, g, fp8, T, mask=None, fill=None):
     """One layer per entry of ROWS; q[..., 0] is 1, so that entry 0 of a key alone decides whether its logit is infinite.
     mask: kept positions (every one of a row's leading `mask` kept positions) whose keys hold -inf there."""
     import paper_2410_23317_amd as V
@@ -32,6 +32,8 @@ def _setup(dtype, d, g, fp8, T, mask=None):
     kn, vn = r.standard_normal((T, cfg.L, 1, 2, d)), r.standard_normal((T, cfg.L, 1, 2, d))
     path = VLCachePath(make_shape(cfg), alpha=(1, 1), T_max=T,
                        options=V.make_options(unit_slots=128, layer_unit_slots=128, kv_fp8=int(fp8)))
+    if fill is not None:
+        path.cache.arena.fill_(fill)                 # bytes that the compaction does not write keep this value
     path.scores.copy_(torch.arange(cfg.m, 0, -1, device="cuda").float().expand(path.scores.shape))       # the leading positions are kept
     path.topk_compact(put(k), put(v), k=torch.tensor([ROWS], dtype=torch.int32, device="cuda"))
     path.status()
@@ -110,6 +112,22 @@ def test_infinite_values_and_nan_keys_stay_where_they_belong(dtype, d, g, fp8):
             want = O.decode_attn(dq[l, 0, :g], k[:1], v[:1], cfg.d ** -0.5)
             rest = np.arange(d) != 5
             assert_close(out[l, 0, :g][:, rest], want[:, rest], what=f"step {t} row of {ROWS[l]}", **out_tol(cfg))
+
+
+@pytest.mark.parametrize("dtype,fp8,d,g", [("f32", False, d, g) for d in (64, 128) for g in range(1, 9)] +
+                         [("bf16", fp8, d, g) for fp8 in (False, True) for d in (64, 128) for g in (4, 7)])
+def test_rows_around_the_edges_of_tiles_and_units(dtype, fp8, d, g):
+    """Rows that end before, on and behind a 32-slot tile and a 128-slot unit, of 1 to 11 units, grown by three appends; all bytes of
+    the arena are NaN beforehand, so that what a cache does not hold shows if a tile lets it through."""
+    cfg, path, put, q, kn, vn = _setup(dtype, d, g, fp8, T=3, fill=255)
+    for t in range(3):
+        dq, out = _decode(cfg, path, put, q, kn, vn, t, per_layer=t != 1)
+        for l in range(cfg.L):
+            k, v = _rows(path, l, appended=t + 1)
+            assert_close(out[l, 0], O.decode_attn(dq[l, 0], k, v, cfg.d ** -0.5), what=f"step {t} row of {ROWS[l]}", **out_tol(cfg))
+            if not fp8:                              # the appended row, bit for bit
+                assert np.array_equal(k[:, -1], put(kn[t, l, 0]).double().cpu().numpy()) and np.array_equal(v[:, -1], put(vn[t, l, 0]).double().cpu().numpy())
+    path.status()
 
 
 @pytest.mark.parametrize("merge", [1, 2], ids=["in-kernel", "merge-kernel"])
