@@ -179,8 +179,11 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : RB == 1 ? 6 : 4) void 
 
 // ------------------------------------------------------------------------------------------------
 // Sweep 2: column sums of the softmax over all window rows of the KV group, and per-head counts.
-// CHUNK as above, but every chunk ends in a sum over the waves: 4 waves 44.5 / 43.6 / 43.2 us for 128 / 64 / 32 keys, 8 waves
-// 933 / 970 / 995, 2795 / 3060 / 3300, 16 waves 3100 / 3180 for 128 / 64.
+// CHUNK as above, but every chunk ends in a sum over the waves: for 128 / 64 / 32 keys 8 waves 933 / 970 / 995, 2795 / 3060 / 3300
+// us, 16 waves 3100 / 3180 for 128 / 64.  4 waves: long splits gain by 128 keys, short ones by the block that 64 keys let in
+// (32 rows; KV groups x keys, splits): 352 x 38432 (12928 keys per split) 758 / 882 / 947 us, 256 x 100000 (33408) 1307 / 1296 / 1364,
+// 256 x 10368 (3456) 143 / 140 / 146, 512 x 4096 (2048) 120 / 104 / 108, 256 x 2944 (1024) 36.3 / 35.8 / 36.9, 2048 x 1000 118 / 109 /
+// 114; of 128 rows 834 / 904 / 993, 1375 / 1428 / 1536, 156 / 161 / 171, 153 / 122 / 124, 46.3 / 44.4 / 46.8, 147 / 130 / 130.
 template <int WAVES, int RB, int CHUNK>
 __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 4) void colsweep_mfma_kernel(MfmaArgs a) {   // waves per SIMD: 2 blocks of 8 waves, or 3 of 4
     constexpr int THREADS = WAVES * 64;
@@ -474,7 +477,8 @@ hipError_t launch_colsweep_mfma(const ScoreArgs& a, bool merge_partials) {
         const int nrb = total_rb - rb0 < kMaxRowBlocksPerLaunch ? total_rb - rb0 : kMaxRowBlocksPerLaunch;
         m.rb0 = rb0; m.rb_above = 0;
         m.accumulate = rb0 > 0;                 // launches of one stream run in order: the column sums add up deterministically
-        if (nrb <= 4) colsweep_mfma_kernel<4, 1, 32><<<grid, 256, 0, a.stream>>>(m);
+        if (nrb <= 4 && p.keys_per_split <= 2048) colsweep_mfma_kernel<4, 1, 64><<<grid, 256, 0, a.stream>>>(m);
+        else if (nrb <= 4) colsweep_mfma_kernel<4, 1, kChunk><<<grid, 256, 0, a.stream>>>(m);
         else if (nrb <= 8) colsweep_mfma_kernel<8, 1, kChunk><<<grid, 512, 0, a.stream>>>(m);
         else {
             if (launch_per_class(s)) {
