@@ -15,8 +15,8 @@
 // multiplied).  Sweep 1 packs the window rows of the group's heads into 32-row blocks one after the other (a lane
 // owns a row whatever block it is in, so the statistics have the same bits).  In sweep 2 each head's tau rows are padded to a
 // multiple of 32 so that every 32-row block belongs to one query head, and its sums keep their order; padded rows carry a
-// +inf offset and vanish from every sum, and groups of eight rows that are all padding are left out (the exponentials are
-// what costs power here, and power bounds both sweeps).  256 KV groups of 131072 keys, 4 heads of 50 rows (7 blocks instead of
+// +inf offset and vanish from every sum, and groups of eight rows that are all padding are left out where that pays (SKIP; the
+// exponentials are what costs power here, and power bounds both sweeps).  256 KV groups of 131072 keys, 4 heads of 50 rows (7 blocks instead of
 // 8, 7 of 8 row groups): both sweeps 5990 -> 5600 us; 8 ragged requests of up to 100 rows 1325 -> 1270.
 // In a ragged batch the blocks are those of the request's own window length, dealt to the waves from the first on (and
 // round-robin where a wave takes two), so a shorter window costs the blocks it holds: the waves beyond it only
@@ -184,7 +184,10 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : RB == 1 ? 6 : 4) void 
 // (32 rows; KV groups x keys, splits): 352 x 38432 (12928 keys per split) 758 / 882 / 947 us, 256 x 100000 (33408) 1307 / 1296 / 1364,
 // 256 x 10368 (3456) 143 / 140 / 146, 512 x 4096 (2048) 120 / 104 / 108, 256 x 2944 (1024) 36.3 / 35.8 / 36.9, 2048 x 1000 118 / 109 /
 // 114; of 128 rows 834 / 904 / 993, 1375 / 1428 / 1536, 156 / 161 / 171, 153 / 122 / 124, 46.3 / 44.4 / 46.8, 147 / 130 / 130.
-template <int WAVES, int RB, int CHUNK>
+// SKIP: row groups of padding are left out.  16 waves with / without: 352 groups of 38432 keys, 8 heads of 64 rows 2610 / 2546 us, 1920
+// of 10000, 7 heads of 64 rows 3072 / 3030, 256 of 10368, 8 heads of 50 rows 416 / 410, of 40 rows 399 / 391; but 8 ragged requests of up to
+// 100 rows, where whole windows are short, a compression 1534 / 1541.
+template <int WAVES, int RB, int CHUNK, bool SKIP>
 __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 4) void colsweep_mfma_kernel(MfmaArgs a) {   // waves per SIMD: 2 blocks of 8 waves, or 3 of 4
     constexpr int THREADS = WAVES * 64;
     __shared__ __align__(16) bf16_t sK[CHUNK * kPitch];
@@ -324,7 +327,7 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : 4) void colsweep_mfma_
                         col = fmaf(e, iz[rb][i], col);
                         cnt[rb] += (uint32_t)__popcll(__ballot(valid && ea >= a.log2p));
                     }
-                } else if (rows > 24) {
+                } else if (!SKIP || rows > 24) {
 #pragma unroll
                     for (int i = 0; i < 16; ++i) add(acc[i], rb, i);
                 } else {
@@ -477,16 +480,17 @@ hipError_t launch_colsweep_mfma(const ScoreArgs& a, bool merge_partials) {
         const int nrb = total_rb - rb0 < kMaxRowBlocksPerLaunch ? total_rb - rb0 : kMaxRowBlocksPerLaunch;
         m.rb0 = rb0; m.rb_above = 0;
         m.accumulate = rb0 > 0;                 // launches of one stream run in order: the column sums add up deterministically
-        if (nrb <= 4 && p.keys_per_split <= 2048) colsweep_mfma_kernel<4, 1, 64><<<grid, 256, 0, a.stream>>>(m);
-        else if (nrb <= 4) colsweep_mfma_kernel<4, 1, kChunk><<<grid, 256, 0, a.stream>>>(m);
-        else if (nrb <= 8) colsweep_mfma_kernel<8, 1, kChunk><<<grid, 512, 0, a.stream>>>(m);
+        if (nrb <= 4 && p.keys_per_split <= 2048) colsweep_mfma_kernel<4, 1, 64, true><<<grid, 256, 0, a.stream>>>(m);
+        else if (nrb <= 4) colsweep_mfma_kernel<4, 1, kChunk, true><<<grid, 256, 0, a.stream>>>(m);
+        else if (nrb <= 8) colsweep_mfma_kernel<8, 1, kChunk, true><<<grid, 512, 0, a.stream>>>(m);
         else {
             if (launch_per_class(s)) {
                 m.rb_upto = 8;
-                colsweep_mfma_kernel<8, 1, kChunk><<<grid, 512, 0, a.stream>>>(m);
+                colsweep_mfma_kernel<8, 1, kChunk, true><<<grid, 512, 0, a.stream>>>(m);
                 m.rb_above = 8; m.rb_upto = INT32_MAX;
             }
-            colsweep_mfma_kernel<16, 1, kChunk><<<grid, 1024, 0, a.stream>>>(m);
+            if (s.lens) colsweep_mfma_kernel<16, 1, kChunk, true><<<grid, 1024, 0, a.stream>>>(m);
+            else colsweep_mfma_kernel<16, 1, kChunk, false><<<grid, 1024, 0, a.stream>>>(m);
         }
     }
     return hipGetLastError();
