@@ -64,7 +64,11 @@ __device__ __forceinline__ bool in_class(const MfmaArgs& a, int row_blocks) {
 // CHUNK: keys staged at once.  Small chunks start a block sooner, and their registers (16 for 128 keys) make room for a third
 // 8-wave block per CU.  Chunks of 128 / 64 / 32 keys, profiled: 4 waves (256 KV groups of 2944 keys, 128 rows) 41 / 38 / 35 us,
 // 8 waves (1024 groups of 10368, 256 rows) 934 / 905 / 818, (256 of 131072, 200 rows) 2512 / 2450 / 2350.  Two LDS buffers and
-// one barrier per chunk instead: 37.3, 853, 2389.
+// one barrier per chunk instead: 37.3, 853, 2389.  64 keys in two places, 64 / 32 keys: up
+// to three row blocks in several rounds whose last one six blocks per CU leave the emptier of the two (1024 groups of 10368 keys, 2048
+// blocks, one row block 451 / 485, three 482 / 527; 1920 of 10000, 3840 blocks, 838 / 847, 868 / 877; but 768 of 20000, 1536
+// blocks, 716 / 638, and four row blocks 931 / 893); and two row blocks per wave over more than 8192 keys (256 groups of 100000,
+// 512 rows 3680 / 3770, 64 of 100000 923 / 944).
 // Two row blocks per wave: a K fragment is used for both as it arrives, instead of all eight fragments of a tile being held
 // while one block's chain of products runs and then the other's.  That fits the registers of two blocks per CU: (1920 groups
 // of 10368 keys, 448 rows) 2943 -> 2720 us, (ragged, up to 400 rows) 485 -> 377; within the old registers 3250 and 503.
@@ -180,10 +184,12 @@ __global__ __launch_bounds__(WAVES * 64, WAVES == 4 ? 3 : RB == 1 ? 6 : 4) void 
 // ------------------------------------------------------------------------------------------------
 // Sweep 2: column sums of the softmax over all window rows of the KV group, and per-head counts.
 // CHUNK as above, but every chunk ends in a sum over the waves: for 128 / 64 / 32 keys 8 waves 933 / 970 / 995, 2795 / 3060 / 3300
-// us, 16 waves 3100 / 3180 for 128 / 64.  4 waves: long splits gain by 128 keys, short ones by the block that 64 keys let in
-// (32 rows; KV groups x keys, splits): 352 x 38432 (12928 keys per split) 758 / 882 / 947 us, 256 x 100000 (33408) 1307 / 1296 / 1364,
-// 256 x 10368 (3456) 143 / 140 / 146, 512 x 4096 (2048) 120 / 104 / 108, 256 x 2944 (1024) 36.3 / 35.8 / 36.9, 2048 x 1000 118 / 109 /
-// 114; of 128 rows 834 / 904 / 993, 1375 / 1428 / 1536, 156 / 161 / 171, 153 / 122 / 124, 46.3 / 44.4 / 46.8, 147 / 130 / 130.
+// us, 16 waves 3100 / 3180 for 128 / 64.  4 waves: three blocks of 128 keys or four of 64 fit a CU, and the
+// launch of several rounds takes the form whose rounds are the fuller; in one round short splits gain by the earlier start of 64
+// keys (256 groups of 2944 keys, 1024 per split, 36.3 / 35.8 / 36.9 us, four row blocks 46.3 / 44.4 / 46.8).  In brackets, blocks; one row block: 352 groups of 38432 keys (1056) 758 / 882 / 947,
+// 768 of 20000 (1536) 795 / 878 / 930, 256 of 100000 (768) 1307 / 1296 / 1364, 1920 of 10000 (3840) 985 / 999 / 1047, 1024 of 10368 (2048)
+// 535 / 528 / 557, 512 of 4096 (1024) 120 / 104 / 108, 2048 of 1000 (2048) 118 / 109 / 114; of four row blocks 834 / 904 / 993,
+// 833 / 852 / 962, 1375 / 1428 / 1536, 1057 / 1044 / 1096, 582 / 575 / 607, 153 / 122 / 124, 147 / 130 / 130.
 // SKIP: row groups of padding are left out.  16 waves with / without: 352 groups of 38432 keys, 8 heads of 64 rows 2610 / 2546 us, 1920
 // of 10000, 7 heads of 64 rows 3072 / 3030, 256 of 10368, 8 heads of 50 rows 416 / 410, of 40 rows 399 / 391; but 8 ragged requests of up to
 // 100 rows, where whole windows are short, a compression 1534 / 1541.
@@ -428,6 +434,13 @@ size_t score_mfma_workspace_bytes(const vlc_shape& s) {
     return part_bytes(s, make_plan(s));
 }
 
+// How full a launch's rounds of resident blocks are, with so many of them per CU.
+constexpr int kCUs = 256;
+double round_fill(int64_t blocks, int per_cu) {
+    const int64_t round = (int64_t)per_cu * kCUs;
+    return (double)blocks / (double)((blocks + round - 1) / round * round);
+}
+
 // A launch covers up to 16 row blocks (32 padded window rows each) of every KV group; longer windows
 // take several launches over consecutive row-block ranges.  Block shape by row blocks in the launch:
 // up to 4 -> 4 waves, up to 8 -> 8 waves, else 8 waves x 2 row blocks (sweep 1) or 16 waves (sweep 2).
@@ -451,11 +464,13 @@ hipError_t launch_rowstats_mfma(const ScoreArgs& a) {
     // splits of a group run on one XCD and share its Q' rows in that XCD's L2 (cfg1: 44.7 -> 42.3 us, sweep 2
     // 49.5 -> 45.5 us; no change for shapes whose splits are dispatched rounds apart).
     dim3 grid(groups, p.nsplit);
+    const int64_t blocks = (int64_t)groups * p.nsplit;
     const int total_rb = (m.g * s.tau + 31) / 32;           // the heads' rows are packed
     for (int rb0 = 0; rb0 < total_rb; rb0 += kMaxRowBlocksPerLaunch) {
         const int nrb = total_rb - rb0 < kMaxRowBlocksPerLaunch ? total_rb - rb0 : kMaxRowBlocksPerLaunch;
         m.rb0 = rb0; m.rb_above = 0;
-        if (nrb <= 4) rowstats_mfma_kernel<4, 1, 32><<<grid, 256, 0, a.stream>>>(m);
+        if (nrb <= 3 && blocks > 6 * kCUs && round_fill(blocks, 5) > round_fill(blocks, 6)) rowstats_mfma_kernel<4, 1, 64><<<grid, 256, 0, a.stream>>>(m);
+        else if (nrb <= 4) rowstats_mfma_kernel<4, 1, 32><<<grid, 256, 0, a.stream>>>(m);
         else if (nrb <= 8) rowstats_mfma_kernel<8, 1, 32><<<grid, 512, 0, a.stream>>>(m);
         else {
             if (launch_per_class(s)) {          // the requests with short windows in the form for them
@@ -463,7 +478,9 @@ hipError_t launch_rowstats_mfma(const ScoreArgs& a) {
                 rowstats_mfma_kernel<8, 1, 32><<<grid, 512, 0, a.stream>>>(m);
                 m.rb_above = 8; m.rb_upto = INT32_MAX;
             }
-            rowstats_mfma_kernel<8, 2, 32><<<grid, 512, 0, a.stream>>>(m);        // measured faster than 16 x 1 for this sweep
+            // two row blocks per wave: measured faster than 16 x 1 for this sweep
+            if (p.keys_per_split > 8192) rowstats_mfma_kernel<8, 2, 64><<<grid, 512, 0, a.stream>>>(m);
+            else rowstats_mfma_kernel<8, 2, 32><<<grid, 512, 0, a.stream>>>(m);
         }
     }
     return hipGetLastError();
@@ -475,12 +492,14 @@ hipError_t launch_colsweep_mfma(const ScoreArgs& a, bool merge_partials) {
     MfmaArgs m = make_args(a, p);
     if (merge_partials) m.part_in = m.part;          // sweep 1 ran just before on the same workspace
     dim3 grid(s.B * s.L * s.Hkv, p.nsplit);       // group-major, as in sweep 1
+    const int64_t blocks = (int64_t)s.B * s.L * s.Hkv * p.nsplit;
+    const bool small_chunks = blocks <= 3 * kCUs ? p.keys_per_split <= 2048 : round_fill(blocks, 4) > round_fill(blocks, 3);
     const int total_rb = p.RP / 32;
     for (int rb0 = 0; rb0 < total_rb; rb0 += kMaxRowBlocksPerLaunch) {
         const int nrb = total_rb - rb0 < kMaxRowBlocksPerLaunch ? total_rb - rb0 : kMaxRowBlocksPerLaunch;
         m.rb0 = rb0; m.rb_above = 0;
         m.accumulate = rb0 > 0;                 // launches of one stream run in order: the column sums add up deterministically
-        if (nrb <= 4 && p.keys_per_split <= 2048) colsweep_mfma_kernel<4, 1, 64, true><<<grid, 256, 0, a.stream>>>(m);
+        if (nrb <= 4 && small_chunks) colsweep_mfma_kernel<4, 1, 64, true><<<grid, 256, 0, a.stream>>>(m);
         else if (nrb <= 4) colsweep_mfma_kernel<4, 1, kChunk, true><<<grid, 256, 0, a.stream>>>(m);
         else if (nrb <= 8) colsweep_mfma_kernel<8, 1, kChunk, true><<<grid, 512, 0, a.stream>>>(m);
         else {

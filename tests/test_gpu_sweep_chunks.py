@@ -9,12 +9,14 @@ pytestmark = pytest.mark.gpu
 # keys per split: 768 / groups splits (at least two from 16 chunks of 128 keys on), in whole chunks
 @pytest.mark.parametrize("L,Hkv,g,m,tau", [
     (1, 1, 2, 2049, 20),             # splits of one chunk
-    (64, 8, 1, 4096, 32),            # 2048 keys per split: the last with chunks of 64 in sweep 2
-    (64, 8, 3, 4097, 32),            # 2176: the first with chunks of 128
+    (64, 8, 1, 4096, 32),            # 512 groups, two splits: one full round of four blocks of 64 keys per CU in sweep 2
+    (64, 8, 3, 4097, 32),            # 2176 keys per split
     (64, 8, 4, 4200, 7),             # the last split ends in the middle of a chunk
-    (128, 6, 1, 1000, 33),           # 768 groups, one split
-    (128, 6, 2, 2200, 32),           # 768 groups: chunks of 64 in sweep 1 for up to two row blocks
-    (128, 6, 3, 2200, 32),           # three
+    (128, 6, 1, 1000, 33),           # 768 groups, one split: chunks of 128 keys in sweep 2
+    (128, 6, 3, 2200, 32),           # two splits, 1536 blocks: one round of sweep 1's blocks of 32 keys
+    (128, 8, 2, 2200, 32),           # 2048 blocks: of 64 keys for up to three row blocks
+    (128, 8, 3, 2201, 31),
+    (128, 8, 4, 2200, 32),           # four
     (127, 6, 1, 2200, 64),           # 762 groups
     (96, 8, 8, 16500, 64),           # 16 row blocks, 8320 keys per split: sweep 1's long form
     (96, 8, 5, 16300, 57),           # 8192
