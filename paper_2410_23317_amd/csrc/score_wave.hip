@@ -47,7 +47,6 @@ struct SweepArgs {
     float log2p, default_scale;
     int L, Hq, Hkv, g, m, tau, keys_per_split, nsplit;
     int head_shift;          // shared blocks: log2 of the rows a head is padded to
-    int packed;              // sweep 1: the heads' rows follow each other, a block may hold rows of several heads
     int rb0;                 // first 32-row block of this launch
     int accumulate;          // sweep 2: add to scores instead of overwriting (row groups after the first)
 };
@@ -81,20 +80,23 @@ __device__ __forceinline__ LogitScale logit_scale(const SweepArgs& a, int l) {
     return s;
 }
 
+// PACKED (sweep 1): the heads' rows follow each other, a block may hold rows of several heads.  A parameter of the code, not of the launch:
+// looked at there, it cost every launch of a window that takes several 0.5 to 1 us (8 KV groups of 500 keys, 7 heads of 40 rows in
+// fp32, d = 128: four launches, 112.2 -> 118.5).
 // What the blocks of one (request, layer, KV head) share.
 struct Where {
     int hkv, bl, l, mb, tb, nb, nrb;        // nb: 32-row blocks per head, nrb: row blocks of this launch
     int k_begin, k_end, nt;                 // key range of the split, its 32-key tiles
     LogitScale ls;
 };
-template <typename F>
+template <typename F, bool PACKED>
 __device__ __forceinline__ Where locate(const SweepArgs& a, int group, int split) {
     Where w;
     w.hkv = group % a.Hkv; w.bl = group / a.Hkv; w.l = w.bl % a.L;
     const ReqLen rl = request_len(a.lens, w.bl / a.L, a.m, a.tau);
     w.mb = rl.m; w.tb = rl.tau;                             // this request's prompt and window length
     w.nb = (w.tb + 31) >> 5;
-    w.nrb = F::SHARED ? ((a.g << a.head_shift) + 31) >> 5 : a.packed ? (a.g * w.tb + 31) >> 5 : min(a.g * w.nb - a.rb0, F::NRB);
+    w.nrb = F::SHARED ? ((a.g << a.head_shift) + 31) >> 5 : PACKED ? (a.g * w.tb + 31) >> 5 : min(a.g * w.nb - a.rb0, F::NRB);
     w.k_begin = split * a.keys_per_split;
     w.k_end = min(w.mb, w.k_begin + a.keys_per_split);
     w.nt = w.k_end > w.k_begin ? (w.k_end - w.k_begin + 31) >> 5 : 0;
@@ -120,7 +122,7 @@ __device__ __forceinline__ float exp2_rest(float a, double b) { return fabsf(a) 
 
 // Row r of the launch's row blocks: its head, its window row, and whether it exists.
 struct Row { int hl, iw; bool real; };
-template <typename F>
+template <typename F, bool PACKED>
 __device__ __forceinline__ Row window_row(const SweepArgs& a, const Where& w, int r) {
     Row o;
     if (F::SHARED) {
@@ -129,7 +131,7 @@ __device__ __forceinline__ Row window_row(const SweepArgs& a, const Where& w, in
         o.real = o.hl < a.g && o.iw < w.tb;
         return o;
     }
-    if (a.packed) {
+    if (PACKED) {
         o.hl = r / w.tb;
         o.iw = r - o.hl * w.tb;
         o.real = o.hl < a.g;
@@ -160,13 +162,13 @@ __device__ __forceinline__ void load_keys(const char* kg, int key0, int mb, int 
 // The block's Q' rows into LDS.  A row that does not exist takes the values of its head's last row, which sees every key:
 // its products are then the numbers of a row that exists, and drop out by an exponent of -inf (zeros would not: times a
 // key's infinite entry they are NaN).  All requests of a thread are in flight together.
-template <typename F>
+template <typename F, bool PACKED>
 __device__ __forceinline__ void stage_q(const SweepArgs& a, const Where& w, char* sQ) {
     uint4 q[F::NQ];
 #pragma unroll
     for (int u = 0; u < F::NQ; ++u) {
         const int x = threadIdx.x + F::THREADS * u, r = x / F::CPR;
-        const Row o = window_row<F>(a, w, r);
+        const Row o = window_row<F, PACKED>(a, w, r);
         const char* src = a.q_win + (((size_t)w.bl * a.Hq + (size_t)w.hkv * a.g + min(o.hl, a.g - 1)) * a.tau + min(o.iw, w.tb - 1)) * F::RBYTES;
         q[u] = *reinterpret_cast<const uint4*>(src + (x % F::CPR) * 16);
     }
@@ -208,21 +210,21 @@ __device__ __forceinline__ f32x16_t tile_product(const char* sQ, int rb, int lan
 
 // ------------------------------------------------------------------------------------------------
 // Sweep 1: partial row statistics of one key range of one KV group.
-template <typename F>
+template <typename F, bool PACKED>
 __global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void rowstats_wave_kernel(SweepArgs a) {
     constexpr int RBYTES = F::RBYTES, NRB = F::NRB, W = F::W, KS = F::KS;
     constexpr int QBYTES = F::ROWS * F::PITCH, MBYTES = W * F::ROWS * (int)sizeof(float2);
     __shared__ __align__(16) char smem[QBYTES > MBYTES ? QBYTES : MBYTES];      // Q' rows; after the sweep the waves' statistics
     const int group = blockIdx.x, split = blockIdx.y;       // group-major: see the launch
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;     // wave index in a scalar register
-    const Where w = locate<F>(a, group, split);
+    const Where w = locate<F, PACKED>(a, group, split);
     if (a.nnz && split == 0 && a.rb0 == 0 && (int)threadIdx.x < a.g)
         a.nnz[(size_t)w.bl * a.Hq + (size_t)w.hkv * a.g + threadIdx.x] = 0;      // sweep 2 adds into these
     if (w.nrb <= 0) return;                                 // a shorter window than the longest of the batch
     const char* kg = a.k + (size_t)group * a.m * RBYTES;
     uint4 kf[KS];
     if (wave < w.nt) load_keys<KS, RBYTES>(kg, w.k_begin + wave * 32, w.mb, lane, kf);
-    stage_q<F>(a, w, smem);
+    stage_q<F, PACKED>(a, w, smem);
     __syncthreads();
     float m_run[NRB], z_run[NRB];                           // this lane's row of each row block, over the keys its half holds
 #pragma unroll
@@ -242,7 +244,7 @@ __global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void rowstats_wave_k
                 if (masked) {                               // last key this lane's row may see (causal mask of Alg. 1)
                     int rbg = a.rb0 + rb;
                     asm volatile("" : "+s"(rbg));           // computed here: hoisted, the limits of all row blocks would take registers
-                    const int iw = a.packed ? (rbg * 32 + (lane & 31)) % w.tb : lane_row<F>(a, rbg % w.nb, lane);
+                    const int iw = PACKED ? (rbg * 32 + (lane & 31)) % w.tb : lane_row<F>(a, rbg % w.nb, lane);
                     const int jlim = min(w.mb - w.tb + iw, w.mb - 1) - key0;
 #pragma unroll
                     for (int i = 0; i < 16; ++i) v[i] = acc_row(i, lane) <= jlim ? v[i] : -INFINITY;
@@ -274,7 +276,7 @@ __global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void rowstats_wave_k
     }
     __syncthreads();
     const int r = threadIdx.x;
-    const Row o = window_row<F>(a, w, r);
+    const Row o = window_row<F, PACKED>(a, w, r);
     if (r < F::ROWS && o.real) {
         float M = -INFINITY, Z = 0.f;
 #pragma unroll
@@ -326,12 +328,12 @@ __global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void colsweep_wave_k
     __shared__ uint32_t sRow[F::SHARED ? F::ROWS : 1];      // shared blocks: per row
     const int group = blockIdx.x, split = blockIdx.y;       // group-major: see the launch
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;     // wave index in a scalar register
-    const Where w = locate<F>(a, group, split);
+    const Where w = locate<F, false>(a, group, split);
     if (w.nrb <= 0) return;
     const char* kg = a.k + (size_t)group * a.m * RBYTES;
     // Order of the first requests: the few bytes of the statistics go out first (every block of the launch starts at
     // once, and behind the K bursts they would wait), then the first K tile, then Q'.
-    const Row o = window_row<F>(a, w, (int)threadIdx.x);
+    const Row o = window_row<F, false>(a, w, (int)threadIdx.x);
     const bool mine = (int)threadIdx.x < F::ROWS && o.real;
     constexpr int kSplitRegs = 4;                           // splits whose partials a thread holds at once (more are merged in rounds)
     float2 pin[kSplitRegs];
@@ -343,7 +345,7 @@ __global__ __launch_bounds__(F::THREADS, F::WAVES_PER_SIMD) void colsweep_wave_k
     }
     uint4 kf[KS];
     if (wave < w.nt) load_keys<KS, RBYTES>(kg, w.k_begin + wave * 32, w.mb, lane, kf);
-    stage_q<F>(a, w, sQ);
+    stage_q<F, false>(a, w, sQ);
     if (threadIdx.x < 8) sCnt[threadIdx.x] = 0;
     if (F::SHARED && (int)threadIdx.x < F::ROWS) sRow[threadIdx.x] = 0;
     if ((int)threadIdx.x < F::ROWS) {
@@ -526,15 +528,16 @@ SweepArgs make_args(const ScoreArgs& a, const Plan& p) {
     m.L = s.L; m.Hq = s.Hq; m.Hkv = s.Hkv; m.g = s.Hq / s.Hkv; m.m = s.m; m.tau = s.tau;
     m.keys_per_split = p.keys_per_split; m.nsplit = p.nsplit;
     m.head_shift = p.head_shift;
-    m.packed = 0; m.rb0 = 0; m.accumulate = 0;
+    m.rb0 = 0; m.accumulate = 0;
     return m;
 }
 
 template <bool SWEEP1, bool F32, int RBYTES, int NRB, int W, bool SHARED = false>
-void launch_form(const SweepArgs& m, dim3 grid, hipStream_t st) {
+void launch_form(const SweepArgs& m, bool packed, dim3 grid, hipStream_t st) {
     using F = Form<F32, RBYTES, NRB, W, SHARED>;
-    if (SWEEP1) rowstats_wave_kernel<F><<<grid, F::THREADS, 0, st>>>(m);
-    else colsweep_wave_kernel<F><<<grid, F::THREADS, 0, st>>>(m);
+    if (!SWEEP1) colsweep_wave_kernel<F><<<grid, F::THREADS, 0, st>>>(m);
+    else if (!SHARED && packed) rowstats_wave_kernel<F, !SHARED><<<grid, F::THREADS, 0, st>>>(m);
+    else rowstats_wave_kernel<F, false><<<grid, F::THREADS, 0, st>>>(m);
 }
 
 // Windows of more row blocks than a launch holds take several launches over consecutive row-block ranges.  Group-major
@@ -549,26 +552,26 @@ hipError_t launch_sweep(SweepArgs m, const Plan& p, const vlc_shape& s, hipStrea
     // other (with the form, and with it each row's order of additions, chosen as for blocks of one head).  192 KV groups of 4096
     // keys, 4 heads of 50 rows of 64 in bf16, 7 blocks instead of 8: a
     // whole compression 152.1 -> 146.5 us.
-    m.packed = SWEEP1 && p.head_shift < 0 && p.nrb <= step;
+    const bool packed = SWEEP1 && p.head_shift < 0 && p.nrb <= step;
     for (int rb0 = 0; rb0 < p.nrb; rb0 += step) {
         const int nrb = p.nrb - rb0 < step ? p.nrb - rb0 : step;
         m.rb0 = rb0;
         m.accumulate = rb0 > 0;                 // launches of one stream run in order: the column sums add up deterministically
         if (p.head_shift >= 0) {                // at most 8 heads of 16 rows
-            if (s.dtype == VLC_F32 && s.d == 128) launch_form<SWEEP1, true, 512, 4, 8, true>(m, grid, st);
-            else if (s.dtype == VLC_F32) launch_form<SWEEP1, true, 256, 4, 8, true>(m, grid, st);
-            else launch_form<SWEEP1, false, 128, 4, 8, true>(m, grid, st);
+            if (s.dtype == VLC_F32 && s.d == 128) launch_form<SWEEP1, true, 512, 4, 8, true>(m, packed, grid, st);
+            else if (s.dtype == VLC_F32) launch_form<SWEEP1, true, 256, 4, 8, true>(m, packed, grid, st);
+            else launch_form<SWEEP1, false, 128, 4, 8, true>(m, packed, grid, st);
         } else if (s.dtype == VLC_F32 && s.d == 128) {
-            if (nrb <= 4) launch_form<SWEEP1, true, 512, 4, 8>(m, grid, st);
-            else launch_form<SWEEP1, true, 512, 8, 8>(m, grid, st);
+            if (nrb <= 4) launch_form<SWEEP1, true, 512, 4, 8>(m, packed, grid, st);
+            else launch_form<SWEEP1, true, 512, 8, 8>(m, packed, grid, st);
         } else if (s.dtype == VLC_F32) {
-            if (nrb <= 4) launch_form<SWEEP1, true, 256, 4, 8>(m, grid, st);
-            else if (nrb <= 8) launch_form<SWEEP1, true, 256, 8, 8>(m, grid, st);
-            else launch_form<SWEEP1, true, 256, 16, 16>(m, grid, st);
+            if (nrb <= 4) launch_form<SWEEP1, true, 256, 4, 8>(m, packed, grid, st);
+            else if (nrb <= 8) launch_form<SWEEP1, true, 256, 8, 8>(m, packed, grid, st);
+            else launch_form<SWEEP1, true, 256, 16, 16>(m, packed, grid, st);
         } else {
-            if (nrb <= 4) launch_form<SWEEP1, false, 128, 4, 8>(m, grid, st);
-            else if (nrb <= 8) launch_form<SWEEP1, false, 128, 8, 8>(m, grid, st);
-            else launch_form<SWEEP1, false, 128, 16, 8>(m, grid, st);
+            if (nrb <= 4) launch_form<SWEEP1, false, 128, 4, 8>(m, packed, grid, st);
+            else if (nrb <= 8) launch_form<SWEEP1, false, 128, 8, 8>(m, packed, grid, st);
+            else launch_form<SWEEP1, false, 128, 16, 8>(m, packed, grid, st);
         }
     }
     return hipGetLastError();
