@@ -211,37 +211,36 @@ __global__ __launch_bounds__(WAVES * 64, 2) void window_attn_kernel(WinArgs a) {
     if (lane < 32) a.part_ms[prow] = make_float2(m_run, z);
 }
 
-// Merge of the per-split partials: 32 lanes (4 d-values each) per row, 32 rows per block.
-__global__ __launch_bounds__(256) void window_attn_merge_kernel(WinArgs a, int groups) {
-    const int sub = threadIdx.x >> 5, lane = threadIdx.x & 31;
-    for (int it = 0; it < 4; ++it) {
-        const size_t x = ((size_t)blockIdx.x * 4 + it) * 8 + sub;      // (group, row)
-        if (x >= (size_t)groups * a.R) return;
-        const int r = (int)(x % a.R), group = (int)(x / a.R);
-        const int hkv = group % a.Hkv, bl = group / a.Hkv;
-        const int tb = request_len(a.lens, bl / a.L, a.m, a.tau).tau;
-        const int hl = r / tb, iw = r % tb;
-        if (hl >= a.g) continue;
-        float M = -INFINITY;
-        for (int s = 0; s < a.nsplit; ++s) M = fmaxf(M, a.part_ms[((size_t)group * a.nsplit + s) * a.R + r].x);
-        float Z = 0.f;
-        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int s = 0; s < a.nsplit; ++s) {
-            const size_t prow = ((size_t)group * a.nsplit + s) * a.R + r;
-            const float2 ms = a.part_ms[prow];
-            if (!(ms.x > -INFINITY)) continue;                         // this split saw no key of the row
-            const float w = exp2_fast(ms.x - M);
-            const float4 po = *reinterpret_cast<const float4*>(a.part_o + prow * kD + lane * 4);
-            Z += ms.y * w;
-            acc.x = fmaf(po.x, w, acc.x); acc.y = fmaf(po.y, w, acc.y); acc.z = fmaf(po.z, w, acc.z); acc.w = fmaf(po.w, w, acc.w);
-        }
-        const size_t orow = ((size_t)bl * a.Hq + (size_t)hkv * a.g + hl) * a.tau + iw;
-        const float inv = 1.f / Z;
-        const uint32_t lo = f32_to_bf16_bits(acc.x * inv) | (f32_to_bf16_bits(acc.y * inv) << 16);
-        const uint32_t hi = f32_to_bf16_bits(acc.z * inv) | (f32_to_bf16_bits(acc.w * inv) << 16);
-        *reinterpret_cast<uint2*>(a.out + orow * kD + lane * 4) = make_uint2(lo, hi);
-        if (lane == 0) { a.row_max[orow] = M * kLn2; a.row_sum[orow] = Z; }
+// Merge of the per-split partials: 32 lanes (4 d-values each) per row, 8 rows per block.  A row is a chain of loads over its splits, so
+// rows go side by side, not one after the other (16 KV groups of 100000 keys in 32 splits, 8 rows, whole call 239 us with four
+// rows per 32 lanes, 178 with one).
+__global__ __launch_bounds__(256) void window_attn_merge_kernel(WinArgs a, int rows) {
+    const int x = blockIdx.x * 8 + (threadIdx.x >> 5), lane = threadIdx.x & 31;         // (group, row)
+    if (x >= rows) return;
+    const int r = x % a.R, group = x / a.R;
+    const int hkv = group % a.Hkv, bl = group / a.Hkv;
+    const int tb = request_len(a.lens, bl / a.L, a.m, a.tau).tau;
+    const int hl = r / tb, iw = r % tb;
+    if (hl >= a.g) return;
+    float M = -INFINITY;
+    for (int s = 0; s < a.nsplit; ++s) M = fmaxf(M, a.part_ms[((size_t)group * a.nsplit + s) * a.R + r].x);
+    float Z = 0.f;
+    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int s = 0; s < a.nsplit; ++s) {
+        const size_t prow = ((size_t)group * a.nsplit + s) * a.R + r;
+        const float2 ms = a.part_ms[prow];
+        if (!(ms.x > -INFINITY)) continue;                         // this split saw no key of the row
+        const float w = exp2_fast(ms.x - M);
+        const float4 po = *reinterpret_cast<const float4*>(a.part_o + prow * kD + lane * 4);
+        Z += ms.y * w;
+        acc.x = fmaf(po.x, w, acc.x); acc.y = fmaf(po.y, w, acc.y); acc.z = fmaf(po.z, w, acc.z); acc.w = fmaf(po.w, w, acc.w);
     }
+    const size_t orow = ((size_t)bl * a.Hq + (size_t)hkv * a.g + hl) * a.tau + iw;
+    const float inv = 1.f / Z;
+    const uint32_t lo = f32_to_bf16_bits(acc.x * inv) | (f32_to_bf16_bits(acc.y * inv) << 16);
+    const uint32_t hi = f32_to_bf16_bits(acc.z * inv) | (f32_to_bf16_bits(acc.w * inv) << 16);
+    *reinterpret_cast<uint2*>(a.out + orow * kD + lane * 4) = make_uint2(lo, hi);
+    if (lane == 0) { a.row_max[orow] = M * kLn2; a.row_sum[orow] = Z; }
 }
 
 struct WinPlan { int R, nsplit, keys_per_split; };
@@ -301,9 +300,9 @@ hipError_t launch_window_attn(const WindowAttnArgs& w) {
         else window_attn_kernel<8><<<grid, 512, 0, w.stream>>>(a);
     }
     if (p.nsplit > 1) {
-        const size_t n = (size_t)groups * p.R;
+        const int n = groups * p.R;             // fewer than 512 groups of up to 8 * 4096 rows
         a.rb0 = 0;
-        window_attn_merge_kernel<<<(unsigned)((n + 31) / 32), 256, 0, w.stream>>>(a, groups);
+        window_attn_merge_kernel<<<(n + 7) / 8, 256, 0, w.stream>>>(a, n);
     }
     return hipGetLastError();
 }
