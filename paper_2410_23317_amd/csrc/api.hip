@@ -303,6 +303,7 @@ struct ArenaPlan {
     vlc_cache_options opt;      // resolved
     size_t items_off[vlc::kNumLists], layer_start_off[vlc::kNumLists], row_first_off[vlc::kNumLists], heads_off, partials_off, counters_off, readers_off, lens_off;
     int64_t cap[vlc::kNumLists];
+    int32_t partial_slots;
 };
 
 static bool one_of(int v, std::initializer_list<int> ok) {
@@ -408,8 +409,10 @@ static vlc_status cache_layout(const vlc_shape* s, int32_t T_max, int64_t sum_k_
             return fail(VLC_ERR_SHAPE, "cache of %lld decode units: budgets plus reserved appends are too large", (long long)plan->cap[i]);
     plan->opt = o;
     const int g = s->Hq / s->Hkv;
-    // partial results of decode: a row has at most one unit per kMinUnitSlots slots of its slab, and one for the remainder
-    const int64_t partials = (int64_t)s->B * spr * s->Hkv / vlc::kMinUnitSlots + (int64_t)BL * s->Hkv;
+    // partial results of decode: a row has at most one unit per so many slots of its slab as the smallest unit of the decode lists
+    // holds, and one for the remainder
+    plan->partial_slots = o.layer_unit_slots < o.tail_unit_slots ? o.layer_unit_slots : o.tail_unit_slots;
+    const int64_t partials = (int64_t)s->B * spr * s->Hkv / plan->partial_slots + (int64_t)BL * s->Hkv;
     size_t off = 0;
     lay->status_off = off;      off = align_up(off + 4 * sizeof(int32_t), 256);
     lay->slot_off_off = off;    off = align_up(off + BL * sizeof(int64_t), 256);
@@ -500,6 +503,7 @@ static vlc_status cache_create_common(const char* who, const vlc_shape* shape, i
     c->layout.list_reserved = 0;
     c->dev.heads = (vlc::WorkItem*)(c->arena + plan.heads_off);
     c->dev.partials = (float*)(c->arena + plan.partials_off);
+    c->dev.partial_slots = plan.partial_slots;
     c->dev.counters = (int32_t*)(c->arena + plan.counters_off);
     c->dev.readers = (int32_t*)(c->arena + plan.readers_off);
     c->dev.lens = (int32_t*)(c->arena + plan.lens_off);

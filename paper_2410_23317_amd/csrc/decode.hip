@@ -54,6 +54,7 @@ struct DecodeParams {
     float* scales;
     int32_t* status;
     int ub_shift, us_shift;  // log2 of the list's unit sizes
+    int part_shift;          // log2 of the slots that a row has a partial for
     int B, L, Hq, Hkv, m;
     int layer_begin, n_layers, T_max;
     int append_mode;         // 0: attend only; 1: k_new / v_new are appended by this kernel
@@ -82,9 +83,9 @@ __device__ __forceinline__ int32_t add_agent(int32_t* p, int32_t v) {
     return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Place of a row's first partial result: a row owns a partial for every kMinUnitSlots slots of its slab, and one more.
+// Place of a row's first partial result: a row owns a partial for every 1 << shift slots of its slab, and one more.
 // (Rows follow each other in the slot order, so the ranges of two rows never meet, whatever the unit sizes.)
-__device__ __forceinline__ int64_t first_partial(int64_t idx_base, int row_abs) { return idx_base / kMinUnitSlots + row_abs; }
+__device__ __forceinline__ int64_t first_partial(int64_t idx_base, int row_abs, int shift) { return (idx_base >> shift) + row_abs; }
 
 // 1 / l and o / l as the outputs of type T want them: to the last bit where they keep 32, and by v_rcp_f32, which is within an
 // ulp of that, where they are rounded to bf16.
@@ -807,7 +808,7 @@ __global__ __launch_bounds__(256, (IsBf16<T>::value ? (D == 64 && !Q8 ? 4 : 3) :
         __syncthreads();
         // every thread merges two neighbouring output elements of one head over the waves' shares in sMerge: one weight
         // per wave, one store; into the output, or into the unit's partial
-        float* part = A.partials + (first_partial(idx_base, row_abs) + unit) * PS;
+        float* part = A.partials + (first_partial(idx_base, row_abs, A.part_shift) + unit) * PS;
         auto merge_waves = [&](bool whole) {
             for (int x = tid; x < G * D / 2; x += THREADS) {
                 const int h = x / (D / 2), e = (x % (D / 2)) * 2;
@@ -976,7 +977,7 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(DecodeParams P) {
     if (nu == 1) return;
     T* outp = reinterpret_cast<T*>(P.out) + ((size_t)(lr * P.B + b) * P.Hq + (size_t)hkv * G) * D;
     const int64_t idx_base = P.slot_off[bl] * P.Hkv + (int64_t)hkv * (kept + P.T_max);
-    merge_partials<T, D, G, 256>(P.partials + first_partial(idx_base, bl * P.Hkv + hkv) * partial_floats(G, D), outp, nu, threadIdx.x);
+    merge_partials<T, D, G, 256>(P.partials + first_partial(idx_base, bl * P.Hkv + hkv, P.part_shift) * partial_floats(G, D), outp, nu, threadIdx.x);
 }
 
 template <typename T, int D, int G>
@@ -1032,6 +1033,7 @@ hipError_t launch_decode(const DecodeArgs& a) {
     P.wl = c.dev.list[all_layers ? 1 : 0];
     P.heads = !all_layers && a.n_layers == 1 ? c.dev.heads + (size_t)a.layer_begin * kHeadUnits : nullptr;
     P.ub_shift = log2i(P.wl.u_big); P.us_shift = log2i(P.wl.u_small);
+    P.part_shift = log2i(c.dev.partial_slots);
     P.B = s.B; P.L = s.L; P.Hq = s.Hq; P.Hkv = s.Hkv; P.m = s.m;
     P.layer_begin = a.layer_begin; P.n_layers = a.n_layers; P.T_max = c.T_max;
     P.append_mode = a.k_new ? 1 : 0;

@@ -41,8 +41,7 @@ struct WorkItem {
 };
 static_assert(sizeof(WorkItem) == 64, "WorkItem layout: one 64-byte scalar load");
 
-constexpr int kMinUnitSlots = 128;      // smallest and
-constexpr int kMaxUnitSlots = 2048;     // largest block-unit of a work list (the options admit no others)
+constexpr int kMaxUnitSlots = 2048;     // largest block-unit of a work list (the options admit 128 .. 2048)
 // floats of a unit's partial result: g unnormalised outputs of d values, then g pairs (max, sum); whole 16-byte pieces
 constexpr int partial_floats(int g, int d) { return (g * (d + 2) + 3) & ~3; }
 constexpr int kNumLists = 3;
@@ -66,7 +65,8 @@ struct CacheDev {                      // device pointers into the caller's aren
     int32_t* idx;
     WorkItem* heads;                  // [L][kHeadUnits] copies of the first records of each layer in list 0: found without the layer index
     WorkList list[kNumLists];         // 0: launches over a layer range, 1: launches over all layers, 2: the gather
-    float* partials;                   // [a unit per kMinUnitSlots slots, and one per row][partial_floats(g, d)]
+    float* partials;                   // [a unit per partial_slots slots, and one per row][partial_floats(g, d)]
+    int32_t partial_slots;             // slots of the smallest unit of lists 0 and 1, a power of two
     int32_t* counters;                 // [B*L*Hkv] units of a row that have left their partial result
     int32_t* appended;                 // [L] appends each layer has received since the last compaction
     int32_t* readers;                  // [(L + 1) * kReaderStride] blocks of a launch that have read the append count: per layer, and per launch after the last layer

@@ -169,6 +169,23 @@ def test_default_unit_sizes_of_the_benchmark_shapes(V):
         assert (lay.unit_slots, lay.tail_unit_slots, lay.layer_unit_slots) == units, cid
 
 
+@pytest.mark.parametrize("units,smallest", [((128, 128, 128), 128), ((1024, 512, 512), 512), ((2048, 128, 2048), 128), ((2048, 2048, 1024), 1024)])
+def test_the_arena_holds_the_partial_results_of_its_own_units(V, units, smallest):
+    """Partial results are reserved for the smallest unit of the cache's decode lists, not for the smallest there could be."""
+    B, L, Hkv, g, d, m, T, sum_k = 2, 8, 8, 4, 128, 65536, 100, 8 * 6554
+    s = V.make_shape(B, L, Hkv * g, Hkv, d, m, 50, "bf16")
+    o = V.make_options(unit_slots=units[0], tail_unit_slots=units[1], layer_unit_slots=units[2])
+    n = V.lib.vlc_cache_bytes_opt(C.byref(s), T, sum_k, C.byref(o))
+    cache = C.c_void_p()
+    assert V.lib.vlc_cache_create_opt(C.byref(s), T, sum_k, C.byref(o), 4096, n, C.byref(cache)) == V.VLC_OK
+    lay = V.vlc_cache_layout()
+    assert V.lib.vlc_cache_get_layout(cache, C.byref(lay)) == V.VLC_OK
+    V.lib.vlc_cache_destroy(cache)
+    partials = (B * lay.slots_per_request * Hkv // smallest + B * L * Hkv) * (g * (d + 2)) * 4
+    rest = lay.total_bytes - lay.list_index_off[2]               # behind the work lists: copies of records, partials, counters
+    assert partials <= rest <= partials + L * 256 * 64 + 64 * 1024, (rest, partials)
+
+
 def test_shape_flags(V):
     s = V.make_shape(1, 2, 8, 2, 128, 3000, 32, "bf16")
     plain = V.make_shape(1, 2, 8, 2, 128, 3000, 32, "bf16", flags=V.VLC_SHAPE_SCORE_PLAIN_ALU)
