@@ -241,7 +241,9 @@ __device__ void layout_body(const LayoutArgs& a, CacheDev dev, int lists, int sh
             // units of the third class that precede this row's in the list (all units before it minus big and live)
             const int res0 = n_big + n_live + sResFirst[bl] + h * nres;
             if (ul == 0 && !heads) wl.row_first[x] = w0;
-            for (int u = ul; u < ru.total; u += 1 << lg) {
+            // the copies end with the layer's first units: rows behind them are left at once
+            const int at = w0 - sFirst[l], n = heads ? min(ru.total, kHeadUnits - at) : ru.total;
+            for (int u = ul; u < n; u += 1 << lg) {
                 it.unit = u;
                 it.key0 = u < ru.big ? u * ub : ru.big * ub + (u - ru.big) * us;
                 it.ucap = u < ru.big ? ub : us;
@@ -253,7 +255,7 @@ __device__ void layout_body(const LayoutArgs& a, CacheDev dev, int lists, int sh
                     else ws = res0 + (u - ru.big - ru.live);
                 }
                 if (!heads) wl.items[ws] = it;
-                else if (w0 + u - sFirst[l] < kHeadUnits) heads[l * kHeadUnits + w0 + u - sFirst[l]] = it;
+                else heads[l * kHeadUnits + at + u] = it;
             }
         }
     };
