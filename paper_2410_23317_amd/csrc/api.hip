@@ -301,7 +301,7 @@ vlc_status vlc_sparsity_allocate(const vlc_shape* shape, const uint64_t* nnz, fl
 struct ArenaPlan {
     vlc_cache_layout lay;
     vlc_cache_options opt;      // resolved
-    size_t items_off[vlc::kNumLists], layer_start_off[vlc::kNumLists], row_first_off[vlc::kNumLists], heads_off, partials_off, counters_off, readers_off, lens_off;
+    size_t items_off[vlc::kNumLists], layer_start_off[vlc::kNumLists], heads_off, partials_off, counters_off, readers_off, lens_off;
     int64_t cap[vlc::kNumLists];
     int32_t partial_slots;
 };
@@ -424,7 +424,6 @@ static vlc_status cache_layout(const vlc_shape* s, int32_t T_max, int64_t sum_k_
     for (int i = 0; i < vlc::kNumLists; ++i) {
         plan->items_off[i] = off;        off = align_up(off + (size_t)plan->cap[i] * sizeof(vlc::WorkItem), 256);
         plan->layer_start_off[i] = off;  off = align_up(off + (size_t)(s->L + 2) * sizeof(int32_t), 256);
-        plan->row_first_off[i] = off;    off = align_up(off + BL * s->Hkv * sizeof(int32_t), 256);
     }
     plan->heads_off = off;        off = align_up(off + (size_t)s->L * vlc::kHeadUnits * sizeof(vlc::WorkItem), 256);
     plan->partials_off = off;     off = align_up(off + (size_t)partials * vlc::partial_floats(g, s->d) * sizeof(float), 256);
@@ -484,7 +483,6 @@ static vlc_status cache_create_common(const char* who, const vlc_shape* shape, i
         vlc::WorkList& wl = c->dev.list[i];
         wl.items = (vlc::WorkItem*)(c->arena + plan.items_off[i]);
         wl.layer_start = (int32_t*)(c->arena + plan.layer_start_off[i]);
-        wl.row_first = (int32_t*)(c->arena + plan.row_first_off[i]);
         wl.u_big = i == 0 ? plan.opt.layer_unit_slots : (i == 1 ? plan.opt.unit_slots : vlc::kGatherUnit);
         wl.u_small = i == 0 ? plan.opt.layer_unit_slots : (i == 1 ? plan.opt.tail_unit_slots : vlc::kGatherUnit);
         wl.by_size = i == 1 && plan.opt.decode_order == 2;

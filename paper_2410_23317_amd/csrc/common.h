@@ -13,7 +13,6 @@ constexpr float kLn2 = 0.6931471805599453f;
 constexpr int kWave = 64;
 
 typedef uint16_t bf16_t;                       // raw bfloat16 bits
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;

@@ -33,7 +33,7 @@ struct WorkItem {
     int64_t kbase;                     // element offset of the row's K slab inside the kv region
     int64_t idx_base;                  // offset of the row's kept-index list inside the idx region
     int32_t b, l;
-    int32_t canon;                     // index of this unit in the (layer, request, kv head, unit) order of its list
+    int32_t canon;                     // index of this unit in the (layer, request, kv head, unit) order of its list: for tests and tools
     int32_t ucap;                      // slots of the unit
     int32_t hkv;                       // the row's KV head
     int32_t layer_units;               // units of layer l in this list (every one of them takes a ticket in a launch that appends)
@@ -51,7 +51,6 @@ constexpr int kGatherUnit = 256;        // slots per unit of the gather's list
 struct WorkList {
     WorkItem* items;                   // [cap]
     int32_t* layer_start;              // [L+2]: canon index of each layer's first unit, [L] the number of units, [L+1] the number of u_big units
-    int32_t* row_first;                // [B*L*Hkv]: canon index of each row's first unit
     int32_t u_big, u_small;            // powers of two, u_small <= u_big
     int32_t by_size;                   // items are stored by size class (else in canon order)
     int32_t cap;                       // capacity in units

@@ -240,7 +240,6 @@ __device__ void layout_body(const LayoutArgs& a, CacheDev dev, int lists, int sh
             const int w0 = sFirst[bl] + h * ru.total;
             // units of the third class that precede this row's in the list (all units before it minus big and live)
             const int res0 = n_big + n_live + sResFirst[bl] + h * nres;
-            if (ul == 0 && !heads) wl.row_first[x] = w0;
             // the copies end with the layer's first units: rows behind them are left at once
             const int at = w0 - sFirst[l], n = heads ? min(ru.total, kHeadUnits - at) : ru.total;
             for (int u = ul; u < n; u += 1 << lg) {
