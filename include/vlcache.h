@@ -255,7 +255,7 @@ vlc_status vlc_cache_create_fp8(const vlc_shape* shape, int32_t T_max, int64_t s
  *   decode_zigzag     1: off; 2: a wave walks its tiles backwards on odd steps; 3: also the whole units of a
  *                     size-class walk (what the previous step read last is what the caches still hold)
  *   gather_rows       rows of K and of V one block of the compaction moves: 16, 32, 64 or 128
- *   select_fold       1: the cache layout always runs as a kernel of its own; 2: always inside one more block
+ *   select_fold       1: the cache layout always runs as a kernel of its own; 2: always inside a few more blocks
  *                     of the selection kernel (B * L <= 2048 in either case) */
 typedef struct {
     int32_t kv_fp8;

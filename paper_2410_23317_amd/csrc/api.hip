@@ -396,7 +396,7 @@ static vlc_status cache_layout(const vlc_shape* s, int32_t T_max, int64_t sum_k_
     if (!o.decode_zigzag) o.decode_zigzag = 3;
     if (!o.gather_rows) o.gather_rows = 64;
     {
-        // The layout rides along as one more block of the selection while all rows are resident at once and short
+        // The layout rides along in a few more blocks of the selection while all rows are resident at once and short
         // (m <= 4096), which is where a one-block kernel and its launch gap show.  With more rows the LDS the
         // layout needs would halve the selecting blocks per CU, and with longer rows, whose keys fill the register
         // file, the extra code costs registers (spills at 64 keys per lane).

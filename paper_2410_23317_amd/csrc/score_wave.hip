@@ -159,7 +159,8 @@ __device__ __forceinline__ void load_keys(const char* kg, int key0, int mb, int 
     for (int s = 0; s < KS; ++s) kf[s] = *reinterpret_cast<const uint4*>(base + off + s * 32);
 }
 
-// The block's Q' rows into LDS.  A row that does not exist takes the values of its head's last row, which sees every key:
+// The block's Q' rows into LDS.  A row that does not exist takes the values of a row that does, its head's last one (which sees every
+// key) or, with packed rows, one of the last head's, whose statistics nobody keeps:
 // its products are then the numbers of a row that exists, and drop out by an exponent of -inf (zeros would not: times a
 // key's infinite entry they are NaN).  All requests of a thread are in flight together.
 template <typename F, bool PACKED>

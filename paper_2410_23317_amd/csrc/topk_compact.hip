@@ -696,7 +696,7 @@ hipError_t launch_topk_compact(const vlc_cache& c, const int32_t* lens, const fl
     // every pass visits all register slots (2048 rows of 4099 scores, 9 per lane: 62 us in the form for 24, 45 in this).
     // Rows of 12289 to about 20000 scores leave as many slots of the form for 64 empty; a form between is not built.
     const int per_lane = (((s.m + kSelWaves - 1) / kSelWaves + 63) / 64);
-    // the layout as one more block of the selection (short rows only), or as a kernel of its own
+    // the layout in a few more blocks of the selection (short rows only), or as a kernel of its own
     const bool fold = c.opt.select_fold == 2 && per_lane <= 8;
     if (!fold) layout_kernel<<<kLayoutShares * (own_gather_list(c.dev) ? 4 : 3), 256, 0, st>>>(la, c.dev);
 #define VLC_SELECT(NK) select_kernel<NK, false, false><<<rows, kSelThreads, 0, st>>>(scores, c.dev, s.L, s.Hkv, s.m, lens != nullptr, c.T_max, n_recent, recent_num, recent_den, idx_out, nullptr, nullptr, la)

@@ -251,8 +251,8 @@ WinPlan make_plan(const vlc_shape& s) {
     p.R = g * s.tau;
     const int groups = s.B * s.L * s.Hkv;
     const int chunks = (s.m + kChunk - 1) / kChunk;
-    // Two staged chunks (66 KB of LDS) allow two blocks per compute unit: about one resident round
-    // of blocks per launch, as for the scoring sweeps; a KV group that has a block of its own
+    // Two staged chunks (74 KB of LDS) allow two blocks of four waves per compute unit, the registers one of eight: about one
+    // resident round of the former per launch, as for the scoring sweeps; a KV group that has a block of its own
     // anyway is not split (no partial outputs to merge).
     int ns = (512 + groups - 1) / groups;
     if (ns > chunks) ns = chunks;

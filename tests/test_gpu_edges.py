@@ -514,7 +514,7 @@ def test_rows_that_grow_across_a_unit_boundary_during_decode(unit, merge, order)
 
 
 @pytest.mark.parametrize("fp8", [False, True], ids=["bf16-cache", "fp8-cache"])
-@pytest.mark.parametrize("g,d", [(1, 64), (2, 128), (3, 64), (5, 128), (6, 64), (8, 128)])
+@pytest.mark.parametrize("g,d", [(1, 64), (2, 128), (3, 64), (4, 64), (4, 128), (5, 128), (6, 64), (7, 128), (8, 128)])
 def test_decode_tiles_at_their_edges_for_every_number_of_heads(g, d, fp8):
     """Rows that end just before, on and behind a 32-slot tile and a 128-slot unit, grown over those edges by three
     appends (the appended row is attended over beside the tiles, by the last wave of its unit, which may hold no tile at
@@ -554,7 +554,8 @@ def test_one_layer_with_more_units_than_its_heads_hold():
     kk = np.array([[940, 3, 900], [940, 130, 1], [930, 255, 5], [930, 256, 129], [935, 1, 257], [935, 64, 33]])
     T = 2
     path, dev, caches, scales = _direct_cache(V, cfg, kk, T, dict(layer_unit_slots=128))
-    assert len(_read_list(path, 0, cfg.L)[0]) > 256
+    starts = _read_list(path, 0, cfg.L)[1]
+    assert starts[1] - starts[0] > 256 >= starts[2] - starts[1]      # one layer with more, one with fewer
     out = torch.empty((cfg.L, cfg.B, cfg.Hq, cfg.d), dtype=torch.bfloat16, device="cuda")
     for step in range(T):
         d_host = W.decode_step_inputs(cfg, step)
