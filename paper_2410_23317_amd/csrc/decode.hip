@@ -1039,14 +1039,18 @@ hipError_t launch_decode(const DecodeArgs& a) {
     const int rows = a.n_layers * s.B * s.Hkv;
     // One block per unit.  The budgets, and with them the true number of units, are known on the device only: the grid is
     // the upper bound, every row at the full prompt length and never more than the whole work list, and blocks beyond the
-    // slice leave at once.  Where the bound is beyond eight resident rounds (three blocks per CU) these cost more than the walk does:
-    // a launch over a layer range then gets one resident round, which walks.  us per launch over one layer, 7B shape, covering
-    // grid / walk: 32 prompts of 4096 tokens at 1 % (8448 blocks, 256 to 512 units) 8.7 / 6.3, 64 of 2944 at 1 % (12288) 13.9 / 8.3,
-    // 64 of 2944 at 10 % 27.8 / 26.8; 8 of 32768 at 1 % (a bound of 5504) 7.9 / 8.1, 16 of 2944 at 10 % (3072) 10.1 / 10.3.
+    // slice leave at once.  A launch over a layer range gets one resident round of blocks (three per CU) that walk the units instead
+    // where the blocks to leave are more than eight rounds and cannot hide behind the reads: about 2000 of them come and go
+    // per us, and half of the time that the rows take (5 MB per us) covers them.  us per launch, covering grid / walk, 7B shape: one
+    // layer of 32 prompts of 4096 tokens at 1 % (8448 blocks for 512 units, 5 MB) 8.7 / 6.3, 64 of 2944 at 1 % (12288 for 1024, 8 MB)
+    // 13.9 / 8.3, 128 of 1024 at 1 % (9216 for 2048, 5 MB) 13.6 / 9.9, at 10 % (52 MB) 23.6 / 24.6; two layers of one prompt of 131072
+    // (8208 for 832, 107 MB) 32.1 / 35.2, eight (32832, 430 MB) 97 / 115; 16 layers of 16 prompts of 2944 (49152, 308 MB) 83 / 88.
     int64_t grid = (int64_t)rows * (((int64_t)s.m + c.T_max) / P.wl.u_small + 1);
     if (grid > P.wl.cap) grid = P.wl.cap;
-    const int64_t round = 3 * (int64_t)c.num_cus;
-    const bool walk = !all_layers && grid > 8 * round;
+    const int64_t round = 3 * (int64_t)c.num_cus, mean_row = c.sum_k_max / s.L;
+    const int64_t leave = grid - rows * ((mean_row + c.T_max) / P.wl.u_small + 1);
+    const int64_t bytes = rows * mean_row * 2 * s.d * (c.kv_fp8 ? 1 : s.dtype == VLC_F32 ? 4 : 2);
+    const bool walk = !all_layers && leave > 8 * round && leave > bytes / 5000;
     if (walk) grid = round;
     if (grid < 1) grid = 1;
     const int g = s.Hq / s.Hkv;
