@@ -237,9 +237,9 @@ struct TileMfma {
         for (int e = 0; e < EV; ++e) acc[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
 
-    // The tile that starts at slot t0 (at least one slot of it is there).  Slots that memory does not hold read as zeros.
+    // The tile that starts at slot t0.  Slots that memory does not hold read as zeros, without an access.
     __device__ __forceinline__ void request_k(const RowRefs<bf16_t>& r, int t0, int lane) {
-        const int rows = min(r.held - t0, TK);
+        const int rows = uniform(max(min(r.held - t0, TK), 0));
         const auto kr = slots_buffer(r.K + (int64_t)t0 * RB, rows * RB);
 #pragma unroll
         for (int t = 0; t < 2; ++t)
@@ -255,7 +255,7 @@ struct TileMfma {
         }
     }
     __device__ __forceinline__ void request_v(const RowRefs<bf16_t>& r, int t0, int lane) {
-        const int rows = min(r.held - t0, TK);
+        const int rows = uniform(max(min(r.held - t0, TK), 0));
         const auto vr = slots_buffer(r.V + (int64_t)t0 * RB, rows * RB);
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
@@ -710,14 +710,29 @@ __global__ __launch_bounds__(256, (IsBf16<T>::value ? (D == 64 && !Q8 ? 4 : 3) :
         const int tw0 = key0 + wave * TK;
         const int nt_w = tw0 < lim ? (lim - tw0 + NW * TK - 1) / (NW * TK) : 0;    // tiles of this wave that hold slots
         const bool rev = A.zigzag > 1 && (step & 1);
-        int t0 = tw0 + (rev ? nt_w - 1 : 0) * NW * TK;
+        int t0 = tw0 + (rev && nt_w > 0 ? nt_w - 1 : 0) * NW * TK;
         const int stride = rev ? -NW * TK : NW * TK;
         // the last wave of the unit that holds the new slot (it has the fewest rows) also attends over and stores the new row
         const bool fresh = BF && appending && wave == NW - 1 && new_slot >= key0 && new_slot < key0 + ucap;       // wave-uniform
-        uint4 nk[BF ? D / 32 : 1];
-        uint32_t nv[BF ? D / 32 : 1];
-        uint4 raw_k = make_uint4(0, 0, 0, 0), raw_v = raw_k;
-        if constexpr (BF) {
+        auto request = [&](int at) { tile.request_k(row, at, lane); tile.request_v(row, at, lane); };
+        int ticket = -1;                        // taken when the first tile's rows are on their way
+        if constexpr (!BF) {
+#pragma unroll 1
+            for (int i = nt_w; i > 0; --i, t0 += stride) {      // a tile ahead does not fit the registers
+                request(t0);
+                if (i == nt_w) ticket = take_ticket();          // (wave 0 of a unit that holds slots has a tile)
+                tile.logits(row, t0, lane);
+                tile.outputs(row, t0);
+            }
+        } else if (nt_w > 0 || fresh) {
+            // The new row is requested in front of the first tile, multiplied and stored while that is on its way.  A wave that
+            // attends over the new row alone requests a tile of no bytes: with a test around the request, the compiler would wait
+            // for the new row as if no tile had been requested, which is until the tile is there.  (That and K stored with one
+            // instruction instead of four, us per launch over all layers, rows of 102 to 121 slots: 4096 of them 47.4 -> 38.3,
+            // 16384 206.6 -> 192.2, with one query head 201.5 -> 185.0; launches over one layer of the 7B shape 5.8 -> 5.7.)
+            uint4 nk[D / 32];
+            uint32_t nv[D / 32];
+            uint4 raw_k = make_uint4(0, 0, 0, 0), raw_v = raw_k;
             if (fresh) {
                 if constexpr (Q8) {             // lane c of every D / 8: elements 8 c .. 8 c + 7, to be quantised
                     raw_k = *reinterpret_cast<const uint4*>(row.knew + (lane % (D / 8)) * 8);
@@ -730,16 +745,12 @@ __global__ __launch_bounds__(256, (IsBf16<T>::value ? (D == 64 && !Q8 ? 4 : 3) :
                     for (int w = 0; w < D / 32; ++w) nv[w] = src[w];
                 }
             }
-        }
-        auto request = [&](int at) { tile.request_k(row, at, lane); tile.request_v(row, at, lane); };
-        int ticket = -1;                        // taken when the first tile's rows are on their way
-        if (BF && nt_w > 0) request(t0);
-        if (BF) ticket = take_ticket();
-        if constexpr (BF) {
+            request(t0);
+            ticket = take_ticket();
             if (fresh) {
+                float sk = 0.f, sv = 0.f;
                 char* kdst = const_cast<char*>(row.K) + (int64_t)new_slot * RB;
                 char* vdst = const_cast<char*>(row.V) + (int64_t)new_slot * RB;
-                float sk = 0.f, sv = 0.f;
                 if constexpr (Q8) {
                     constexpr int LPR = D / 8;
                     const uint2 qk = quantize_row_e4m3<LPR>(raw_k, sk), qv = quantize_row_e4m3<LPR>(raw_v, sv);
@@ -766,10 +777,11 @@ __global__ __launch_bounds__(256, (IsBf16<T>::value ? (D == 64 && !Q8 ? 4 : 3) :
                         nv[0] = lane & 1 ? w2 : w0; nv[1] = lane & 1 ? w3 : w1;
                     }
                 } else {
-                    if ((lane & 15) == 0) {
+                    // lane c of every 16 stores the piece of k-step c that its group holds: the whole row in one instruction
+                    uint4 piece = nk[0];
 #pragma unroll
-                        for (int k = 0; k < D / 32; ++k) *reinterpret_cast<uint4*>(kdst + 2 * Tile::k_elem(k, lane >> 4)) = nk[k];
-                    }
+                    for (int k = 1; k < D / 32; ++k) if ((lane & 15) == k) piece = nk[k];
+                    if ((lane & 15) < D / 32) *reinterpret_cast<uint4*>(kdst + 2 * Tile::k_elem(lane & 15, lane >> 4)) = piece;
                     if (lane < 16) {
 #pragma unroll
                         for (int w = 0; w < D / 32; ++w) reinterpret_cast<uint32_t*>(vdst)[lane * (D / 32) + w] = nv[w];
@@ -778,17 +790,15 @@ __global__ __launch_bounds__(256, (IsBf16<T>::value ? (D == 64 && !Q8 ? 4 : 3) :
                 if (lane == 0) A.idx[idx_base + new_slot] = A.m + appended;
                 tile.add_new(row, nk, nv, sk, sv, lane);
             }
-        }
 #pragma unroll 1
-        for (int i = nt_w; i > 0; --i, t0 += stride) {
-            if (!BF) {                          // fp32: a tile ahead does not fit the registers
-                request(t0);
-                if (i == nt_w) ticket = take_ticket();      // (wave 0 of a unit that holds slots has a tile)
+            for (int i = nt_w; i > 0; --i, t0 += stride) {
+                tile.logits(row, t0, lane);
+                if (i > 1) tile.request_k(row, t0 + stride, lane);
+                tile.outputs(row, t0);
+                if (i > 1) tile.request_v(row, t0 + stride, lane);
             }
-            tile.logits(row, t0, lane);
-            if (BF && i > 1) tile.request_k(row, t0 + stride, lane);
-            tile.outputs(row, t0);
-            if (BF && i > 1) tile.request_v(row, t0 + stride, lane);
+        } else {
+            ticket = take_ticket();
         }
 
         // fp32 storage: the unit that holds the new slot also stores the new row into the cache
