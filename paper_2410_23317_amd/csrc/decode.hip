@@ -790,12 +790,21 @@ __global__ __launch_bounds__(256, (IsBf16<T>::value ? (D == 64 && !Q8 ? 4 : 3) :
                 if (lane == 0) A.idx[idx_base + new_slot] = A.m + appended;
                 tile.add_new(row, nk, nv, sk, sv, lane);
             }
+            // The last tile stands behind the loop, so that the requests in the loop have no test and every wait is for what it
+            // needs: the logits for K, the outputs for V.  Launches over several layers wait for V in front of the logits all
+            // the same, which keeps K of the next tile behind it: batch of four of 10368 tokens, all layers, 103.5 us, without
+            // that wait 107.2 (launches over one layer of it 10.0, with it 10.2; of one FP8 prompt of 32768 tokens 8.0 and 8.3).
 #pragma unroll 1
-            for (int i = nt_w; i > 0; --i, t0 += stride) {
+            for (int i = nt_w; i > 1; --i, t0 += stride) {
+                if (!A.heads) __builtin_amdgcn_s_waitcnt(0x0f70);       // vmcnt(0)
                 tile.logits(row, t0, lane);
-                if (i > 1) tile.request_k(row, t0 + stride, lane);
+                tile.request_k(row, t0 + stride, lane);
                 tile.outputs(row, t0);
-                if (i > 1) tile.request_v(row, t0 + stride, lane);
+                tile.request_v(row, t0 + stride, lane);
+            }
+            if (nt_w > 0) {
+                tile.logits(row, t0, lane);
+                tile.outputs(row, t0);
             }
         } else {
             ticket = take_ticket();
