@@ -32,8 +32,8 @@ MFMA_BF16_PEAK_FLOPS = 2.5e15
 # counter reads for a plain 256 MiB copy), measured offline on the default run of a config: 10 % budget,
 # 100 decode steps.  The figures and the commands are in profiles/all_kernels_cfg*.md; TRAFFIC_MEASURED_AT names
 # the commit whose decode kernel they were measured on (a test checks that the constants match the profiles).
-MEASURED_DECODE_TRAFFIC_MIB = {1: 44.98 + 1.18, 2: 546.19 + 2.11}
-TRAFFIC_MEASURED_AT = "14f7594"
+MEASURED_DECODE_TRAFFIC_MIB = {1: 44.97 + 1.18, 2: 546.63 + 2.11}
+TRAFFIC_MEASURED_AT = "74d400e"
 
 
 def options_from_args(V, args):
